@@ -495,7 +495,12 @@ lxw_status ensure_init() {
   fill_tab(t->line3_d); fill_tab(t->line3_f);
   fill_tab(t->tri3_d); fill_tab(t->tri3_f);
   fill_tab(t->tet_d); fill_tab(t->tet_f);
-  hipError_t e = upload_tables(*t);
+  hipError_t e = upload_tables<ElLine>(t->line_d, t->line_f);
+  if (e == hipSuccess) e = upload_tables<ElQuad>(t->quad_d, t->quad_f);
+  if (e == hipSuccess) e = upload_tables<ElTri>(t->tri_d, t->tri_f);
+  if (e == hipSuccess) e = upload_tables<ElLine3>(t->line3_d, t->line3_f);
+  if (e == hipSuccess) e = upload_tables<ElTri3>(t->tri3_d, t->tri3_f);
+  if (e == hipSuccess) e = upload_tables<ElTet>(t->tet_d, t->tet_f);
   if (e != hipSuccess) {
     g_init_state = -1;
     return fail(LXW_ERR_DEVICE, std::string("uploading reference tables: ") + hipGetErrorString(e));
@@ -796,8 +801,11 @@ struct lxw_solver {
   std::vector<DevBuf> bufs;
   View<double> vd{};
   View<float> vf{};
-  Scalars* sc = nullptr;
-  DevError* err = nullptr;
+  Scalars* sc = nullptr;       // [n_mesh], followed by *tail
+  DevTail* tail = nullptr;
+  int* perm = nullptr;         // [N] internal -> caller element (state transfer)
+  double* stage = nullptr;     // staging buffer of states in host memory
+  size_t stage_bytes = 0;
   Scalars hsc{};
   bool debug = false;
   // diagnostics copies
@@ -833,6 +841,7 @@ struct lxw_solver {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (cap) (void)hipStreamDestroy(cap);
     for (auto& b : bufs) if (b.p) (void)hipFree(b.p);
+    if (stage) (void)hipFree(stage);
     for (auto& e : ev_pool) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   }
   template <class T>
@@ -954,7 +963,7 @@ lxw_status setup_view(lxw_solver* S, View<R>& v) {
     HIPCHK(hipMemcpy(v.cedge, ones.data(), ones.size() * sizeof(double), hipMemcpyHostToDevice));
   }
   v.sc = S->sc;
-  v.err = S->err;
+  v.err = &S->tail->err;
   v.gamma = S->P.gamma;
   v.eps0 = S->P.eps0;
   for (int c = 0; c < 4; ++c) v.inflow[c] = S->P.inflow[c];
@@ -1086,11 +1095,15 @@ lxw_status sync_check(lxw_solver* S) {
     }
     S->ev_used = 0;
   }
+  // the meshes' scalars and the error record behind them in one copy
+  S->hscv.resize(S->n_mesh + 1);
+  static_assert(sizeof(DevTail) <= sizeof(Scalars), "the record behind the scalars fits one more of them");
+  HIPCHK(hipMemcpy(S->hscv.data(), S->sc, S->n_mesh * sizeof(Scalars) + sizeof(DevTail), hipMemcpyDeviceToHost));
+  DevTail tail{};
+  std::memcpy(&tail, &S->hscv[S->n_mesh], sizeof tail);
   S->hscv.resize(S->n_mesh);
-  HIPCHK(hipMemcpy(S->hscv.data(), S->sc, S->n_mesh * sizeof(Scalars), hipMemcpyDeviceToHost));
   S->hsc = S->hscv[0];
-  DevError de{};
-  HIPCHK(hipMemcpy(&de, S->err, sizeof(DevError), hipMemcpyDeviceToHost));
+  const DevError de = tail.err;
   if (de.code != 0) {
     const int caller = (de.elem >= 0 && de.elem < S->M->N) ? S->M->perm[de.elem] : -1;
     const char* what = de.code == LXW_ERR_CFL ? "Lax-Friedrichs update not positive: time step too large"
@@ -1104,58 +1117,84 @@ lxw_status sync_check(lxw_solver* S) {
       snprintf(buf, sizeof buf, "%s (element %d, t = %.17g)", what, caller, S->hsc.t);
     }
     DevError z{};
-    HIPCHK(hipMemcpy(S->err, &z, sizeof(DevError), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(&S->tail->err, &z, sizeof(DevError), hipMemcpyHostToDevice));
     return fail(de.code, buf);
   }
   return LXW_OK;
 }
 
-// Checks a caller state of mesh Mloc (rho_bar >= eps0, p_bar > 0, finite) and uploads it, in the
-// internal order, into elements [off, off + Mloc.N) of the solver's state.
+// Rows of the caller's array that one piece of a state in host memory holds: the staging buffer is at
+// most 64 MiB (a state above that goes through it in pieces, so that the solver's device memory stays
+// that of the step).
+int stage_rows(const lxw_mesh& Mloc) {
+  const size_t row = (size_t)Mloc.V * Mloc.ML * sizeof(double);
+  return (int)std::min<size_t>((size_t)Mloc.N, std::max<size_t>(1, ((size_t)64 << 20) / row));
+}
+
+// Staging buffer of `bytes` for states in host memory (kept with the solver, grown when a larger mesh
+// of a batch needs it).
+lxw_status staging(lxw_solver* S, size_t bytes, double** out) {
+  if (S->stage_bytes < bytes) {
+    if (S->stage) HIPCHK(hipFree(S->stage));
+    S->stage = nullptr;
+    S->stage_bytes = 0;
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess) return fail(LXW_ERR_OOM, std::string("device allocation failed: ") + hipGetErrorString(e));
+    S->stage = (double*)p;
+    S->stage_bytes = bytes;
+  }
+  *out = S->stage;
+  return LXW_OK;
+}
+
+// Checks a caller state of mesh Mloc (rho_bar >= eps0, p_bar > 0, finite) and brings it, in the
+// internal order, into elements [off, off + Mloc.N) of the solver's state.  A state that fails the
+// check changes nothing.
 lxw_status load_state(lxw_solver* S, const lxw_mesh& Mloc, int off, const double* Q, int32_t flags) {
-  const int N = Mloc.N, V = Mloc.V, ML = Mloc.ML, dim = Mloc.dim, Nt = S->M->N;
-  const size_t n = (size_t)N * V * ML;
-  std::vector<double> h(n);
+  const int N = Mloc.N, V = Mloc.V, ML = Mloc.ML, Nt = S->M->N;
+  const size_t row = (size_t)V * ML;
+  // device memory of the caller may have been written by work on the default stream
+  HIPCHK(hipStreamSynchronize(nullptr));
   HIPCHK(hipStreamSynchronize(S->st));
-  if (flags & LXW_DEVICE_PTR) {
-    HIPCHK(hipMemcpy(h.data(), Q, n * sizeof(double), hipMemcpyDeviceToHost));
-  } else {
-    std::memcpy(h.data(), Q, n * sizeof(double));
+  const bool dev = (flags & LXW_DEVICE_PTR) != 0;
+  const int rows = dev ? N : stage_rows(Mloc);
+  double* buf = nullptr;
+  if (!dev) {
+    lxw_status s = staging(S, (size_t)rows * row * sizeof(double), &buf);
+    if (s) return s;
   }
-  for (int c = 0; c < N && !(flags & LXW_STATE_UNCHECKED); ++c) {
-    const double* q = &h[(size_t)c * V * ML];
-    double qb[4];
-    bool fin = true;
-    for (int v = 0; v < V; ++v) { qb[v] = q[v * ML]; for (int l = 0; l < ML; ++l) fin = fin && std::isfinite(q[v * ML + l]); }
-    double k = 0.0;
-    for (int d = 0; d < dim; ++d) k += qb[1 + d] * qb[1 + d];
-    const double pb = (S->P.gamma - 1.0) * (qb[V - 1] - 0.5 * k / qb[0]);
-    if (!fin || !(qb[0] >= S->P.eps0) || !(pb > 0.0)) {
-      char buf[160];
-      snprintf(buf, sizeof buf, "initial state violates rho_bar >= eps0, p_bar > 0 or is not finite (element %d)", c);
-      return fail(LXW_ERR_STATE, buf);
+  int staged = -1;  // first row the staging buffer holds
+  auto piece = [&](int c0, int n) -> hipError_t {
+    if (dev || staged == c0) return hipSuccess;
+    staged = c0;
+    return hipMemcpyAsync(buf, Q + (size_t)c0 * row, (size_t)n * row * sizeof(double), hipMemcpyHostToDevice, S->st);
+  };
+  if (!(flags & LXW_STATE_UNCHECKED)) {
+    for (int c0 = 0; c0 < N; c0 += rows) {
+      const int n = std::min(rows, N - c0);
+      HIPCHK(piece(c0, n));
+      HIPCHK(launch_check(dev ? Q : buf, c0, n, V, ML, S->P.gamma - 1.0, S->P.eps0, &S->tail->bad, S->st));
+    }
+    HIPCHK(hipStreamSynchronize(S->st));
+    int bad = 0;
+    const int none = INT32_MAX;
+    HIPCHK(hipMemcpy(&bad, &S->tail->bad, sizeof bad, hipMemcpyDeviceToHost));
+    if (bad != none) {
+      HIPCHK(hipMemcpy(&S->tail->bad, &none, sizeof none, hipMemcpyHostToDevice));
+      char msg[160];
+      snprintf(msg, sizeof msg, "initial state violates rho_bar >= eps0, p_bar > 0 or is not finite (element %d)", bad);
+      return fail(LXW_ERR_STATE, msg);
     }
   }
-  std::vector<double> qbar((size_t)V * N);  // [N][V]
-  std::vector<double> qh((size_t)V * (ML - 1) * N);
-  for (int i = 0; i < N; ++i) {
-    const double* q = &h[(size_t)Mloc.perm[i] * V * ML];
-    for (int v = 0; v < V; ++v) {
-      qbar[(size_t)i * V + v] = q[v * ML];
-      for (int l = 1; l < ML; ++l) qh[((size_t)v * (ML - 1) + l - 1) * N + i] = q[v * ML + l];
-    }
+  for (int c0 = 0; c0 < N; c0 += rows) {
+    const int n = std::min(rows, N - c0);
+    HIPCHK(piece(c0, n));
+    const double* src = dev ? Q : buf;
+    if (S->fp32) HIPCHK(launch_import<float>(src, c0, c0 + n, S->perm, off, N, V, ML, Nt, S->vf.Qbar, S->vf.Qh, S->st));
+    else HIPCHK(launch_import<double>(src, c0, c0 + n, S->perm, off, N, V, ML, Nt, S->vd.Qbar, S->vd.Qh, S->st));
   }
-  double* dbar = S->fp32 ? S->vf.Qbar : S->vd.Qbar;
-  HIPCHK(hipMemcpy(dbar + (size_t)off * V, qbar.data(), qbar.size() * sizeof(double), hipMemcpyHostToDevice));
-  const int rows = V * (ML - 1);
-  if (S->fp32) {
-    std::vector<float> f(qh.begin(), qh.end());
-    for (int r = 0; r < rows; ++r)
-      HIPCHK(hipMemcpy(S->vf.Qh + (size_t)r * Nt + off, &f[(size_t)r * N], N * sizeof(float), hipMemcpyHostToDevice));
-  } else {
-    for (int r = 0; r < rows; ++r)
-      HIPCHK(hipMemcpy(S->vd.Qh + (size_t)r * Nt + off, &qh[(size_t)r * N], N * sizeof(double), hipMemcpyHostToDevice));
-  }
+  HIPCHK(hipStreamSynchronize(S->st));
   return LXW_OK;
 }
 
@@ -1174,31 +1213,26 @@ lxw_status reset_scalars(lxw_solver* S, int b, double t0) {
   return LXW_OK;
 }
 
-// Device state of elements [off, off + Mloc.N) -> caller layout of mesh Mloc (float64).
-lxw_status store_state(lxw_solver* S, const lxw_mesh& Mloc, int off, bool upd_copy, std::vector<double>& out) {
+// State of elements [off, off + Mloc.N) in the caller layout of mesh Mloc (float64) to Q.
+lxw_status store_state(lxw_solver* S, const lxw_mesh& Mloc, int off, double* Q, int32_t flags) {
   const int N = Mloc.N, V = Mloc.V, ML = Mloc.ML, Nt = S->M->N;
-  std::vector<double> qbar((size_t)V * N), qh((size_t)V * (ML - 1) * N);
-  const double* src_bar = upd_copy ? S->dq_upd_bar : (S->fp32 ? S->vf.Qbar : S->vd.Qbar);
-  const char* src_h = (const char*)(upd_copy ? S->dq_upd_h : (S->fp32 ? (const void*)S->vf.Qh : (const void*)S->vd.Qh));
-  HIPCHK(hipMemcpy(qbar.data(), src_bar + (size_t)off * V, qbar.size() * sizeof(double), hipMemcpyDeviceToHost));
-  const int rows = V * (ML - 1);
-  if (S->fp32) {
-    std::vector<float> f(qh.size());
-    for (int r = 0; r < rows; ++r)
-      HIPCHK(hipMemcpy(&f[(size_t)r * N], src_h + ((size_t)r * Nt + off) * sizeof(float), N * sizeof(float), hipMemcpyDeviceToHost));
-    for (size_t x = 0; x < f.size(); ++x) qh[x] = f[x];
-  } else {
-    for (int r = 0; r < rows; ++r)
-      HIPCHK(hipMemcpy(&qh[(size_t)r * N], src_h + ((size_t)r * Nt + off) * sizeof(double), N * sizeof(double), hipMemcpyDeviceToHost));
+  const size_t row = (size_t)V * ML;
+  const bool dev = (flags & LXW_DEVICE_PTR) != 0;
+  const int rows = dev ? N : stage_rows(Mloc);
+  double* buf = nullptr;
+  if (!dev) {
+    lxw_status s = staging(S, (size_t)rows * row * sizeof(double), &buf);
+    if (s) return s;
   }
-  out.assign((size_t)N * V * ML, 0.0);
-  for (int i = 0; i < N; ++i) {
-    double* q = &out[(size_t)Mloc.perm[i] * V * ML];
-    for (int v = 0; v < V; ++v) {
-      q[v * ML] = qbar[(size_t)i * V + v];
-      for (int l = 1; l < ML; ++l) q[v * ML + l] = qh[((size_t)v * (ML - 1) + l - 1) * N + i];
-    }
+  for (int c0 = 0; c0 < N; c0 += rows) {
+    const int n = std::min(rows, N - c0);
+    double* dst = dev ? Q : buf;
+    if (S->fp32) HIPCHK(launch_export<float>(dst, c0, c0 + n, S->perm, off, N, V, ML, Nt, S->vf.Qbar, S->vf.Qh, S->st));
+    else HIPCHK(launch_export<double>(dst, c0, c0 + n, S->perm, off, N, V, ML, Nt, S->vd.Qbar, S->vd.Qh, S->st));
+    if (!dev)
+      HIPCHK(hipMemcpyAsync(Q + (size_t)c0 * row, buf, (size_t)n * row * sizeof(double), hipMemcpyDeviceToHost, S->st));
   }
+  HIPCHK(hipStreamSynchronize(S->st));
   return LXW_OK;
 }
 
@@ -1347,12 +1381,15 @@ lxw_status create_solver(const lxw_mesh* m, const lxw_params* p, void* stream, B
     S->eoff = {0, m->N};
     S->geo_m = {m->geo};
   }
-  if ((s = S->alloc(&S->sc, S->n_mesh))) return s;
-  if ((s = S->alloc(&S->err, 1))) return s;
+  if ((s = S->alloc(&S->sc, S->n_mesh + 1))) return s;
+  S->tail = reinterpret_cast<DevTail*>(S->sc + S->n_mesh);
   for (int b = 0; b < S->n_mesh; ++b)
     if ((s = reset_scalars(S.get(), b, 0.0))) return s;
-  DevError ze{};
-  HIPCHK(hipMemcpy(S->err, &ze, sizeof ze, hipMemcpyHostToDevice));
+  const DevTail tail0{{0, 0}, INT32_MAX};
+  HIPCHK(hipMemcpy(S->tail, &tail0, sizeof tail0, hipMemcpyHostToDevice));
+  const int* perm = nullptr;
+  if ((s = upload(S.get(), &perm, m->perm))) return s;
+  S->perm = const_cast<int*>(perm);
   if (S->fp32) s = setup_view<float>(S.get(), S->vf);
   else s = setup_view<double>(S.get(), S->vd);
   if (s) return s;
@@ -1867,7 +1904,7 @@ lxw_status lxw_set_state(lxw_solver* S, const double* Q, double t0, int32_t flag
   if (s) return s;
   if ((s = reset_scalars(S, 0, t0))) return s;
   DevError ze{};
-  HIPCHK(hipMemcpy(S->err, &ze, sizeof ze, hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(&S->tail->err, &ze, sizeof ze, hipMemcpyHostToDevice));
   return LXW_OK;
 }
 
@@ -1880,14 +1917,7 @@ lxw_status lxw_get_state(lxw_solver* S, double* Q, double* t, int32_t flags) {
     if ((s = enqueue_shock(S))) return s;
     if ((s = sync_check(S))) return s;
   }
-  std::vector<double> h;
-  if ((s = store_state(S, *S->M, 0, false, h))) return s;
-  if (flags & LXW_DEVICE_PTR) {
-    HIPCHK(hipMemcpyAsync(Q, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, S->st));
-    HIPCHK(hipStreamSynchronize(S->st));
-  } else {
-    std::memcpy(Q, h.data(), h.size() * sizeof(double));
-  }
+  if ((s = store_state(S, *S->M, 0, Q, flags))) return s;
   if (t) *t = S->hsc.t;
   return LXW_OK;
 }
@@ -2273,13 +2303,7 @@ lxw_status lxw_batch_get_state(lxw_batch* B, int32_t i, double* Q, double* t, in
     if ((s = enqueue_shock(S))) return s;
     if ((s = sync_check(S))) return s;
   }
-  std::vector<double> h;
-  if ((s = store_state(S, *B->ms[i], S->eoff[i], false, h))) return s;
-  if (flags & LXW_DEVICE_PTR) {
-    HIPCHK(hipMemcpy(Q, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
-  } else {
-    std::memcpy(Q, h.data(), h.size() * sizeof(double));
-  }
+  if ((s = store_state(S, *B->ms[i], S->eoff[i], Q, flags))) return s;
   if (t) *t = S->hscv[i].t;
   return LXW_OK;
 }

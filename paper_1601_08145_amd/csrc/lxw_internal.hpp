@@ -87,6 +87,12 @@ struct DevError {
   int elem;
 };
 
+// Behind the meshes' scalars, so that one copy brings both to the host.
+struct DevTail {
+  DevError err;
+  int bad;  // first element of a caller's state that fails its check (INT32_MAX: none)
+};
+
 // Boundary codes stored in an element's edge slot (slot = edge*8 + side*4 + bc).
 enum { SB_INTERIOR = 0, SB_TRANSPARENT = 1, SB_REFLECTIVE = 2, SB_INFLOW = 3 };
 
@@ -183,7 +189,8 @@ struct HostTabs {
 static_assert(sizeof(HostTabs) <= 256 * 1024, "reference tables larger than intended");
 
 // ---- host-side launchers implemented in lxw_kernels.hip -----------------------------------
-hipError_t upload_tables(const HostTabs& t);
+template <class E>
+hipError_t upload_tables(const RefTab<E, double>& d, const RefTab<E, float>& f);
 // End time of every mesh (stream-ordered): steps are clipped to reach it and change nothing after.
 hipError_t launch_set_end(Scalars* sc, int n_mesh, double T, hipStream_t st);
 
@@ -209,6 +216,18 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
 // lanes (64, 128 or 256), as many as stay resident together; same results as the separate kernels.
 template <class E, class R>
 hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mesh, int n_steps);
+
+// ---- state transfer (lxw_state.hip) -----------------------------------------------------------
+// Rows [c0, c1) of a caller's array Q[.][V][ML] (row c0 at Q) to and from elements off .. off + n of a
+// solver of Nt elements, where element off + i is the caller's perm[off + i] - off.
+template <class R>
+hipError_t launch_import(const double* Q, int c0, int c1, const int* perm, int off, int n, int V, int ML, int Nt,
+                         double* Qbar, R* Qh, hipStream_t st);
+template <class R>
+hipError_t launch_export(double* Q, int c0, int c1, const int* perm, int off, int n, int V, int ML, int Nt,
+                         const double* Qbar, const R* Qh, hipStream_t st);
+// The smallest c0 + index of the n rows at Q whose state is not a valid start, into *bad (minimum).
+hipError_t launch_check(const double* Q, int c0, int n, int V, int ML, double gm1, double eps0, int* bad, hipStream_t st);
 
 // ---- learned troubled-cell indicator (lxw_indicator.hip) ------------------------------------
 // Network 48 -> 64 (ReLU) -> 64 (ReLU) -> 1 (sigmoid); flat FP32 parameters W1[48][64], b1[64],

@@ -33,48 +33,37 @@
 
 namespace lxw {
 
-__constant__ RefTab<ElLine, double> c_line_d;
-__constant__ RefTab<ElLine, float> c_line_f;
-__constant__ RefTab<ElQuad, double> c_quad_d;
-__constant__ RefTab<ElQuad, float> c_quad_f;
-__constant__ RefTab<ElTri, double> c_tri_d;
-__constant__ RefTab<ElTri, float> c_tri_f;
-__constant__ RefTab<ElLine3, double> c_line3_d;
-__constant__ RefTab<ElLine3, float> c_line3_f;
-__constant__ RefTab<ElTri3, double> c_tri3_d;
-__constant__ RefTab<ElTri3, float> c_tri3_f;
-__constant__ RefTab<ElTet, double> c_tet_d;
-__constant__ RefTab<ElTet, float> c_tet_f;
+// This file is compiled once per element configuration (LXW_PART, see build.py), side by side: each
+// object holds that configuration's kernels in both precisions and its two reference tables.
+#ifndef LXW_PART
+#error "LXW_PART selects the element configuration: 0 line, 1 quad, 2 triangle, 3 P3 line, 4 P3 triangle, 5 tetrahedron"
+#endif
+#if LXW_PART == 0
+using EL = ElLine;
+#elif LXW_PART == 1
+using EL = ElQuad;
+#elif LXW_PART == 2
+using EL = ElTri;
+#elif LXW_PART == 3
+using EL = ElLine3;
+#elif LXW_PART == 4
+using EL = ElTri3;
+#else
+using EL = ElTet;
+#endif
+
+static __constant__ RefTab<EL, double> c_tab_d;
+static __constant__ RefTab<EL, float> c_tab_f;
 
 template <class E, class R>
 struct TabSel;
-template <> struct TabSel<ElLine, double> { static __device__ __forceinline__ const RefTab<ElLine, double>& get() { return c_line_d; } };
-template <> struct TabSel<ElLine, float> { static __device__ __forceinline__ const RefTab<ElLine, float>& get() { return c_line_f; } };
-template <> struct TabSel<ElQuad, double> { static __device__ __forceinline__ const RefTab<ElQuad, double>& get() { return c_quad_d; } };
-template <> struct TabSel<ElQuad, float> { static __device__ __forceinline__ const RefTab<ElQuad, float>& get() { return c_quad_f; } };
-template <> struct TabSel<ElTri, double> { static __device__ __forceinline__ const RefTab<ElTri, double>& get() { return c_tri_d; } };
-template <> struct TabSel<ElTri, float> { static __device__ __forceinline__ const RefTab<ElTri, float>& get() { return c_tri_f; } };
-template <> struct TabSel<ElLine3, double> { static __device__ __forceinline__ const RefTab<ElLine3, double>& get() { return c_line3_d; } };
-template <> struct TabSel<ElLine3, float> { static __device__ __forceinline__ const RefTab<ElLine3, float>& get() { return c_line3_f; } };
-template <> struct TabSel<ElTri3, double> { static __device__ __forceinline__ const RefTab<ElTri3, double>& get() { return c_tri3_d; } };
-template <> struct TabSel<ElTri3, float> { static __device__ __forceinline__ const RefTab<ElTri3, float>& get() { return c_tri3_f; } };
-template <> struct TabSel<ElTet, double> { static __device__ __forceinline__ const RefTab<ElTet, double>& get() { return c_tet_d; } };
-template <> struct TabSel<ElTet, float> { static __device__ __forceinline__ const RefTab<ElTet, float>& get() { return c_tet_f; } };
+template <> struct TabSel<EL, double> { static __device__ __forceinline__ const RefTab<EL, double>& get() { return c_tab_d; } };
+template <> struct TabSel<EL, float> { static __device__ __forceinline__ const RefTab<EL, float>& get() { return c_tab_f; } };
 
-hipError_t upload_tables(const HostTabs& t) {
-  hipError_t e = hipSuccess;
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_line_d), &t.line_d, sizeof(t.line_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_line_f), &t.line_f, sizeof(t.line_f));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_quad_d), &t.quad_d, sizeof(t.quad_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_quad_f), &t.quad_f, sizeof(t.quad_f));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tri_d), &t.tri_d, sizeof(t.tri_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tri_f), &t.tri_f, sizeof(t.tri_f));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_line3_d), &t.line3_d, sizeof(t.line3_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_line3_f), &t.line3_f, sizeof(t.line3_f));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tri3_d), &t.tri3_d, sizeof(t.tri3_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tri3_f), &t.tri3_f, sizeof(t.tri3_f));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tet_d), &t.tet_d, sizeof(t.tet_d));
-  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tet_f), &t.tet_f, sizeof(t.tet_f));
+template <>
+hipError_t upload_tables<EL>(const RefTab<EL, double>& d, const RefTab<EL, float>& f) {
+  hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab_d), &d, sizeof(d));
+  if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_tab_f), &f, sizeof(f));
   return e;
 }
 
@@ -797,7 +786,7 @@ __global__ __launch_bounds__(256) void k_pre(View<R> v) {
 // k_dt: per mesh, dt from the CFL condition (reading of Sec. 4.1, "CFL 0.08"), clipped to T.
 // ---------------------------------------------------------------------------------------------
 // Single mesh: one workgroup of 1024 lanes reduces the per-workgroup maxima of k_pre.
-__global__ __launch_bounds__(1024) void k_dt_single(Scalars* sc, DevError* err, const double* spart, int nparts) {
+static __global__ __launch_bounds__(1024) void k_dt_single(Scalars* sc, DevError* err, const double* spart, int nparts) {
   __shared__ double red[16];
   double x = 0.0;
   for (int b = threadIdx.x; b < nparts; b += blockDim.x) x = fmax(x, spart[b]);
@@ -838,7 +827,7 @@ __device__ __forceinline__ void dt_mesh(Scalars* sc, DevError* err, const int m)
   S.dt = dt;
 }
 
-__global__ void k_dt(Scalars* sc, DevError* err, int n_mesh) {
+static __global__ void k_dt(Scalars* sc, DevError* err, int n_mesh) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m < n_mesh) dt_mesh(sc, err, m);
 }
@@ -2014,6 +2003,7 @@ hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mes
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)nb), dim3((unsigned)bs), args, 0, st);
 }
 
+#if LXW_PART == 0
 // Sets the end time of every mesh (a kernel, so that it is ordered on the stream and may be
 // captured).
 __global__ void k_set_end(Scalars* sc, int n_mesh, double T) {
@@ -2025,10 +2015,11 @@ hipError_t launch_set_end(Scalars* sc, int n_mesh, double T, hipStream_t st) {
   hipLaunchKernelGGL(k_set_end, dim3((unsigned)((n_mesh + 63) / 64)), dim3(64), 0, st, sc, n_mesh, T);
   return hipGetLastError();
 }
+#endif
 
 // k_final: marks the pending shock-capturing limiter as applied (after a state read-out applied
 // it).
-__global__ void k_final(Scalars* sc, int n_mesh) {
+static __global__ void k_final(Scalars* sc, int n_mesh) {
   const int m = blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= n_mesh) return;
   sc[m].shock_pending = 0;
@@ -2086,23 +2077,11 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
   return hipGetLastError();
 }
 
-template hipError_t launch_persistent<ElLine, double>(const View<double>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<ElLine, float>(const View<float>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<ElQuad, double>(const View<double>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<ElQuad, float>(const View<float>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<ElTri, double>(const View<double>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<ElTri, float>(const View<float>&, int, hipStream_t, int, int);
-template hipError_t launch<ElLine, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElLine, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElQuad, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElQuad, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTri, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTri, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElLine3, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElLine3, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTri3, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTri3, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTet, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
-template hipError_t launch<ElTet, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
+template hipError_t launch<EL, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
+template hipError_t launch<EL, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
+#if LXW_PART < 3
+template hipError_t launch_persistent<EL, double>(const View<double>&, int, hipStream_t, int, int);
+template hipError_t launch_persistent<EL, float>(const View<float>&, int, hipStream_t, int, int);
+#endif
 
 }  // namespace lxw

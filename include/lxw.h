@@ -274,6 +274,8 @@ lxw_status lxw_sync(lxw_solver* s);
  *   LXW_STAGE_SDT      {s, dt} [2]
  * Per-kernel timing: lxw_set_timing(s, 1) records HIP events around every kernel of later steps;
  * lxw_kernel_times returns, per kernel id (LXW_K_*), the summed milliseconds and launch counts.
+ * LXW_K_EDGE is the kernel of the edge fluxes, the flux limiter and the higher moments' edge terms (one
+ * lane per element); LXW_K_FLIM launches nothing (its work is in LXW_K_EDGE).
  * A step ends inside the LXW_K_UPDATE kernel; LXW_K_FINAL counts only the kernel that closes a
  * state read-out which applied the pending shock-capturing limiter. */
 enum {
@@ -289,15 +291,15 @@ lxw_status lxw_set_timing(lxw_solver* s, int32_t enable);
 lxw_status lxw_kernel_times(lxw_solver* s, double* ms /*[LXW_K_COUNT]*/, int64_t* launches /*[LXW_K_COUNT]*/);
 
 /* ---- Launch shapes and the autotuner --------------------------------------------------------
- * Every element kernel runs one lane per element and the edge kernel one lane per edge, so the
- * workgroup size block[k] of kernel k (indexed by LXW_K_*) is also its number of elements (edges)
- * per workgroup.  LXW_K_PRE, LXW_K_ELEM, LXW_K_EDGE, LXW_K_FLIM and LXW_K_UPDATE accept 64, 128 or
- * 256 (defaults 256, 128, 256, 256, 256); the entries of LXW_K_DT, LXW_K_FINAL and LXW_K_IND are
+ * Every element kernel runs one lane per element, so the workgroup size block[k] of kernel k
+ * (indexed by LXW_K_*) is also its number of elements per workgroup.  LXW_K_PRE, LXW_K_ELEM,
+ * LXW_K_EDGE, LXW_K_FLIM and LXW_K_UPDATE accept 64, 128 or 256 (defaults 256, 128, 256, 256, 256); the
+ * entry of LXW_K_FLIM is kept and has no effect, those of LXW_K_DT, LXW_K_FINAL and LXW_K_IND are
  * ignored.
  * persistent (batches of triangle meshes only): 0 (default) runs a step as one launch per phase,
  * replayed from a HIP graph; 128 or 256 runs lxw_batch_advance_steps as one cooperative launch of a
  * persistent kernel (up to 1024 steps per launch) whose workgroups of that many lanes stay resident
- * and run every phase of every step over tiles of elements and edges, with grid-wide barriers where
+ * and run every phase of every step over tiles of elements, with grid-wide barriers where
  * the per-phase launches have kernel boundaries.  It applies while per-kernel timing, stage
  * read-out and the learned indicator are off (the per-phase launches run otherwise).
  * Launch shapes change no result bit. */

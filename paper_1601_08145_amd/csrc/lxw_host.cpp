@@ -809,6 +809,7 @@ struct lxw_solver {
   Scalars hsc{};
   bool debug = false;
   // diagnostics copies
+  double *dfw = nullptr, *dff = nullptr;  // [E][V] fluxes
   double* dq_upd_bar = nullptr;
   void* dq_upd_h = nullptr;
   // timing
@@ -824,7 +825,7 @@ struct lxw_solver {
   int n_mesh = 1;
   bool batch = false;
   std::vector<int> eoff{0, 0};
-  std::vector<int> mesh_of, e_mesh;  // host copies uploaded by setup_view (batched form only)
+  std::vector<int> mesh_of;          // host copy uploaded by setup_view (batched form only)
   std::vector<double> geo_m;         // per mesh max |dT|/(2|T|)
   std::vector<Scalars> hscv;         // per-mesh scalars after the last sync
   // one step captured in a HIP graph (replayed by lxw_run_steps)
@@ -924,9 +925,6 @@ lxw_status setup_view(lxw_solver* S, View<R>& v) {
     delta[i] = S->P.alpha0 * std::pow(M.hsz[i], 1.5);
   }
   std::vector<R> JiR(Ji.begin(), Ji.end()), noR(no.begin(), no.end());
-  std::vector<double> en((size_t)dim * E);
-  for (int e = 0; e < E; ++e)
-    for (int d = 0; d < dim; ++d) en[(size_t)d * E + e] = M.e_n[(size_t)e * dim + d];
   if ((st = upload(S, &v.area, M.area))) return st;
   if ((st = upload(S, &v.Jinv, JiR))) return st;
   if ((st = upload(S, &v.nout, noR))) return st;
@@ -939,24 +937,16 @@ lxw_status setup_view(lxw_solver* S, View<R>& v) {
     if ((st = upload(S, &v.fperm, fp))) return st;
   }
   if ((st = upload(S, &v.delta, delta))) return st;
-  if ((st = upload(S, &v.e_i, M.e_i))) return st;
-  if ((st = upload(S, &v.e_j, M.e_j))) return st;
-  if ((st = upload(S, &v.e_bc, M.e_bc))) return st;
-  if ((st = upload(S, &v.e_n, en))) return st;
+  if ((st = upload(S, &v.e_n, M.e_n))) return st;
   v.mesh_of = nullptr;
-  v.e_mesh = nullptr;
-  if (S->batch) {
+  if (S->batch)
     if ((st = upload(S, &v.mesh_of, S->mesh_of))) return st;
-    if ((st = upload(S, &v.e_mesh, S->e_mesh))) return st;
-  }
   if ((st = S->alloc(&v.Qbar, (size_t)V * N))) return st;
   if ((st = S->alloc(&v.Qh, (size_t)V * (ML - 1) * N))) return st;
   if ((st = S->alloc(&v.theta, (size_t)N))) return st;
   if ((st = S->alloc(&v.spart, (size_t)egrid_blocks(N, 64)))) return st;  // smallest tunable workgroup
   if ((st = S->alloc(&v.tr, (size_t)2 * NQE * V * E))) return st;
-  if ((st = S->alloc(&v.fstar, (size_t)NQE * V * E))) return st;
-  if ((st = S->alloc(&v.fLxW, (size_t)V * E))) return st;
-  if ((st = S->alloc(&v.fLxF, (size_t)V * E))) return st;
+  if ((st = S->alloc(&v.Qold, (size_t)V * N))) return st;
   if ((st = S->alloc(&v.cedge, (size_t)2 * E))) return st;
   {
     std::vector<double> ones((size_t)2 * E, 1.0);
@@ -1043,8 +1033,7 @@ lxw_status enqueue_step_t(lxw_solver* S, const View<R>& v) {
   HIPCHK((launch_one<E, R>(S, v, K_PRE, 0)));
   HIPCHK((launch_one<E, R>(S, v, K_DT, 0)));
   HIPCHK((launch_one<E, R>(S, v, K_ELEM, 0)));
-  HIPCHK((launch_one<E, R>(S, v, K_EDGE, 0)));
-  HIPCHK((launch_one<E, R>(S, v, K_FLIM, 0)));
+  HIPCHK((launch_one<E, R>(S, v, K_FLUX, 0)));
   HIPCHK((launch_one<E, R>(S, v, K_UPDATE, 0)));
   if (S->debug) {
     HIPCHK(hipMemcpyAsync(S->dq_upd_bar, v.Qbar, (size_t)V * N * sizeof(double), hipMemcpyDeviceToDevice, S->st));
@@ -1278,9 +1267,9 @@ lxw_status check_params(const lxw_params* p) {
 }
 
 // Solver over mesh m.  With `batch` (the merged mesh of a batch, m == batch->mesh), the per-mesh
-// offsets, element and edge mesh indices and geometry factors come from it.
+// offsets, element mesh indices and geometry factors come from it.
 struct BatchLayout {
-  std::vector<int> eoff, mesh_of, e_mesh;
+  std::vector<int> eoff, mesh_of;
   std::vector<double> geo;
 };
 
@@ -1299,7 +1288,6 @@ lxw_status merge_meshes(const std::vector<const lxw_mesh*>& ms, lxw_mesh& M, Bat
   bl.eoff.assign(1, 0);
   bl.geo.clear();
   bl.mesh_of.resize(Nt);
-  bl.e_mesh.resize(Et);
   M.geo = 0.0;
   int eo = 0, go = 0;
   for (size_t b = 0; b < ms.size(); ++b) {
@@ -1327,7 +1315,6 @@ lxw_status merge_meshes(const std::vector<const lxw_mesh*>& ms, lxw_mesh& M, Bat
       M.e_bc.push_back(m.e_bc[e]);
       M.e_ki.push_back(m.e_ki[e]);
       M.e_kj.push_back(m.e_kj[e]);
-      bl.e_mesh[go + e] = (int)b;
     }
     M.e_n.insert(M.e_n.end(), m.e_n.begin(), m.e_n.end());
     bl.geo.push_back(m.geo);
@@ -1375,7 +1362,6 @@ lxw_status create_solver(const lxw_mesh* m, const lxw_params* p, void* stream, B
     S->n_mesh = (int)bl->geo.size();
     S->eoff = std::move(bl->eoff);
     S->mesh_of = std::move(bl->mesh_of);
-    S->e_mesh = std::move(bl->e_mesh);
     S->geo_m = std::move(bl->geo);
   } else {
     S->eoff = {0, m->N};
@@ -1978,6 +1964,9 @@ lxw_status lxw_set_debug(lxw_solver* S, int32_t keep) {
   if (check_solver(S)) return LXW_ERR_ARG;
   if (S->batch) return fail(LXW_ERR_UNSUPPORTED, "stage read-out is for single meshes");
   S->debug = keep != 0;
+  // the fluxes are written only while the read-out is on
+  S->vd.fLxW = S->vf.fLxW = S->debug ? S->dfw : nullptr;
+  S->vd.fLxF = S->vf.fLxF = S->debug ? S->dff : nullptr;
   if (!S->debug) return LXW_OK;
   const lxw_mesh& M = *S->M;
   const int N = M.N, V = M.V, ML = M.ML, K = M.K;
@@ -1988,7 +1977,11 @@ lxw_status lxw_set_debug(lxw_solver* S, int32_t keep) {
     char* p2 = nullptr;
     if ((s = S->alloc(&p2, (size_t)V * (ML - 1) * N * rs))) return s;
     S->dq_upd_h = p2;
-    double *a, *b, *c, *d, *q;
+    double *a, *b, *c, *d, *q, *fw, *ff;
+    if ((s = S->alloc(&fw, (size_t)V * M.E))) return s;
+    if ((s = S->alloc(&ff, (size_t)V * M.E))) return s;
+    S->dfw = fw;
+    S->dff = ff;
     if ((s = S->alloc(&q, (size_t)V * ML * N))) return s;
     if ((s = S->alloc(&a, N))) return s;
     if ((s = S->alloc(&b, N))) return s;
@@ -1996,7 +1989,7 @@ lxw_status lxw_set_debug(lxw_solver* S, int32_t keep) {
     if ((s = S->alloc(&d, (size_t)K * N))) return s;
     std::vector<double> ones(N, 1.0);
     HIPCHK(hipMemcpy(b, ones.data(), N * sizeof(double), hipMemcpyHostToDevice));
-    auto set = [&](auto& v) { v.dbg_theta = a; v.dbg_theta_sc = b; v.dbg_vol = c; v.dbg_lame = d; v.dbg_qlim = q; };
+    auto set = [&](auto& v) { v.dbg_theta = a; v.dbg_theta_sc = b; v.dbg_vol = c; v.dbg_lame = d; v.dbg_qlim = q; v.fLxW = fw; v.fLxF = ff; };
     set(S->vd);
     set(S->vf);
   }
@@ -2063,7 +2056,7 @@ lxw_status lxw_debug_stage(lxw_solver* S, int32_t stage, double* out) {
     case LXW_STAGE_FLXW:
     case LXW_STAGE_FLXF: {
       const bool w = stage == LXW_STAGE_FLXW;
-      if ((s = dget(S->fp32 ? (w ? S->vf.fLxW : S->vf.fLxF) : (w ? S->vd.fLxW : S->vd.fLxF), (size_t)V * E, h))) return s;
+      if ((s = dget(w ? S->dfw : S->dff, (size_t)V * E, h))) return s;
       for (int i = 0; i < N; ++i)
         for (int k = 0; k < K; ++k) {
           const int slot = M.eslot[(size_t)i * K + k];
@@ -2175,7 +2168,7 @@ lxw_status lxw_autotune(lxw_solver* S, int32_t trial_steps, lxw_tune* out) {
   S->timing = true;
   LaunchCfg best = S->cfg;
   const int sizes[3] = {64, 128, 256};
-  const int order[5] = {K_ELEM, K_PRE, K_EDGE, K_UPDATE, K_FLIM};
+  const int order[4] = {K_ELEM, K_PRE, K_FLUX, K_UPDATE};
   const double inf = std::numeric_limits<double>::infinity();
   for (int k : order) {
     double best_ms = inf;

@@ -112,11 +112,7 @@ struct View {
   const double* delta;    // [N] shock-limiter relaxation alpha0 h^1.5
   const int* mesh_of;     // [N] mesh index (batched form) or null
   // edges
-  const int* e_i;         // [E] element i_e (n_e points out of it)
-  const int* e_j;         // [E] element j_e or -1
-  const int* e_bc;        // [E] boundary code (SB_*)
-  const double* e_n;      // [DIM][E] n_e, |n_e| = edge length
-  const int* e_mesh;      // [E] mesh index or null
+  const double* e_n;      // [E][DIM] n_e out of the first element, |n_e| = edge length
   // state
   double* Qbar;           // [N][V] cell averages (array of structures: the kernels also gather
                           //   them by neighbour index, and one element's averages then share
@@ -124,17 +120,13 @@ struct View {
   R* Qh;                  // [V][ML-1][N] modes 2..ML
   // work
   double* theta;          // [N] limiter factor of the step (shock x moment), applied by k_elem
-  R* tr;                  // [2][E][NQE][V] one trace per edge side (side 0 = i_e, side 1 = j_e or
+  R* tr;                  // [E][2][NQE][V] one trace per edge side (side 0 = i_e, side 1 = j_e or
                           //   the ghost state), n_out . F_T / 2 + (s |n_e| / 2) q of that side,
                           //   so that F*_T . n_e = side 0 - side 1; points in i_e's order along
-                          //   the edge: one record per edge side, written by the element with
-                          //   vector stores, read by k_edge with coalesced vector loads
-  // Per-edge records (array of structures): the element kernels gather them by edge index, and
-  // one record spans one or two cache lines instead of one line per component.
-  R* fstar;               // [E][NQE][V] F*_T . n_e at the edge points
-  double* fLxW;           // [E][V] f^LxW of edge e (read by the flux limiter; k_update forms it
-                          //   again from the F* record, bit for bit)
-  double* fLxF;           // [E][V] f^LxF of edge e
+                          //   the edge: one record per edge, each side written by its element with
+                          //   vector stores, both read by both elements (k_flux)
+  double* Qold;           // [N][V] the averages at the start of the step (copied by k_elem): k_flux
+                          //   writes the new ones into Qbar while neighbours still read these
   double* cedge;          // [E][2] damping candidate of each side (1 on a ghost side)
   const unsigned char* ind_flag;  // [N] learned indicator decision (0: the shock-capturing limiter
                                  //   is skipped) or null (plain detection everywhere)
@@ -151,6 +143,8 @@ struct View {
   double* dbg_theta;      // [N]
   double* dbg_theta_sc;   // [N]
   double* dbg_vol;        // [V][ML][N]
+  double* fLxW;           // [E][V] f^LxW of edge e, in the first element's orientation
+  double* fLxF;           // [E][V] f^LxF likewise
   double* dbg_lame;       // [K][N]
   double* dbg_qlim;       // [V][ML][N] limited state at the start of the step
 };
@@ -194,19 +188,19 @@ hipError_t upload_tables(const RefTab<E, double>& d, const RefTab<E, float>& f);
 // End time of every mesh (stream-ordered): steps are clipped to reach it and change nothing after.
 hipError_t launch_set_end(Scalars* sc, int n_mesh, double T, hipStream_t st);
 
-enum KernelId { K_PRE = 0, K_DT = 1, K_ELEM = 2, K_EDGE = 3, K_FLIM = 4, K_UPDATE = 5, K_FINAL = 6, K_IND = 7,
+enum KernelId { K_PRE = 0, K_DT = 1, K_ELEM = 2, K_FLUX = 3, K_UPDATE = 5, K_FINAL = 6, K_IND = 7,
                 K_SHOCK = 8 };
 
-// Workgroup size (one lane per element or edge, so also elements or edges per workgroup) of each
-// kernel, indexed by KernelId; the scalar kernels (K_DT, K_FINAL) and the indicator (K_IND, one
-// wavefront per 64 elements) have fixed shapes.  Every
-// tunable kernel accepts 64, 128 or 256.
+// Workgroup size (one lane per element, so also elements per workgroup) of each kernel, indexed by
+// KernelId (K_FLUX is the public interface's LXW_K_EDGE; its LXW_K_FLIM, index 4, launches nothing); the
+// scalar kernels (K_DT, K_FINAL) and the indicator (K_IND, one wavefront per 64 elements) have fixed
+// shapes.  Every tunable kernel accepts 64, 128 or 256.
 struct LaunchCfg {
   int bs[8] = {256, 0, 128, 256, 256, 256, 0, 0};
   int persistent = 0;  // batches: 0 per-phase launches (graph replay), else k_persist with this workgroup size
 };
-inline bool tunable(int k) { return k == K_PRE || k == K_ELEM || k == K_EDGE || k == K_FLIM || k == K_UPDATE; }
-// Number of workgroups of an element or edge kernel: padded to a multiple of 8 (one contiguous
+inline bool tunable(int k) { return k == K_PRE || k == K_ELEM || k == K_FLUX || k == 4 || k == K_UPDATE; }
+// Number of workgroups of an element kernel: padded to a multiple of 8 (one contiguous
 // range of workgroups per XCD).
 inline int egrid_blocks(int n, int bs) { return ((n + bs - 1) / bs + 7) / 8 * 8; }
 

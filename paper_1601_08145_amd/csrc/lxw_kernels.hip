@@ -1,7 +1,7 @@
 // HIP kernels (gfx950) of the positivity-preserving Lax-Wendroff DG step
 // (Moe, Rossmanith, Seal, arXiv:1601.08145).
 //
-// One step is six launches on one stream (grid-wide dependencies separate them):
+// One step is five launches on one stream (grid-wide dependencies separate them):
 //   k_pre    per element: pending shock-capturing limiter of the previous step (Sec. 1.5 Step 5),
 //            moment limiter (Sec. 3.1), cell-average checks, and the global wave speed s
 //            (one partial maximum per workgroup for a single mesh; in a batch one atomic maximum
@@ -12,15 +12,16 @@
 //            of Eq. (taylor3-flux) at every interior and edge point (Sec. 2.2, 2.3 Step 2), the
 //            volume term (Sec. 2.3 Step 3) added to the higher modes, and the edge traces (each
 //            side's half of Eq. (LLF), which is linear in the two sides' values);
-//   k_edge   per edge: Lax-Friedrichs flux of F_T at the edge points (Eq. (LLF)), the
-//            edge-averaged high-order flux f^LxW and the low-order flux f^LxF (Sec. 3.3 Step 3);
-//   k_flim   per element, float64: the flux limiter of Sec. 3.3 Steps 4-5 (Gamma, Lambda_ik, the
-//            corner states and the damping-factor solve mu_c), one candidate per (element, edge);
-//   k_update per element: Lambda_e = min over the two sides, the blended cell-average update and
-//            the higher-moment update of Sec. 3.3 Step 6, and the positivity check; the first
-//            element of each mesh then ends the mesh's step (t += dt);
+//   k_flux   per element: on each of its edges the Lax-Friedrichs flux of F_T at the edge points
+//            (Eq. (LLF)), the edge-averaged high-order flux f^LxW and the low-order flux f^LxF (Sec. 3.3
+//            Step 3); the higher moments' edge terms (Step 6); the flux limiter of Steps 4-5 in float64
+//            (Gamma, Lambda_ik, the corner states and the damping-factor solve mu_c), one candidate
+//            per (element, edge); and the average's update with the high-order flux everywhere;
+//   k_update per element: Lambda_e = min over the two sides; where one is below 1 the average's update
+//            of Step 6 with the blended fluxes instead; the positivity check; the first element of each
+//            mesh then ends the mesh's step (t += dt);
 //   k_final  per mesh, after a state read-out applied the pending shock limiter: marks it done.
-// Thread-per-element (or per-edge) mapping; reference tables sit in __constant__ memory and are
+// Thread-per-element mapping; reference tables sit in __constant__ memory and are
 // read through the scalar cache (every lane of a wave reads the same entry).  State is stored as
 // cell averages Qbar[N][V] (float64, one record per element: also gathered by neighbour index) and
 // higher modes as structure-of-arrays Qh[V][ML-1][N].
@@ -871,7 +872,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
-  const int N = v.N, NE = v.E;
+  const int N = v.N;
   if (i >= N) return;
   const int mid = mesh_id<R>(v.mesh_of, i);
   // At the end time the step changes nothing: the stored modes are written back as they were.
@@ -886,6 +887,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
 #pragma unroll
   for (int c = 0; c < V; ++c) {
     qb[c] = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
     for (int l = 1; l < ML; ++l) Qr[c][l - 1] = v.Qh[(c * (ML - 1) + l - 1) * N + i];
   }
@@ -1169,7 +1171,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
       R b[V];
 #pragma unroll
       for (int c = 0; c < V; ++c) b[c] = R(0.5) * fn[c] + hs * q[c];
-      store_rec<R, V>(v.tr + (((size_t)side * NE + e) * NQE + jj) * V, b);
+      store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
       if (bc != SB_INTERIOR) {
         R qg[V], fgn[V];
         if (bc == SB_TRANSPARENT) {
@@ -1196,7 +1198,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
         R bg[V];
 #pragma unroll
         for (int c = 0; c < V; ++c) bg[c] = hs * qg[c] - R(0.5) * fgn[c];
-        store_rec<R, V>(v.tr + (((size_t)NE + e) * NQE + jj) * V, bg);
+        store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
       }
     }
   }
@@ -1216,7 +1218,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
-  const int N = v.N, NE = v.E;
+  const int N = v.N;
   if (i >= N) return;
   const int mid = mesh_id<R>(v.mesh_of, i);
   const bool idle = v.sc[mid].idle;
@@ -1228,6 +1230,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 #pragma unroll
   for (int c = 0; c < V; ++c) {
     qb[c] = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
     for (int l = 1; l < ML; ++l) Qr[c][l - 1] = v.Qh[(c * (ML - 1) + l - 1) * N + i];
   }
@@ -1539,7 +1542,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
       R b[V];
 #pragma unroll
       for (int c = 0; c < V; ++c) b[c] = R(0.5) * fn[c] + hs * q[c];
-      store_rec<R, V>(v.tr + (((size_t)side * NE + e) * NQE + jj) * V, b);
+      store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
       if (bc != SB_INTERIOR) {
         R qg[V], FTg[DIM][V];
         if (bc == SB_TRANSPARENT) {
@@ -1575,7 +1578,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
           for (int d = 0; d < DIM; ++d) f += n[d] * FTg[d][c];
           bg[c] = hs * qg[c] - R(0.5) * f;
         }
-        store_rec<R, V>(v.tr + (((size_t)NE + e) * NQE + jj) * V, bg);
+        store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
       }
     }
   }
@@ -1593,28 +1596,45 @@ __global__ __launch_bounds__(256, (ElemOcc<E, R>::waves)) void k_elem(View<R> v)
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_edge: F*_T . n_e = (1/2)(n_e.F_T(q+) + n_e.F_T(q-)) - (s |n_e| / 2)(q+ - q-) at each edge point
-// (Eq. (LLF) with the scaled normal; the flux is linear in the two sides' values, so each element
-// wrote its half n_out.F_T/2 + (s |n_e|/2) q and F* is side 0 minus side 1),
-// f^LxW_e = (1/2) sum_j omega_j F*_j (float64 sum), and
-// f^LxF_e = (1/2) n_e.(F(q_bar_j) + F(q_bar_i)) - (s |n_e| / 2)(q_bar_j - q_bar_i) in float64.
+// Edge fluxes, formed by both elements of an edge from the same data.  F*_T . n_e = (1/2)(n_e.F_T(q+)
+// + n_e.F_T(q-)) - (s |n_e| / 2)(q+ - q-) at each edge point (Eq. (LLF) with the scaled normal; it is
+// linear in the two sides' values, so each element wrote its half n_out.F_T/2 + (s |n_e|/2) q and F* is
+// side 0 minus side 1); f^LxW_e = (1/2) sum_j omega_j F*_j and
+// f^LxF_e = (1/2) n_e.(F(q_bar_j) + F(q_bar_i)) - (s |n_e| / 2)(q_bar_j - q_bar_i) in float64.  The two
+// elements get the same bits up to the sign (the averages' update is conservative to rounding): F* and
+// f^LxW are formed in the first element's orientation and point order, and every operation of f^LxF
+// is written out, changes sign with the normal and is symmetric in the two states.
 // ---------------------------------------------------------------------------------------------
-// Copies nbytes (a multiple of 4) from LDS to global memory with the whole workgroup, 16 bytes per
-// lane and store where both ends allow it: consecutive lanes write consecutive addresses.
-template <int ALIGN16>
-__device__ __forceinline__ void lds_to_global(unsigned char* dst, const unsigned char* src, int nbytes) {
-  if constexpr (ALIGN16) {
-    for (int o = (int)threadIdx.x * 16; o < nbytes; o += (int)blockDim.x * 16)
-      *reinterpret_cast<uint4*>(dst + o) = *reinterpret_cast<const uint4*>(src + o);
+// V values of one record at p (consecutive)
+template <class R, int V>
+__device__ __forceinline__ void load_rec(const R* p, R (&x)[V]) {
+  if constexpr ((V * sizeof(R)) % 16 == 0) {
+    typedef R vec __attribute__((ext_vector_type(V)));
+    const vec t = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int c = 0; c < V; ++c) x[c] = t[c];
   } else {
-    for (int o = (int)threadIdx.x * 4; o < nbytes; o += (int)blockDim.x * 4)
-      *reinterpret_cast<unsigned*>(dst + o) = *reinterpret_cast<const unsigned*>(src + o);
+#pragma unroll
+    for (int c = 0; c < V; ++c) x[c] = p[c];
   }
 }
 
-// f^LxW_e = (1/2) sum_j omega_j F*_j in float64, summed in the edge's point order with explicit
-// fused multiply-adds: k_edge stores it for the flux limiter and k_update forms it again from the
-// F* record, and the two agree bit for bit.
+// F* at the points of edge e in the first element's order
+template <class E, class R>
+__device__ __forceinline__ void edge_points(const View<R>& v, int e, R (&fs)[E::NQE][E::V]) {
+  constexpr int V = E::V, NQE = E::NQE;
+  const R* t = v.tr + (size_t)e * (2 * NQE * V);
+#pragma unroll
+  for (int jj = 0; jj < NQE; ++jj) {
+    R a[V], b[V];
+    load_rec<R, V>(t + jj * V, a);
+    load_rec<R, V>(t + (NQE + jj) * V, b);
+#pragma unroll
+    for (int c = 0; c < V; ++c) fs[jj][c] = a[c] - b[c];
+  }
+}
+
+// f^LxW_e in float64, summed in the edge's point order
 template <class E, class R>
 __device__ __forceinline__ void lxw_average(const RefTab<E, R>& T, const R (&fs)[E::NQE][E::V], double (&W)[E::V]) {
 #pragma unroll
@@ -1627,101 +1647,75 @@ __device__ __forceinline__ void lxw_average(const RefTab<E, R>& T, const R (&fs)
   }
 }
 
-// Edge e of k_edge; every lane of the workgroup calls it with the edges e0 + threadIdx.x of one
-// contiguous tile (the records are staged through LDS and written together).
-template <class E, class R>
-__device__ __forceinline__ void edge_tile(View<R> v, const int e) {
-  constexpr int V = E::V, DIM = E::DIM, NQE = E::NQE;
-  // per-edge records: F* at the edge points, f^LxW and f^LxF; each lane writes its edge's records
-  // into LDS as it computes them
-  constexpr int FS = NQE * V * (int)sizeof(R), FL = V * (int)sizeof(double);
-  __shared__ __align__(16) unsigned char rec_fs[256 * FS];
-  __shared__ __align__(16) unsigned char rec_fw[256 * FL];
-  __shared__ __align__(16) unsigned char rec_ff[256 * FL];
-  const RefTab<E, R>& T = TabSel<E, R>::get();
-  const int NE = v.E;
-  const bool valid = e < NE;
-  const int e0 = e - (int)threadIdx.x;  // first edge of the workgroup (its edges are consecutive)
-  const int nrec = max(0, min((int)blockDim.x, NE - e0));
-  R* fsr = reinterpret_cast<R*>(rec_fs + threadIdx.x * FS);
-  double* fwr = reinterpret_cast<double*>(rec_fw + threadIdx.x * FL);
-  double* ffr = reinterpret_cast<double*>(rec_ff + threadIdx.x * FL);
-  if (valid) {
-    const int mid = v.e_mesh ? at(v.e_mesh, e) : 0;
-    const double s = v.sc[mid].s;
-    const double gam = v.gamma;
-    double n[DIM], len2 = 0.0;
+// Velocity and pressure of an average, every operation written out
+template <int DIM>
+struct AvgPrim { double u[DIM], p; };
+template <int DIM>
+__device__ __forceinline__ AvgPrim<DIM> avg_prim(const double* q, double gm1) {
+  AvgPrim<DIM> P;
+  const double r = 1.0 / q[0];
+  double mu = 0.0;
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) { n[d] = at(v.e_n + (size_t)d * NE, e); len2 += n[d] * n[d]; }
-    const double len = sqrt(len2);
-    const int ie = at(v.e_i, e), je = at(v.e_j, e);
-    R fs[NQE][V];
-#pragma unroll
-    for (int jj = 0; jj < NQE; ++jj) {
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        // (n.F_T(q-) + n.F_T(q+))/2 - hs (q+ - q-), from the two sides' traces
-        fs[jj][c] = v.tr[((size_t)e * NQE + jj) * V + c] - v.tr[(((size_t)NE + e) * NQE + jj) * V + c];
-        fsr[jj * V + c] = fs[jj][c];
-      }
-    }
-    double W[V];
-    lxw_average<E, R>(T, fs, W);
-#pragma unroll
-    for (int c = 0; c < V; ++c) fwr[c] = W[c];
-
-    const int i = ie, j = je;
-    double qi[V], qj[V];
-#pragma unroll
-    for (int c = 0; c < V; ++c) qi[c] = v.Qbar[(size_t)i * V + c];
-    if (j >= 0) {
-#pragma unroll
-      for (int c = 0; c < V; ++c) qj[c] = v.Qbar[(size_t)j * V + c];
-    } else {
-      const int bc = at(v.e_bc, e);
-      if (bc == SB_REFLECTIVE) {
-        double nh[DIM];
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) nh[d] = n[d] / len;
-        reflect<DIM, double>(qi, nh, qj);
-      } else if (bc == SB_INFLOW) {
-        inflow_state<DIM, double>(v.inflow, qj);
-      } else {
-#pragma unroll
-        for (int c = 0; c < V; ++c) qj[c] = qi[c];
-      }
-    }
-    St<DIM, double> si = base_state<DIM, double>(qi, gam - 1.0);
-    St<DIM, double> sj = base_state<DIM, double>(qj, gam - 1.0);
-    double Lf[V];
-#pragma unroll
-    for (int c = 0; c < V; ++c) Lf[c] = 0.0;
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      double Fi[V], Fj[V];
-      flux<DIM, double>(si, d, Fi);
-      flux<DIM, double>(sj, d, Fj);
-#pragma unroll
-      for (int c = 0; c < V; ++c) Lf[c] += 0.5 * n[d] * (Fj[c] + Fi[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < V; ++c) ffr[c] = Lf[c] - 0.5 * s * len * (qj[c] - qi[c]);
+  for (int d = 0; d < DIM; ++d) {
+    P.u[d] = __dmul_rn(q[1 + d], r);
+    mu = __fma_rn(q[1 + d], P.u[d], mu);
   }
-  // The records of the workgroup's edges are one contiguous range: staged in LDS, they are written
-  // with coalesced stores (written straight from the lanes, every store instruction would touch a
-  // cache line per lane).
-  __syncthreads();
-  lds_to_global<FS % 16 == 0>(reinterpret_cast<unsigned char*>(v.fstar) + (size_t)max(e0, 0) * FS, rec_fs, nrec * FS);
-  lds_to_global<FL % 16 == 0>(reinterpret_cast<unsigned char*>(v.fLxW) + (size_t)max(e0, 0) * FL, rec_fw, nrec * FL);
-  lds_to_global<FL % 16 == 0>(reinterpret_cast<unsigned char*>(v.fLxF) + (size_t)max(e0, 0) * FL, rec_ff, nrec * FL);
-  // the staging area is free again only when every lane has copied its part out (a workgroup of
-  // the persistent kernel goes on to its next tile)
-  __syncthreads();
+  P.p = __dmul_rn(gm1, __fma_rn(-0.5, mu, q[DIM + 1]));
+  return P;
+}
+// n . F(q)
+template <int DIM>
+__device__ __forceinline__ void avg_flux(const double* q, const AvgPrim<DIM>& P, const double* n, double* F) {
+  double un = __dmul_rn(P.u[0], n[0]), mn = __dmul_rn(q[1], n[0]);
+#pragma unroll
+  for (int d = 1; d < DIM; ++d) { un = __fma_rn(P.u[d], n[d], un); mn = __fma_rn(q[1 + d], n[d], mn); }
+  F[0] = mn;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) F[1 + k] = __fma_rn(q[1 + k], un, __dmul_rn(P.p, n[k]));
+  F[DIM + 1] = __dmul_rn(un, __dadd_rn(q[DIM + 1], P.p));
 }
 
+// f^LxF through local edge k of element i (edge e on its side `side`), out of the element; q and P are
+// the element's average.
 template <class E, class R>
-__global__ __launch_bounds__(256) void k_edge(View<R> v) {
-  edge_tile<E, R>(v, xcd_item());
+__device__ __forceinline__ void lxf_out(const View<R>& v, int i, int k, int e, int side, const double (&q)[E::V],
+                                        const AvgPrim<E::DIM>& P, double s, double (&f)[E::V]) {
+  constexpr int V = E::V, DIM = E::DIM;
+  const double gm1 = v.gamma - 1.0;
+  double n[DIM], len2 = 0.0;
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    const double x = v.e_n[(size_t)e * DIM + d];
+    n[d] = side ? -x : x;
+    len2 = __fma_rn(x, x, len2);
+  }
+  const double len = sqrt(len2);
+  const int j = at(v.nbr + (size_t)k * v.N, i);
+  double qn[V];
+  if (j >= 0) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) qn[c] = v.Qold[(size_t)j * V + c];
+  } else {
+    const int bc = at(v.eslot + (size_t)k * v.N, i) & 3;
+    if (bc == SB_REFLECTIVE) {
+      double nh[DIM];
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) nh[d] = n[d] / len;
+      reflect<DIM, double>(q, nh, qn);
+    } else if (bc == SB_INFLOW) {
+      inflow_state<DIM, double>(v.inflow, qn);
+    } else {
+#pragma unroll
+      for (int c = 0; c < V; ++c) qn[c] = q[c];
+    }
+  }
+  const AvgPrim<DIM> Pn = avg_prim<DIM>(qn, gm1);
+  double Fo[V], Fn[V];
+  avg_flux<DIM>(q, P, n, Fo);
+  avg_flux<DIM>(qn, Pn, n, Fn);
+  const double h = __dmul_rn(0.5, __dmul_rn(s, len));
+#pragma unroll
+  for (int c = 0; c < V; ++c) f[c] = __fma_rn(-h, __dsub_rn(qn[c], q[c]), __dmul_rn(0.5, __dadd_rn(Fo[c], Fn[c])));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1737,6 +1731,18 @@ __device__ __forceinline__ bool mu_ok(const double* qL, const double* qa, double
 #pragma unroll
   for (int c = 0; c < V; ++c) q[c] = qL[c] + mu * (qa[c] - qL[c]);
   return q[0] > 0.0 && pressure<DIM>(q, gam) >= epsp;
+}
+
+// Sufficient for mu_ok at mu = 1 without its division: rho (p - eps_p) exceeds a hundred times the
+// rounding of either form (each is a sum of terms no larger than (gamma-1)(|E| rho + |M|^2) and
+// eps_p rho, with relative errors of a few 2^-53).
+template <int DIM>
+__device__ __forceinline__ bool mu_sure(const double* q, double gam, double epsp) {
+  double k = 0.0;
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) k += q[1 + d] * q[1 + d];
+  const double Er = q[DIM + 1] * q[0], g1 = gam - 1.0;
+  return q[0] > 0.0 && g1 * (Er - 0.5 * k) - epsp * q[0] > 1e-13 * (g1 * (fabs(Er) + k) + epsp * q[0]);
 }
 
 template <int DIM>
@@ -1766,40 +1772,140 @@ __device__ double mu_solve(const double* qL, const double* qa, double gam, doubl
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_flim: the flux limiter of Sec. 3.3 Steps 4-5, float64, per element.  Readings: every edge flux
-// of the element carries eps_ik (as in the printed Step 4); Cases 1-4 of the sorted Delta f are
-// evaluated as "each edge with Delta f_k < 0 gets min(1, Gamma / |sum of the negative Delta f|)"
-// (no sort); the corner states keep the Lax-Friedrichs flux on the edges switched off, so that
+// k_flux: everything an element does on its edges, in one kernel: F* at the edge points, f^LxW and
+// f^LxF, the higher-moment update of Sec. 3.3 Step 6
+//   Q^(l) -= dt/|T| sum_k eps_ik (1/2) sum_j omega_j phi_l(x_kj) F*_kj . n_e,  l >= 2
+// (the volume part was added by k_elem), the flux limiter of Steps 4-5 in float64, and the average's
+// update with f^LxW on every edge, which k_update replaces where an edge is limited.  Limiter readings:
+// every edge flux of the element carries eps_ik (as in the printed Step 4); Cases 1-4 of the sorted
+// Delta f are evaluated as "each edge with Delta f_k < 0 gets min(1, Gamma / |sum of the negative
+// Delta f|)" (no sort); the corner states keep the Lax-Friedrichs flux on the edges switched off, so that
 // corner 000 is the pure LxF update; the pressure target is eps_p = min(eps0, p(q^LxF)).
+//
+// Bound by HBM: the traces and the modes in and out.  Each edge's fluxes are formed twice (by both
+// elements) so that no per-edge flux record is written and gathered again: on 999,698 triangles,
+// FP32-mixed, k_edge, k_flim and k_update (380 + 174 + 400 MB) took 67 + 43 + 88 us; k_flux and the new
+// k_update take 115 + 18 us.  Traces of an edge's two sides are one record (96 bytes here): the element
+// that reads both touches one or two cache lines.
 // ---------------------------------------------------------------------------------------------
+// Faces one after another in a loop, their fluxes kept in LDS, or all unrolled, their fluxes in registers:
+// unrolled where every face's loads then fit the registers together (1D; float32 P2 triangles: 235
+// registers, 115 us on 999,698 against 126 us in the loop), the loop elsewhere (it needs no spill and
+// little code: float64 triangles 42 against 49 us on 250k, the float64 square 35 / 40 us on 118k, P3
+// 38 / 46 us on 250k, tetrahedra 133 / 182 us on 280k and 37 / 109 us in float64 on 25k).
 template <class E, class R>
-__device__ __forceinline__ void flim_item(View<R> v, const int i) {
-  constexpr int V = E::V, DIM = E::DIM, K = E::K;
+struct FluxShape {
+  static constexpr bool roll = E::DIM > 1 && !(E::kind == ElTri::kind && E::DEG == 2 && sizeof(R) == 4);
+};
+
+template <class E, class R>
+__device__ __forceinline__ void flux_item(View<R> v, const int i) {
+  constexpr int V = E::V, ML = E::ML, DIM = E::DIM, K = E::K, NQE = E::NQE;
+  const RefTab<E, R>& T = TabSel<E, R>::get();
   const int N = v.N;
   if (i >= N) return;
   const int mid = mesh_id<R>(v.mesh_of, i);
-  const double dt = v.sc[mid].dt;
-  const bool idle = v.sc[mid].idle;  // at the end time nothing is reported (the step is discarded)
+  const double dt = v.sc[mid].dt, s = v.sc[mid].s;
+  // at the end time the step changes nothing: the flag is read here and applied at the stores, and
+  // nothing is reported
+  const bool idle = v.sc[mid].idle;
   const double gam = v.gamma;
   const double area = at(v.area, i);
   const double r = dt / area;
   double qb[V];
+  R Qh[V][ML - 1];
 #pragma unroll
-  for (int c = 0; c < V; ++c) qb[c] = v.Qbar[(size_t)i * V + c];
-  double fW[K][V], fF[K][V], df[K];
-  int eidx[K], sd[K];
-  double Gam = area * qb[0] / dt;
+  for (int c = 0; c < V; ++c) {
+    qb[c] = v.Qold[(size_t)i * V + c];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int slot = at(v.eslot + (size_t)k * N, i);
-    eidx[k] = slot >> 3;
-    sd[k] = (slot >> 2) & 1;
-    const double ep = sd[k] ? -1.0 : 1.0;
+    for (int l = 0; l < ML - 1; ++l) Qh[c][l] = at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i);
+  }
+  const AvgPrim<DIM> P = avg_prim<DIM>(qb, gam - 1.0);
+  double fW[K][V], fF[K][V];
+  int slot[K];
+  auto face = [&](const int k, double (&W)[V], double (&F)[V]) -> int {
+    const int sl = at(v.eslot + (size_t)k * N, i);
+    const int e = sl >> 3, side = (sl >> 2) & 1;
+    const double ep = side ? -1.0 : 1.0;
+    R fs[NQE][V];
+    edge_points<E, R>(v, e, fs);
+    lxw_average<E, R>(T, fs, W);
+#pragma unroll
+    for (int c = 0; c < V; ++c) W[c] *= ep;
+    lxf_out<E, R>(v, i, k, e, side, qb, P, s, F);
+    // higher moments; the element's point jl is the first element's jl, the reverse of it, or (on a
+    // face) that of the vertex permutation, which moves the two three-point orbits 1-3 and 4-6 alike
+    const R re = R(r * ep);
+    const int perm = (DIM == 3) ? at(v.fperm + (size_t)k * N, i) : 0;
+#pragma unroll
+    for (int jl = 0; jl < NQE; ++jl) {
+      const int pj = (DIM == 3) ? T.pperm[perm][jl] : 0;
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        R x;
+        if constexpr (DIM == 3) {
+          if (jl == 0) x = fs[0][c];
+          else {
+            const int o = jl < 4 ? 1 : 4;
+            x = pj == o ? fs[o][c] : (pj == o + 1 ? fs[o + 1][c] : fs[o + 2][c]);
+          }
+        } else {
+          x = side ? fs[NQE - 1 - jl][c] : fs[jl][c];
+        }
+        const R f = re * x;
+#pragma unroll
+        for (int l = 1; l < ML; ++l) Qh[c][l - 1] -= T.ephi[k][jl][l] * f;
+      }
+    }
+    return sl;
+  };
+  if constexpr (FluxShape<E, R>::roll) {
+    // one face at a time: the lane's fluxes wait in LDS (columns of consecutive lanes) until the modes are
+    // stored
+    __shared__ double sf[K * 2 * V][256];
+    const int t = (int)threadIdx.x;
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+      double W[V], F[V];
+      face(k, W, F);
+#pragma unroll
+      for (int c = 0; c < V; ++c) { sf[(2 * k) * V + c][t] = W[c]; sf[(2 * k + 1) * V + c][t] = F[c]; }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      slot[k] = at(v.eslot + (size_t)k * N, i);
+#pragma unroll
+      for (int c = 0; c < V; ++c) { fW[k][c] = sf[(2 * k) * V + c][t]; fF[k][c] = sf[(2 * k + 1) * V + c][t]; }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k) slot[k] = face(k, fW[k], fF[k]);
+  }
+  if (!idle) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
-      fW[k][c] = ep * v.fLxW[(size_t)eidx[k] * V + c];
-      fF[k][c] = ep * v.fLxF[(size_t)eidx[k] * V + c];
+      double q = qb[c];
+#pragma unroll
+      for (int k = 0; k < K; ++k) q -= r * fW[k][c];
+      v.Qbar[(size_t)i * V + c] = q;
+#pragma unroll
+      for (int l = 0; l < ML - 1; ++l) at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = Qh[c][l];
     }
+  }
+  if (v.fLxW) {  // stage read-out: the first element's fluxes
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (!((slot[k] >> 2) & 1))
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+          v.fLxW[(size_t)(slot[k] >> 3) * V + c] = fW[k][c];
+          v.fLxF[(size_t)(slot[k] >> 3) * V + c] = fF[k][c];
+        }
+  }
+  // Steps 4-5
+  double Gam = area * qb[0] / dt, df[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
     Gam -= fF[k][0];
     df[k] = fF[k][0] - fW[k][0];
   }
@@ -1822,111 +1928,111 @@ __device__ __forceinline__ void flim_item(View<R> v, const int i) {
   const double pL = qL[0] > 0.0 ? pressure<DIM>(qL, gam) : -1.0;
   bad = bad || !(pL > 0.0);
   const double epsp = fmin(v.eps0, pL);
-  double mm[K];
+  // the flux of an edge that is switched on
 #pragma unroll
-  for (int k = 0; k < K; ++k) mm[k] = 1.0;
+  for (int k = 0; k < K; ++k)
 #pragma unroll
-  for (int a = 1; a < (1 << K); ++a) {
-    double qa[V];
+    for (int c = 0; c < V; ++c) fW[k][c] = Lam[k] * fW[k][c] + (1.0 - Lam[k]) * fF[k][c];
+  // Corner states: nearly always every one passes the sufficient test mu_sure (then mu = 1 for all of
+  // them); otherwise the lane solves every corner, in a loop at run time (15 inlined solves on the
+  // tetrahedron are more code than the instruction cache holds, and a wavefront runs through once).
+  auto corner = [&](int a, double* qa) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       double acc = 0.0;
 #pragma unroll
-      for (int k = 0; k < K; ++k) {
-        const double th = ((a >> k) & 1) ? Lam[k] : 0.0;
-        acc += th * fW[k][c] + (1.0 - th) * fF[k][c];
-      }
+      for (int k = 0; k < K; ++k) acc += ((a >> k) & 1) ? fW[k][c] : fF[k][c];
       qa[c] = qb[c] - r * acc;
     }
-    const double mu = pL > 0.0 ? mu_solve<DIM>(qL, qa, gam, epsp) : 0.0;
+  };
+  double mm[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-      if ((a >> k) & 1) mm[k] = fmin(mm[k], mu);
+  for (int k = 0; k < K; ++k) mm[k] = 1.0;
+  bool sure = pL > 0.0;
+#pragma unroll
+  for (int a = 1; a < (1 << K); ++a) {
+    double qa[V];
+    corner(a, qa);
+    sure = sure && mu_sure<DIM>(qa, gam, epsp);
+  }
+  if (!sure) {
+#pragma unroll 1
+    for (int a = 1; a < (1 << K); ++a) {
+      double qa[V];
+      corner(a, qa);
+      const double mu = pL > 0.0 ? mu_solve<DIM>(qL, qa, gam, epsp) : 0.0;
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if ((a >> k) & 1) mm[k] = fmin(mm[k], mu);
+    }
   }
   if (bad && !idle) report(v.err, E_CFL, i);
 #pragma unroll
-  for (int k = 0; k < K; ++k) v.cedge[(size_t)eidx[k] * 2 + sd[k]] = Lam[k] * mm[k];
+  for (int k = 0; k < K; ++k) v.cedge[(size_t)(slot[k] >> 3) * 2 + ((slot[k] >> 2) & 1)] = Lam[k] * mm[k];
 }
 
 template <class E, class R>
-__global__ __launch_bounds__(256) void k_flim(View<R> v) {
-  flim_item<E, R>(v, xcd_item());
+__global__ __launch_bounds__(256) void k_flux(View<R> v) {
+  flux_item<E, R>(v, xcd_item());
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_update: Sec. 3.3 Step 6 with theta_k = Lambda_{e_ik} = min(1, both sides' candidates):
+// k_update: Sec. 3.3 Step 6 for the averages, theta_k = Lambda_{e_ik} = min(1, both sides' candidates):
 //   Q^(1) -= dt/|T| sum_k eps_ik [theta_k f^LxW + (1 - theta_k) f^LxF]            (float64)
-//   Q^(l) -= dt/|T| sum_k eps_ik (1/2) sum_j omega_j phi_l(x_kj) F*_kj . n_e,  l >= 2
-// (the volume part of the higher moments was added by k_elem), then the positivity check of the
-// new cell average.
+// k_flux has formed it for theta = 1 on every edge; an element with a limited edge forms it again
+// from the step's averages and the traces (rare: the same functions, so the same fluxes bit for bit).
+// Then the positivity check of the new average.
 // ---------------------------------------------------------------------------------------------
 template <class E, class R>
 __device__ __forceinline__ void update_item(View<R> v, const int i) {
-  constexpr int V = E::V, ML = E::ML, DIM = E::DIM, K = E::K, NQE = E::NQE;
-  const RefTab<E, R>& T = TabSel<E, R>::get();
+  constexpr int V = E::V, DIM = E::DIM, K = E::K, NQE = E::NQE;
   const int N = v.N;
   if (i >= N) return;
   const int mid = mesh_id<R>(v.mesh_of, i);
   // at the end time the step changes nothing: the flag is read here and applied at the stores
   const bool idle = v.sc[mid].idle;
   const double dt = v.sc[mid].dt;
-  const double r = dt / at(v.area, i);
-  double qb[V];
-  R Qh[V][ML - 1];
+  double q[V];
 #pragma unroll
-  for (int c = 0; c < V; ++c) {
-    qb[c] = v.Qbar[(size_t)i * V + c];
-#pragma unroll
-    for (int l = 0; l < ML - 1; ++l) Qh[c][l] = at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i);
-  }
+  for (int c = 0; c < V; ++c) q[c] = v.Qbar[(size_t)i * V + c];
+  double low = 1.0;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    const int slot = at(v.eslot + (size_t)k * N, i);
-    const int e = slot >> 3, side = (slot >> 2) & 1;
-    const double ep = side ? -1.0 : 1.0;
+    const int e = at(v.eslot + (size_t)k * N, i) >> 3;
     const double th = fmin(1.0, fmin(v.cedge[(size_t)e * 2], v.cedge[(size_t)e * 2 + 1]));
     if (v.dbg_lame) v.dbg_lame[k * N + i] = th;
-    // 1D and 2D: the edge's F* record in registers, and f^LxW formed from it as k_edge formed the
-    // one the limiter used (one record read instead of two); 3D: f^LxW as stored (a face record of
-    // 7 points per face, four faces in flight, would not fit the registers)
-    R fsr[NQE][V];
-    double W[V];
-    if constexpr (DIM == 3) {
-#pragma unroll
-      for (int c = 0; c < V; ++c) W[c] = v.fLxW[(size_t)e * V + c];
-    } else {
-#pragma unroll
-      for (int jj = 0; jj < NQE; ++jj)
-#pragma unroll
-        for (int c = 0; c < V; ++c) fsr[jj][c] = v.fstar[(size_t)e * (NQE * V) + jj * V + c];
-      lxw_average<E, R>(T, fsr, W);
-    }
-#pragma unroll
-    for (int c = 0; c < V; ++c) qb[c] -= r * ep * (th * W[c] + (1.0 - th) * v.fLxF[(size_t)e * V + c]);
-    const R re = R(r * ep);
-    const int perm = (DIM == 3) ? at(v.fperm + (size_t)k * N, i) : 0;
-#pragma unroll
-    for (int jl = 0; jl < NQE; ++jl) {
-      const int jj = (DIM == 3) ? T.pperm[perm][jl] : (side ? (NQE - 1 - jl) : jl);
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        const R fs = re * ((DIM == 3) ? v.fstar[(size_t)e * (NQE * V) + jj * V + c] : fsr[jj][c]);
-#pragma unroll
-        for (int l = 1; l < ML; ++l) Qh[c][l - 1] -= T.ephi[k][jl][l] * fs;
-      }
-    }
+    low = fmin(low, th);
   }
   if (idle) return;
+  if (low < 1.0) {
+    const RefTab<E, R>& T = TabSel<E, R>::get();
+    const double s = v.sc[mid].s, r = dt / at(v.area, i);
+    double qb[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) q[c] = qb[c] = v.Qold[(size_t)i * V + c];
+    const AvgPrim<DIM> P = avg_prim<DIM>(qb, v.gamma - 1.0);
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+      const int slot = at(v.eslot + (size_t)k * N, i);
+      const int e = slot >> 3, side = (slot >> 2) & 1;
+      const double ep = side ? -1.0 : 1.0;
+      const double th = fmin(1.0, fmin(v.cedge[(size_t)e * 2], v.cedge[(size_t)e * 2 + 1]));
+      R fs[NQE][V];
+      edge_points<E, R>(v, e, fs);
+      double W[V], F[V];
+      lxw_average<E, R>(T, fs, W);
+      lxf_out<E, R>(v, i, k, e, side, qb, P, s, F);
+#pragma unroll
+      for (int c = 0; c < V; ++c) q[c] -= r * (th * (ep * W[c]) + (1.0 - th) * F[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < V; ++c) v.Qbar[(size_t)i * V + c] = q[c];
+  }
   bool finite = true;
 #pragma unroll
-  for (int c = 0; c < V; ++c) {
-    v.Qbar[(size_t)i * V + c] = qb[c];
-    finite = finite && isfinite(qb[c]);
-#pragma unroll
-    for (int l = 0; l < ML - 1; ++l) at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = Qh[c][l];
-  }
+  for (int c = 0; c < V; ++c) finite = finite && isfinite(q[c]);
   if (!finite) report(v.err, E_NONFINITE, i);
-  else if (!(qb[0] > 0.0) || !(pressure<DIM>(qb, v.gamma) > 0.0)) report(v.err, E_POSITIVITY, i);
+  else if (!(q[0] > 0.0) || !(pressure<DIM>(q, v.gamma) > 0.0)) report(v.err, E_POSITIVITY, i);
   // The first element of each mesh ends the mesh's step: t += dt, the wave-speed maximum is reset
   // and the shock-capturing limiter becomes due.  Every lane has read dt above and no kernel of
   // this step reads the fields written here.
@@ -1946,8 +2052,8 @@ __global__ __launch_bounds__(256) void k_update(View<R> v) {
 
 // ---------------------------------------------------------------------------------------------
 // k_persist: n_steps whole steps of a batch of meshes in one cooperative launch.  Every workgroup
-// stays resident and runs each phase of the step (the bodies of k_pre, k_dt, k_elem, k_edge,
-// k_flim, k_update) over tiles of elements or edges, with a grid-wide barrier where the separate
+// stays resident and runs each phase of the step (the bodies of k_pre, k_dt, k_elem, k_flux,
+// k_update) over tiles of elements, with a grid-wide barrier where the separate
 // launches have a kernel boundary; the arithmetic is that of the separate kernels, so the results
 // are the same bit for bit.  The grid is a multiple of 8 workgroups: workgroup b runs on XCD b mod 8,
 // and the tiles of each XCD are one contiguous range of the space-filling-curve order.
@@ -1969,9 +2075,7 @@ __global__ __launch_bounds__(256, (ElemOcc<E, R>::waves)) void k_persist(View<R>
     grid.sync();
     tiles(v.N, [&](int i) { elem_item<E, R>(v, i); });
     grid.sync();
-    tiles(v.E, [&](int e) { edge_tile<E, R>(v, e); });
-    grid.sync();
-    tiles(v.N, [&](int i) { flim_item<E, R>(v, i); });
+    tiles(v.N, [&](int i) { flux_item<E, R>(v, i); });
     grid.sync();
     tiles(v.N, [&](int i) { update_item<E, R>(v, i); });
     grid.sync();
@@ -2060,11 +2164,8 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
     case K_ELEM:
       if (v.N > 0) hipLaunchKernelGGL((k_elem<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);
       break;
-    case K_EDGE:
-      if (v.E > 0) hipLaunchKernelGGL((k_edge<E, R>), egrid(v.E, bs), dim3(bs), 0, st, v);
-      break;
-    case K_FLIM:
-      if (v.N > 0) hipLaunchKernelGGL((k_flim<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);
+    case K_FLUX:
+      if (v.N > 0) hipLaunchKernelGGL((k_flux<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);
       break;
     case K_UPDATE:
       if (v.N > 0) hipLaunchKernelGGL((k_update<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);

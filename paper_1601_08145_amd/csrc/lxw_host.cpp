@@ -312,6 +312,14 @@ double basis(int kind, int deg, int l, const double* xi, int dx, int dy, int dz 
   return s;
 }
 
+// phi_l = sum_j coef(l, j) monomial_j on the triangle and the tetrahedron
+double monomial_coef(int kind, int deg, int l, int j) {
+  static const TetBasis tb;
+  static const TriBasis<6> tb2;
+  static const TriBasis<10> tb3;
+  return kind == LXW_TET ? tb.C[l][j] : (deg == 3 ? tb3.C[l][j] : tb2.C[l][j]);
+}
+
 int nverts(int kind) { return kind == LXW_LINE ? 2 : (kind == LXW_QUAD || kind == LXW_TET ? 4 : 3); }
 
 void ref_vertex(int kind, int a, double* xi) {
@@ -449,6 +457,13 @@ void fill_tab(RefTab<E, R>& T) {
         }
     }
   }
+  for (int m = 0; m < E::NI; ++m) {
+    T.wm[m][0] = R(r.w[m]);
+    for (int d = 0; d < E::DIM; ++d) T.wm[m][1 + d] = R(r.w[m] * pts[m * E::DIM + d]);
+  }
+  if constexpr (E::kind == LXW_TRI || E::kind == LXW_TET)
+    for (int l = 0; l < E::ML; ++l)
+      for (int j = 0; j < E::ML; ++j) T.cm[l][j] = R(monomial_coef(E::kind, E::DEG, l, j));
   // in 1D a face is a point with the single weight 2, so that (1/2) sum omega = 1
   for (int j = 0; j < E::NQE; ++j) T.om[j] = R(edge_w<E>(j));
   for (int k = 0; k < E::K; ++k)

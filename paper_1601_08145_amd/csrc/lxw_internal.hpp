@@ -64,6 +64,9 @@ struct RefTab {
                                    // complete P2 on the line and the triangle)
   R d3c[E::ND3][E::ML];            // reference third derivatives (xxx[, xxy, xyy, yyy]): constant
                                    // for complete P3, unused at degree 2
+  R wm[E::NI][1 + E::DIM];         // w_m (1, xi_m): moments of the volume term
+  R cm[E::ML][E::ML];              // basis in monomials (triangle, tetrahedron; the order of lxw.h):
+                                   // phi_l = sum_{j <= l} cm[l][j] monomial_j
   int pperm[6][E::NQE];            // tetrahedron faces: point jl of a face whose vertices are those
                                    // of the first element's face permuted by permutation p is that
                                    // face's point pperm[p][jl] (p = 0 the identity); unused in 1D/2D
@@ -151,15 +154,19 @@ struct View {
 
 // Entry i of a structure-of-arrays column that starts at `col` (a pointer the whole wavefront
 // shares).  The byte offset is formed in 32 bits (i < 2^29, and no column reaches 4 GiB), so the
-// address is the shared base plus the lane's offset: without this the compiler keeps one 64-bit
-// vector address per column live across a burst of loads, which costs more registers than the
-// data itself.
+// address is the shared base in scalar registers plus the lane's offset.  The empty asm hides how the
+// bases of a burst of columns follow from each other: the compiler otherwise forms each one's 64-bit
+// vector address from the last one's, a serial chain of additions, and where the columns are read again
+// (or written) later in the kernel it keeps those addresses, two registers a column, across everything in
+// between (48 of the 216 registers of the float32 triangle's k_elem).
 template <class T>
 __device__ __forceinline__ T& at(T* col, int i) {
+  asm("" : "+s"(col));
   return *reinterpret_cast<T*>(reinterpret_cast<char*>(col) + (unsigned)i * (unsigned)sizeof(T));
 }
 template <class T>
 __device__ __forceinline__ const T& at(const T* col, int i) {
+  asm("" : "+s"(col));
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(col) + (unsigned)i * (unsigned)sizeof(T));
 }
 

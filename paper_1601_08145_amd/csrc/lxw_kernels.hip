@@ -28,6 +28,7 @@
 #include <hip/hip_cooperative_groups.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "lxw_internal.hpp"
@@ -184,82 +185,150 @@ __device__ __forceinline__ R d2p_of(const St<DIM, R>& s, const Var<DIM, R>& va, 
   return -gm1 * s.rho * t;
 }
 
-// F_T = F + dt/2 A q_t + dt^2/6 (H(q_t, q_t) + A q_tt) for every direction d (Eq. (taylor3-flux)
-// with the chain rule of Sec. 2.2; also the ghost-state flux of Sec. 2.4).  A is linear, so its two
-// products are formed as one, A (dt/2 q_t + dt^2/6 q_tt).  The caller passes the state s of q and
-// the variation vt of q_t (the element kernel has them from the time derivatives).
+// Degree 2: q_t, q_tt and F_T through the variations of u, p and H = E + p instead of one Jacobian and
+// one Hessian product per term and direction.  With F_d = (M_d, M_k u_d + p e_d, u_d H) the product rule
+// gives (subscripts t, d: derivatives in time and along x_d; q_t = -D, D = div F^h)
+//   w = M_t - u rho_t = rho u_t,   u_d = (M_d - u rho_d)/rho,
+//   p_x = (gamma-1)(E_x + |u|^2 rho_x / 2 - u.M_x)  for x = t and every d,
+//   p_td = (gamma-1)(E_td + |u|^2 rho_td / 2 - u.M_td - u_d.w),
+//   div u_t = (sum_d [M_d,td - u_d rho_td - u_d,t rho_d] - rho_t div u)/rho,
+//   rho_tt = -div M_t,   M_k,tt = -(u.grad M_k,t + M_k,t div u + u_t.grad M_k + M_k div u_t) - p_tk,
+//   E_tt = -(u.grad H_t + H_t div u + u_t.grad H + H div u_t),
+// about 80 operations per point in 2D where the Jacobian and Hessian products took about 130.
+// Time derivatives come scaled as F_T = F + c1 F_t + c2 F_tt needs them, q1 = c1 q_t and q2 = c2 q_tt with
+// c1 = dt/2, c2 = dt^2/6 (and so w, u_t, p_t, H_t): with gradients of q scaled by c2/c1 = dt/3 and the
+// gradient of D by c2 the formulas above hold as they stand, and a product's average is
+//   a b + c1 (a b)_t + c2 (a b)_tt = a (b + b1 + b2) + a1 (b + 4/3 b1) + a2 b.
 template <int DIM, class R>
-__device__ __forceinline__ void ft_core(const St<DIM, R>& s, const R* qt, const Var<DIM, R>& vt, const R* qtt, R gm1,
-                                        R dt, R FT[DIM][DIM + 2]) {
+struct Pt2 {
+  R r, u[DIM], u2h, p, H;    // 1/rho, velocity, |u|^2/2, pressure, E + p
+  R w[DIM], ut[DIM], pt, Ht;  // rho u_t, u_t, p_t, H_t
+};
+// from the state and q1
+template <int DIM, class R>
+__device__ __forceinline__ Pt2<DIM, R> pt2_of(const R* q, const R* qt, R gm1) {
   constexpr int V = DIM + 2;
-  const R c1 = R(0.5) * dt, c2 = dt * dt * R(1.0 / 6.0);
-  R qc[V];
-#pragma unroll
-  for (int c = 0; c < V; ++c) qc[c] = c1 * qt[c] + c2 * qtt[c];
-  const Var<DIM, R> vc = var1<DIM, R>(s, qc, gm1);
-  const R d2p = d2p_of<DIM, R>(s, vt, vt, gm1);
+  Pt2<DIM, R> s;
+  s.r = recip(q[0]);
+  R mu = R(0);
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
-    R F[V], A[V], H[V];
-    flux<DIM, R>(s, d, F);
-    dflux<DIM, R>(s, d, qc, vc, A);
-    d2flux_sym<DIM, R>(s, d, qt, vt, d2p, H);
-#pragma unroll
-    for (int c = 0; c < V; ++c) FT[d][c] = F[c] + A[c] + c2 * H[c];
+    s.u[d] = q[1 + d] * s.r;
+    mu += q[1 + d] * s.u[d];
   }
-}
-template <int DIM, class R>
-__device__ __forceinline__ void ft_from(const R* q, const R* qt, const R* qtt, R gm1, R dt, R FT[DIM][DIM + 2]) {
-  const St<DIM, R> s = base_state<DIM, R>(q, gm1);
-  ft_core<DIM, R>(s, qt, var1<DIM, R>(s, qt, gm1), qtt, gm1, dt, FT);
-}
-
-// n . F_T for an edge normal n (length included), from the flux along n, F_n = sum_d n_d F_d, and
-// its variations (the directional formulas above summed over d with weights n_d: only u.n, M.n and
-// p n enter), so an edge point forms one normal flux instead of DIM fluxes and a dot product.
-template <int DIM, class R>
-__device__ __forceinline__ R dot_n(const R* x, const R* n) {
-  R t = R(0);
+  mu *= R(0.5);
+  s.u2h = mu * s.r;
+  s.p = gm1 * (q[V - 1] - mu);
+  s.H = q[V - 1] + s.p;
+  R t = qt[V - 1] + s.u2h * qt[0];
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) t += x[d] * n[d];
-  return t;
+  for (int d = 0; d < DIM; ++d) {
+    t -= s.u[d] * qt[1 + d];
+    s.w[d] = qt[1 + d] - s.u[d] * qt[0];
+    s.ut[d] = s.w[d] * s.r;
+  }
+  s.pt = gm1 * t;
+  s.Ht = qt[V - 1] + s.pt;
+  return s;
 }
+// q2 from the scaled gradients of q and of D
 template <int DIM, class R>
-__device__ __forceinline__ void ftn_core(const St<DIM, R>& s, const R* qt, const Var<DIM, R>& vt, const R* qtt,
-                                         const R* n, R gm1, R dt, R* FTn) {
+__device__ __forceinline__ void qtt_of(const Pt2<DIM, R>& s, const R* q, const R* qt, const R gq[DIM][DIM + 2],
+                                       const R gD[DIM][DIM + 2], R gm1, R* qtt) {
   constexpr int V = DIM + 2;
-  const R c1 = R(0.5) * dt, c2 = dt * dt * R(1.0 / 6.0);
-  R qc[V];  // one Jacobian product A_n (dt/2 q_t + dt^2/6 q_tt), as in ft_core
+  R divu = R(0), sum = R(0), rtt = R(0), ett = R(0), m[DIM], ptd[DIM];
 #pragma unroll
-  for (int c = 0; c < V; ++c) qc[c] = c1 * qt[c] + c2 * qtt[c];
-  const Var<DIM, R> vc = var1<DIM, R>(s, qc, gm1);
-  const R d2p = d2p_of<DIM, R>(s, vt, vt, gm1);
-  const R un = dot_n<DIM, R>(s.u, n), mn = dot_n<DIM, R>(s.m, n);
-  const R dun = dot_n<DIM, R>(vt.du, n), dcn = dot_n<DIM, R>(vc.du, n);
-  const R d2un = -R(2) * dun * qt[0] * s.r;  // (d2u[qt, qt]) . n
-  R an = R(0);
+  for (int k = 0; k < DIM; ++k) m[k] = R(0);
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) an += qc[1 + d] * n[d];
-  // F_n + A_n qc + dt^2/6 H_n(q_t, q_t)
-  FTn[0] = mn + an;
+  for (int d = 0; d < DIM; ++d) {
+    const R* g = gq[d];
+    const R* h = gD[d];
+    R pd = g[V - 1] + s.u2h * g[0], pt = h[V - 1] + s.u2h * h[0];
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) {
-    const R F = s.m[k] * un + s.p * n[k];
-    const R A = qc[1 + k] * un + s.m[k] * dcn + vc.dp * n[k];
-    const R H = R(2) * qt[1 + k] * dun + s.m[k] * d2un + d2p * n[k];
-    FTn[1 + k] = F + A + c2 * H;
+    for (int k = 0; k < DIM; ++k) {
+      const R ud = (g[1 + k] - s.u[k] * g[0]) * s.r;
+      pd -= s.u[k] * g[1 + k];
+      pt -= s.u[k] * h[1 + k];
+      pt += ud * s.w[k];  // h is the gradient of -q_t
+      if (k == d) divu += ud;
+    }
+    pd *= gm1;
+    ptd[d] = gm1 * pt;  // -p_td
+    // sum: rho div u_t + rho_t div u
+    sum -= h[1 + d] - s.u[d] * h[0] + s.ut[d] * g[0];
+    rtt += h[1 + d];
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) m[k] += s.u[d] * h[1 + k] - s.ut[d] * g[1 + k];
+    ett += s.u[d] * (h[V - 1] + ptd[d]) - s.ut[d] * (g[V - 1] + pd);
   }
-  {
-    const R F = un * s.Ep;
-    const R A = dcn * s.Ep + un * (qc[V - 1] + vc.dp);
-    const R H = d2un * s.Ep + R(2) * dun * (qt[V - 1] + vt.dp) + un * d2p;
-    FTn[V - 1] = F + A + c2 * H;
+  const R divut = (sum - qt[0] * divu) * s.r;
+  qtt[0] = rtt;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) qtt[1 + k] = m[k] - qt[1 + k] * divu - q[1 + k] * divut + ptd[k];
+  qtt[V - 1] = ett - s.Ht * divu - s.H * divut;
+}
+// c2 p_tt
+template <int DIM, class R>
+__device__ __forceinline__ R ptt_of(const Pt2<DIM, R>& s, const R* q2, R gm1) {
+  constexpr int V = DIM + 2;
+  R t = q2[V - 1] + s.u2h * q2[0], ww = R(0);
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    t -= s.u[d] * q2[1 + d];
+    ww += s.w[d] * s.ut[d];
+  }
+  return gm1 * (t - R(2.0 / 3.0) * ww);
+}
+// F_T (Eq. (taylor3-flux)) in every direction (M_k u_d = M_d u_k: the momentum part is symmetric)
+template <int DIM, class R>
+__device__ __forceinline__ void ft2(const Pt2<DIM, R>& s, const R* q, const R* q1, const R* q2, R gm1,
+                                    R FT[DIM][DIM + 2]) {
+  constexpr int V = DIM + 2;
+  const R ptt = ptt_of<DIM, R>(s, q2, gm1);
+  const R pb = s.p + s.pt + ptt, Htt = q2[V - 1] + ptt;
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    const R v1 = R(4.0 / 3.0) * s.ut[d];
+    const R utt = (q2[1 + d] - s.u[d] * q2[0] - v1 * q1[0]) * s.r;
+    const R B = s.u[d] + s.ut[d] + utt, X = s.u[d] + v1, Y = s.u[d];
+    FT[d][0] = q[1 + d] + q1[1 + d] + q2[1 + d];
+#pragma unroll
+    for (int k = d; k < DIM; ++k) {
+      R f = q[1 + k] * B + q1[1 + k] * X + q2[1 + k] * Y;
+      if (k == d) f += pb;
+      FT[d][1 + k] = f;
+      FT[k][1 + d] = f;
+    }
+    FT[d][V - 1] = s.H * B + s.Ht * X + Htt * Y;
   }
 }
+// along a normal n: n . F_T
 template <int DIM, class R>
-__device__ __forceinline__ void ftn_from(const R* q, const R* qt, const R* qtt, const R* n, R gm1, R dt, R* FTn) {
-  const St<DIM, R> s = base_state<DIM, R>(q, gm1);
-  ftn_core<DIM, R>(s, qt, var1<DIM, R>(s, qt, gm1), qtt, n, gm1, dt, FTn);
+__device__ __forceinline__ void ftn2(const Pt2<DIM, R>& s, const R* q, const R* q1, const R* q2, const R* n, R gm1,
+                                     R* FTn) {
+  constexpr int V = DIM + 2;
+  const R ptt = ptt_of<DIM, R>(s, q2, gm1);
+  const R pb = s.p + s.pt + ptt, Htt = q2[V - 1] + ptt;
+  R un = s.u[0] * n[0], utn = s.ut[0] * n[0], mttn = q2[1] * n[0], mn = (q[1] + q1[1] + q2[1]) * n[0];
+#pragma unroll
+  for (int d = 1; d < DIM; ++d) {
+    un += s.u[d] * n[d];
+    utn += s.ut[d] * n[d];
+    mttn += q2[1 + d] * n[d];
+    mn += (q[1 + d] + q1[1 + d] + q2[1 + d]) * n[d];
+  }
+  const R v1 = R(4.0 / 3.0) * utn;
+  const R uttn = (mttn - un * q2[0] - v1 * q1[0]) * s.r;
+  const R B = un + utn + uttn, X = un + v1;
+  FTn[0] = mn;
+#pragma unroll
+  for (int k = 0; k < DIM; ++k) FTn[1 + k] = q[1 + k] * B + q1[1 + k] * X + q2[1 + k] * un + pb * n[k];
+  FTn[V - 1] = s.H * B + s.Ht * X + Htt * un;
+}
+// the same from a state and its scaled time derivatives alone (ghost states of Sec. 2.4)
+template <int DIM, class R>
+__device__ __forceinline__ void ftn_from(const R* q, const R* q1, const R* q2, const R* n, R gm1, R* FTn) {
+  ftn2<DIM, R>(pt2_of<DIM, R>(q, q1, gm1), q, q1, q2, n, gm1, FTn);
 }
 
 // Degree 3: the third variation F^(3)_d(a, b, c), through the third variations of u and p (the
@@ -856,6 +925,29 @@ __device__ __forceinline__ void store_rec(R* p, const R (&x)[V]) {
   }
 }
 
+// V values of one record at p (consecutive)
+template <class R, int V>
+__device__ __forceinline__ void load_rec(const R* p, R (&x)[V]) {
+  if constexpr ((V * sizeof(R)) % 16 == 0) {
+    typedef R vec __attribute__((ext_vector_type(V)));
+    const vec t = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int c = 0; c < V; ++c) x[c] = t[c];
+  } else {
+#pragma unroll
+    for (int c = 0; c < V; ++c) x[c] = p[c];
+  }
+}
+
+// x, formed here as far as the compiler can see: what a rare branch computes from it stays in that
+// branch instead of being moved ahead of the loop around it (45 operations per edge, for every element,
+// that only boundary edges need).
+template <class R>
+__device__ __forceinline__ R here(R x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // Index of the second reference derivative d/dxi_a d/dxi_b in the tables (2D: xx, xy, yy; 3D:
 // xx, xy, xz, yy, yz, zz).
 template <int DIM>
@@ -864,9 +956,424 @@ __device__ __forceinline__ constexpr int sidx(int a, int b) {
   return DIM == 3 ? (a == 0 ? b : (a == 1 ? 2 + b : 5)) : a + b;
 }
 
+// P2 on triangles and tetrahedra (affine elements): everything at a point comes from polynomial
+// coefficients formed once per element.
+//  * The limited state q_bar + theta sum_l Q_l phi_l as monomial coefficients a in float64 (the basis in
+//    monomials is the table cm), evaluated by Horner's rule and rounded to the bulk type; on an edge of a
+//    triangle it is a quadratic in one variable.  Interior states serve twice (projection and F_T): they
+//    wait in LDS between the two where they fit.
+//  * grad q in physical coordinates as an affine function of the reference point, G0 + Hx . xi.
+//  * div F^h and its gradient: Step 1's projection composed with div (and its gradient) at the origin is
+//    a fixed table (kd0, kd1), so F^h is never formed; the mass flux M is its own projection, so its
+//    divergence comes from grad q.
+// The edges come before the volume term: the coefficients a are dead by the time its accumulators live,
+// and the modes are read again for the update.
+//
+// Bound by instruction issue: 3,700 VALU instructions per wavefront of float32 triangles (5,870 with
+// Jacobian and Hessian products, states evaluated mode by mode and every V_l accumulated at every point):
+// 168 -> 129 us on 999,698 triangles; float64 250k 78 -> 58 us; tetrahedra 467 -> 307 us (280k, FP32-mixed)
+// and 163 -> 104 us (25k, float64).
 template <class E, class R>
-struct ElemOcc { static constexpr int waves = (E::kind == ElTri::kind && E::DEG == 2 && sizeof(R) == 4) ? 2 : 1; };
+struct ElemShape {
+  // interior states kept in LDS per lane, where four wavefronts per CU still fit (float64 tetrahedra form
+  // them twice)
+  static constexpr bool keep = (E::kind == ElTri::kind && E::DEG == 2) || (E::DIM == 3 && sizeof(R) == 4);
+  static constexpr int lds = keep ? E::NI * E::V * (int)sizeof(R) : 0;
+  // Waves per SIMD the register allocation targets, the most that spill next to nothing: three for float32
+  // triangles (168 registers, 8 bytes of scratch a lane; 129 us on 999,698 against 138 at two), two for
+  // float64 triangles (58 / 65 us on 250k) and the float32 square (111 / 153 us on 262k), one elsewhere
+  // (float32 tetrahedra: their states fill the LDS with one; 307 us on 280k, 463 at two without them).
+  static constexpr int waves = E::DEG == 3 || E::DIM != 2 ? 1 : (E::kind == ElTri::kind ? (sizeof(R) == 4 ? 3 : 2) : (sizeof(R) == 4 ? 2 : 1));
+};
 
+template <class E, class R>
+__device__ __forceinline__ void elem_affine(View<R> v, const int i) {
+  constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
+  constexpr bool keep = ElemShape<E, R>::keep;
+  const RefTab<E, R>& T = TabSel<E, R>::get();
+  const RefTab<E, double>& TD = TabSel<E, double>::get();
+  const int N = v.N;
+  if (i >= N) return;
+  const int mid = mesh_id<R>(v.mesh_of, i);
+  // At the end time the step changes nothing: the stored modes are written back as they were.
+  // The flag is applied at the store (not by an early return), so its load overlaps the others.
+  const bool idle = v.sc[mid].idle;
+  const R dt = R(v.sc[mid].dt);
+  const R gm1 = R(v.gamma - 1.0);
+  extern __shared__ __align__(16) unsigned char dyn[];
+  R* sq = reinterpret_cast<R*>(dyn);
+
+  // monomial coefficients of the limited state
+  const double th = at(v.theta, i);
+  double a[V][ML];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    const double qb = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb;  // the step's averages, for the edge fluxes (k_flux, k_update)
+    double Q[ML - 1];
+#pragma unroll
+    for (int l = 1; l < ML; ++l) Q[l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
+#pragma unroll
+    for (int m = 0; m < ML; ++m) {
+      double acc = 0.0;
+#pragma unroll
+      for (int l = (m > 1 ? m : 1); l < ML; ++l) acc += Q[l - 1] * TD.cm[l][m];
+      a[c][m] = m == 0 ? qb + th * acc : th * acc;
+    }
+  }
+  // the map's gradient scaled for q's gradients (dt/3) and for D (c1 = dt/2), see Pt2
+  R JG[DIM][DIM], JC[DIM][DIM];
+#pragma unroll
+  for (int x = 0; x < DIM; ++x)
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      const R J = at(v.Jinv + (size_t)(x * DIM + d) * N, i);
+      JG[x][d] = dt * R(1.0 / 3.0) * J;
+      JC[x][d] = R(0.5) * dt * J;
+    }
+
+  auto state_at = [&](int p, R* q) {
+    const double x = TD.xr[p][0], y = TD.xr[p][1];
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      const double* A = a[c];
+      if constexpr (DIM == 2) {
+        const double px = A[1] + x * A[3] + y * A[4], py = A[2] + y * A[5];
+        q[c] = R(A[0] + x * px + y * py);
+      } else {
+        const double z = TD.xr[p][2];
+        const double px = A[1] + x * A[4] + y * A[5] + z * A[6], py = A[2] + y * A[7] + z * A[8], pz = A[3] + z * A[9];
+        q[c] = R(A[0] + x * px + y * py + z * pz);
+      }
+    }
+  };
+
+  // (dt/3) grad q at the reference point xi: G0[d][c] + sum_b Hx[b][d][c] xi_b
+  R G0[DIM][V], Hx[DIM][DIM][V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    R g[DIM], h[DIM][DIM];  // reference gradient at the origin and (symmetric) Hessian
+    if constexpr (DIM == 2) {
+      g[0] = R(a[c][1]); g[1] = R(a[c][2]);
+      h[0][0] = R(2) * R(a[c][3]); h[0][1] = h[1][0] = R(a[c][4]); h[1][1] = R(2) * R(a[c][5]);
+    } else {
+      g[0] = R(a[c][1]); g[1] = R(a[c][2]); g[DIM - 1] = R(a[c][3]);
+      h[0][0] = R(2) * R(a[c][4]); h[0][1] = h[1][0] = R(a[c][5]); h[0][DIM - 1] = h[DIM - 1][0] = R(a[c][6 % ML]);
+      h[1][1] = R(2) * R(a[c][7 % ML]); h[1][DIM - 1] = h[DIM - 1][1] = R(a[c][8 % ML]); h[DIM - 1][DIM - 1] = R(2) * R(a[c][9 % ML]);
+    }
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      R t = R(0);
+#pragma unroll
+      for (int x = 0; x < DIM; ++x) t += JG[x][d] * g[x];
+      G0[d][c] = t;
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) {
+        R w = R(0);
+#pragma unroll
+        for (int x = 0; x < DIM; ++x) w += JG[x][d] * h[x][b];
+        Hx[b][d][c] = w;
+      }
+    }
+  }
+
+  // Sec. 2.3 Step 1 composed with div: D0 = c1 div F^h and gDr = its reference gradient, at the origin
+  R D0[V], gDr[V][DIM];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    D0[c] = R(0);
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) gDr[c][b] = R(0);
+  }
+#pragma unroll
+  for (int d = 0; d < DIM; ++d) {
+    D0[0] += R(1.5) * G0[d][1 + d];
+#pragma unroll
+    for (int b = 0; b < DIM; ++b) gDr[0][b] += R(1.5) * Hx[b][d][1 + d];
+  }
+#pragma unroll 1
+  for (int m = 0; m < NI; ++m) {
+    R q[V];
+    state_at(m, q);
+    if constexpr (keep) {
+      R* p = sq + ((size_t)m * blockDim.x + threadIdx.x) * V;
+      store_rec<R, V>(p, q);
+    }
+    const St<DIM, R> s = base_state<DIM, R>(q, gm1);
+    R F[DIM][V];
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) flux<DIM, R>(s, d, F[d]);
+#pragma unroll
+    for (int x = 0; x < DIM; ++x)
+#pragma unroll
+      for (int c = 1; c < V; ++c) {
+        R fc = R(0);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) fc += JC[x][d] * F[d][c];
+        D0[c] += T.kd0[m][x] * fc;
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) gDr[c][b] += T.kd1[m][x][b] * fc;
+      }
+  }
+  R gD[DIM][V];  // c2 times the physical gradient of D, constant
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+      R t = R(0);
+#pragma unroll
+      for (int x = 0; x < DIM; ++x) t += JG[x][d] * gDr[c][x];
+      gD[d][c] = t;
+    }
+
+  // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
+  const double hs0 = 0.5 * v.sc[mid].s;
+  auto edge_point = [&](const R* n, R hs, R len2, int slot, int jj, const R* q, const R (&gq)[DIM][V], const R* D) {
+    const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
+    R qt[V], qtt[V], fn[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) qt[c] = -D[c];
+    const Pt2<DIM, R> s = pt2_of<DIM, R>(q, qt, gm1);
+    qtt_of<DIM, R>(s, q, qt, gq, gD, gm1, qtt);
+    ftn2<DIM, R>(s, q, qt, qtt, n, gm1, fn);
+    R b[V];  // n is half the normal
+#pragma unroll
+    for (int c = 0; c < V; ++c) b[c] = fn[c] + hs * q[c];
+    store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
+    if (bc != SB_INTERIOR) {
+      R qg[V], fgn[V], nb[DIM];
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) nb[d] = here(n[d]);
+      if (bc == SB_TRANSPARENT) {
+#pragma unroll
+        for (int c = 0; c < V; ++c) { qg[c] = q[c]; fgn[c] = fn[c]; }
+      } else if (bc == SB_REFLECTIVE) {
+        R nh[DIM];
+        const R il = R(1) / sqrt(here(len2));
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) nh[d] = nb[d] * il;
+        R qtg[V], qttg[V];
+        reflect<DIM, R>(q, nh, qg);
+        reflect<DIM, R>(qt, nh, qtg);
+        reflect<DIM, R>(qtt, nh, qttg);
+        ftn_from<DIM, R>(qg, qtg, qttg, nb, gm1, fgn);
+      } else {
+        R z[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) z[c] = R(0);
+        inflow_state<DIM, R>(v.inflow, qg);
+        qg[0] = here(qg[0]);
+        ftn_from<DIM, R>(qg, z, z, nb, gm1, fgn);
+      }
+      // the ghost is side 1: its outward normal is -n
+      R bg[V];
+#pragma unroll
+      for (int c = 0; c < V; ++c) bg[c] = hs * qg[c] - fgn[c];
+      store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
+    }
+  };
+  // s |n_e| / 2: both elements of an edge hold the same normal up to sign, so they form it alike
+  auto load_normal = [&](int k, R* n) {
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) n[d] = at(v.nout + (size_t)(k * DIM + d) * N, i);
+  };
+  // (then n is halved, for the trace's factor 1/2, and len2 with it)
+  auto half_speed = [&](R* n, R& len2) {
+    len2 = R(0);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) len2 += n[d] * n[d];
+    const R hs = R(hs0 * double(sqrt(len2)));
+    len2 *= R(0.25);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) n[d] *= R(0.5);
+    return hs;
+  };
+  if constexpr (DIM == 2) {
+    // every edge's slot and normal before the first trace is stored (a store holds later loads back)
+    int slots[K];
+    R nk[K][DIM];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      slots[k] = at(v.eslot + (size_t)k * N, i);
+      load_normal(k, nk[k]);
+    }
+    // along edge k the reference point is (t, 0), (1 - t, t), (0, t), t one of its coordinates; edge 1,
+    // whose coefficients are sums, last: the others' are the element's own
+#pragma unroll
+    for (int x = 0; x < K; ++x) {
+      const int k = x == 0 ? 0 : 3 - x;
+      const int slot = slots[k];
+      R* n = nk[k];
+      R len2;
+      const R hs = half_speed(n, len2);
+      double e0[V], e1[V], e2[V];
+      R g0[DIM][V], g1[DIM][V], d0[V], d1[V];
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        const double* A = a[c];
+        e0[c] = k == 1 ? A[0] + A[1] + A[3] : A[0];
+        e1[c] = k == 0 ? A[1] : (k == 1 ? A[2] - A[1] - 2.0 * A[3] + A[4] : A[2]);
+        e2[c] = k == 0 ? A[3] : (k == 1 ? A[3] - A[4] + A[5] : A[5]);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+          g0[d][c] = k == 1 ? G0[d][c] + Hx[0][d][c] : G0[d][c];
+          g1[d][c] = k == 0 ? Hx[0][d][c] : (k == 1 ? Hx[1][d][c] - Hx[0][d][c] : Hx[1][d][c]);
+        }
+        d0[c] = k == 1 ? D0[c] + gDr[c][0] : D0[c];
+        d1[c] = k == 0 ? gDr[c][0] : (k == 1 ? gDr[c][1] - gDr[c][0] : gDr[c][1]);
+      }
+#pragma unroll 1
+      for (int jl = 0; jl < NQE; ++jl) {
+        const int p = NI + k * NQE + jl;
+        const double td = TD.xr[p][k == 0 ? 0 : 1];
+        const R t = T.xr[p][k == 0 ? 0 : 1];
+        R q[V], gq[DIM][V], D[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+          q[c] = R(e0[c] + td * (e1[c] + td * e2[c]));
+#pragma unroll
+          for (int d = 0; d < DIM; ++d) gq[d][c] = g0[d][c] + g1[d][c] * t;
+          D[c] = d0[c] + d1[c] * t;
+        }
+        // point order of i_e along the edge: reversed on the other side
+        edge_point(n, hs, len2, slot, ((slot >> 2) & 1) ? NQE - 1 - jl : jl, q, gq, D);
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+      const int slot = at(v.eslot + (size_t)k * N, i);
+      const int perm = at(v.fperm + (size_t)k * N, i);
+      R n[DIM], len2;
+      load_normal(k, n);
+      const R hs = half_speed(n, len2);
+#pragma unroll 1
+      for (int jl = 0; jl < NQE; ++jl) {
+        const int p = NI + k * NQE + jl;
+        R q[V], gq[DIM][V], D[V];
+        state_at(p, q);
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+          D[c] = D0[c];
+#pragma unroll
+          for (int b = 0; b < DIM; ++b) D[c] += gDr[c][b] * T.xr[p][b];
+#pragma unroll
+          for (int d = 0; d < DIM; ++d) {
+            gq[d][c] = G0[d][c];
+#pragma unroll
+            for (int b = 0; b < DIM; ++b) gq[d][c] += Hx[b][d][c] * T.xr[p][b];
+          }
+        }
+        edge_point(n, hs, len2, slot, T.pperm[perm][jl], q, gq, D);
+      }
+    }
+  }
+
+  // interior points: volume term V_l = sum_m w_m grad phi_l . F_T, as the moments S = sum_m w_m
+  // (1, xi) F_T (grad phi_l is linear) and their sums once per element: about half the operations of
+  // accumulating every V_l at every point
+  constexpr int NM = 1 + DIM;
+  R S[NM][DIM][V];
+#pragma unroll
+  for (int y = 0; y < NM; ++y)
+#pragma unroll
+    for (int d = 0; d < DIM; ++d)
+#pragma unroll
+      for (int c = 0; c < V; ++c) S[y][d][c] = R(0);
+#pragma unroll 1
+  for (int m = 0; m < NI; ++m) {
+    R q[V], qt[V], qtt[V], gq[DIM][V], FT[DIM][V];
+    if constexpr (keep) load_rec<R, V>(sq + ((size_t)m * blockDim.x + threadIdx.x) * V, q);
+    else state_at(m, q);
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      R D = D0[c];
+#pragma unroll
+      for (int b = 0; b < DIM; ++b) D += gDr[c][b] * T.xr[m][b];
+      qt[c] = -D;
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) {
+        gq[d][c] = G0[d][c];
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) gq[d][c] += Hx[b][d][c] * T.xr[m][b];
+      }
+    }
+    const Pt2<DIM, R> s = pt2_of<DIM, R>(q, qt, gm1);
+    qtt_of<DIM, R>(s, q, qt, gq, gD, gm1, qtt);
+    ft2<DIM, R>(s, q, qt, qtt, gm1, FT);
+#pragma unroll
+    for (int d = 0; d < DIM; ++d)
+#pragma unroll
+      for (int c = 0; c < V; ++c)
+        if (c < 1 + d || c == V - 1 || c == 1 + d)  // F_T's momentum part is symmetric: below the diagonal as above
+#pragma unroll
+          for (int y = 0; y < NM; ++y) S[y][d][c] += T.wm[m][y] * FT[d][c];
+  }
+#pragma unroll
+  for (int d = 0; d < DIM; ++d)
+#pragma unroll
+    for (int k = 0; k < d; ++k)
+#pragma unroll
+      for (int y = 0; y < NM; ++y) S[y][k][1 + d] = S[y][d][1 + k];
+
+  // Sec. 2.3 Step 3 / Sec. 3.3 Step 6, volume part: Q^(l) += dt V_l for l >= 2
+  // (every load before the first store: a store to the modes would hold the next load back)
+  const R thR = R(th);
+  R old[V][ML - 1];
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int l = 0; l < ML - 1; ++l) old[c][l] = at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i);
+  R Ji[DIM][DIM], vol[V][ML - 1];
+#pragma unroll
+  for (int x = 0; x < DIM; ++x)
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) Ji[x][d] = at(v.Jinv + (size_t)(x * DIM + d) * N, i);
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    // contravariant moments, then the monomials' volume terms (gradients 1, 1, 2x, y and x, 2y, ...), then
+    // the basis functions'
+    R Sc[NM][DIM], mono[ML - 1];
+#pragma unroll
+    for (int y = 0; y < NM; ++y)
+#pragma unroll
+      for (int x = 0; x < DIM; ++x) {
+        R t = R(0);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) t += Ji[x][d] * S[y][d][c];
+        Sc[y][x] = t;
+      }
+#pragma unroll
+    for (int x = 0; x < DIM; ++x) mono[x] = Sc[0][x];
+    int j = DIM;
+#pragma unroll
+    for (int x = 0; x < DIM; ++x)
+#pragma unroll
+      for (int y = x; y < DIM; ++y) mono[j++] = x == y ? R(2) * Sc[1 + x][x] : Sc[1 + y][x] + Sc[1 + x][y];
+#pragma unroll
+    for (int l = 1; l < ML; ++l) {
+      R t = R(0);
+#pragma unroll
+      for (int z = 1; z <= l; ++z) t += T.cm[l][z] * mono[z - 1];
+      vol[c][l - 1] = t;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int l = 0; l < ML - 1; ++l)
+      at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = idle ? old[c][l] : thR * old[c][l] + dt * vol[c][l];
+  if (v.dbg_vol) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      v.dbg_vol[(c * ML) * N + i] = 0.0;
+#pragma unroll
+      for (int l = 1; l < ML; ++l) v.dbg_vol[(c * ML + l) * N + i] = double(vol[c][l - 1]);
+    }
+  }
+}
+
+// P2 on the line and Q2 on the square.
 template <class E, class R>
 __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
@@ -889,15 +1396,17 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
     qb[c] = v.Qbar[(size_t)i * V + c];
     v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
-    for (int l = 1; l < ML; ++l) Qr[c][l - 1] = v.Qh[(c * (ML - 1) + l - 1) * N + i];
+    for (int l = 1; l < ML; ++l) Qr[c][l - 1] = at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i);
   }
-  const double th = v.theta[i];
+  const double th = at(v.theta, i);
   const R thR = R(th);
   R Ji[DIM][DIM];
 #pragma unroll
   for (int a = 0; a < DIM; ++a)
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) Ji[a][d] = v.Jinv[(a * DIM + d) * N + i];
+    for (int d = 0; d < DIM; ++d) Ji[a][d] = at(v.Jinv + (size_t)(a * DIM + d) * N, i);
+  // scaled for q's gradients and for F^h (D comes out as c1 D, its gradient as c2 grad D), see Pt2
+  const R sg3 = dt * R(1.0 / 3.0), sc1 = R(0.5) * dt;
 
   // point state of the limited polynomial in float64, q_bar + theta sum_l Q_l phi_l (the
   // expression the moment limiter made positive), then rounded to the bulk precision
@@ -911,33 +1420,19 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
     }
   };
 
-  // Complete P2 on an affine element (line, triangle, tetrahedron): grad q and div F^h are linear
-  // and their derivatives constant, so they are formed once per element from their values at the
-  // reference origin and the constant reference Hessians, and each point costs a few multiply-adds.
-  // In 2D and 3D F^h itself is never needed: Step 1's projection composed with div (and its
-  // gradient) at the origin is a fixed table (kd0, kd1), and D0 = div F^h(0) and gDr = grad div F^h
-  // accumulate directly from the quadrature values.  (1D, three modes, forms F^h as before; on the
-  // tensor Q2 quadrilateral they are not linear, and those points contract F^h and the modes
-  // directly.)
-  constexpr bool AFF = E::kind != ElQuad::kind;
-  constexpr bool KD = AFF && DIM >= 2;
+  // P2 on the line: grad q and div F^h are linear and their derivatives constant, so they are formed
+  // once per element from their values at the reference origin.  On the tensor Q2 square they are not
+  // linear: its points contract F^h and the modes directly.
+  constexpr bool AFF = DIM == 1;
   // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m)
   R Fh[DIM][V][ML];
   R D0[V], gDr[V][DIM];
 #pragma unroll
-  for (int c = 0; c < V; ++c) {
-    D0[c] = R(0);
+  for (int a = 0; a < DIM; ++a)
 #pragma unroll
-    for (int b = 0; b < DIM; ++b) gDr[c][b] = R(0);
-  }
-  if constexpr (!KD) {
+    for (int c = 0; c < V; ++c)
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-      for (int c = 0; c < V; ++c)
-#pragma unroll
-        for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
-  }
+      for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
   for (int m = 0; m < NI; ++m) {
     R q[V];
     state_at(m, q);
@@ -952,14 +1447,9 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
         R fc = R(0);
 #pragma unroll
         for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * F[d][c];
-        if constexpr (KD) {
-          D0[c] += T.kd0[m][a] * fc;
+        fc *= sc1;
 #pragma unroll
-          for (int b = 0; b < DIM; ++b) gDr[c][b] += T.kd1[m][a][b] * fc;
-        } else {
-#pragma unroll
-          for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
-        }
+        for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
       }
   }
 
@@ -973,16 +1463,14 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   if constexpr (AFF) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
-      if constexpr (!KD) {  // 1D: div F^h and its derivative at the origin from F^h
-        R dd = R(0), h = R(0);
+      R dd = R(0), hh = R(0);  // div F^h and its derivative at the origin
 #pragma unroll
-        for (int l = 0; l < ML; ++l) {
-          dd += Fh[0][c][l] * T.dphi0[0][l];
-          h += Fh[0][c][l] * T.d2c[0][l];
-        }
-        D0[c] = dd;
-        gDr[c][0] = h;
+      for (int l = 0; l < ML; ++l) {
+        dd += Fh[0][c][l] * T.dphi0[0][l];
+        hh += Fh[0][c][l] * T.d2c[0][l];
       }
+      D0[c] = dd;
+      gDr[c][0] = hh;
 #pragma unroll
       for (int a = 0; a < DIM; ++a) {
         R acc = R(0);
@@ -1002,14 +1490,13 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
         R sh = R(0);
 #pragma unroll
         for (int a = 0; a < DIM; ++a) sh += Ji[a][d] * gDr[c][a];
-        gDx[d][c] = sh;
+        gDx[d][c] = sg3 * sh;
       }
     }
   }
 
-  // Sec. 2.3 Step 2 at point p: q, grad q, D = div F^h, grad D, then q_t, q_tt and F_T; also the
-  // state s of q and the variation vt of q_t, which F_T needs.
-  auto derivs = [&](int p, R* q, R* qt, R* qtt, St<DIM, R>& s, Var<DIM, R>& vt) {
+  // Sec. 2.3 Step 2 at point p: q, grad q, D = div F^h, grad D, then q_t, q_tt and what F_T needs.
+  auto derivs = [&](int p, R* q, R* qt, R* qtt) {
     R gq[DIM][V], D[V], gD[DIM][V];
     state_at(p, q);
     if constexpr (AFF) {
@@ -1019,25 +1506,14 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
 #pragma unroll
       for (int c = 0; c < V; ++c) {
         R g[DIM];
-        if constexpr (DIM == 1) {
-          g[0] = g0[c][0] + Hq[c][0] * x[0];
-          D[c] = D0[c] + gDr[c][0] * x[0];
-        } else if constexpr (DIM == 2) {
-          g[0] = g0[c][0] + Hq[c][0] * x[0] + Hq[c][1] * x[1];
-          g[1] = g0[c][1] + Hq[c][1] * x[0] + Hq[c][2] * x[1];
-          D[c] = D0[c] + gDr[c][0] * x[0] + gDr[c][1] * x[1];
-        } else {
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-            g[a] = g0[c][a] + Hq[c][sidx<3>(a, 0)] * x[0] + Hq[c][sidx<3>(a, 1)] * x[1] + Hq[c][sidx<3>(a, 2)] * x[2];
-          D[c] = D0[c] + gDr[c][0] * x[0] + gDr[c][1] * x[1] + gDr[c][2] * x[2];
-        }
+        g[0] = g0[c][0] + Hq[c][0] * x[0];
+        D[c] = D0[c] + gDr[c][0] * x[0];
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
           R sg = R(0);
 #pragma unroll
           for (int a = 0; a < DIM; ++a) sg += Ji[a][d] * g[a];
-          gq[d][c] = sg;
+          gq[d][c] = sg3 * sg;
           gD[d][c] = gDx[d][c];
         }
       }
@@ -1068,45 +1544,23 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
           R sg = R(0), sh = R(0);
 #pragma unroll
           for (int a = 0; a < DIM; ++a) { sg += Ji[a][d] * g[a]; sh += Ji[a][d] * h[a]; }
-          gq[d][c] = thR * sg;
-          gD[d][c] = sh;
+          gq[d][c] = (sg3 * thR) * sg;
+          gD[d][c] = sg3 * sh;
         }
       }
     }
-    s = base_state<DIM, R>(q, gm1);
-    const Var<DIM, R> vD = var1<DIM, R>(s, D, gm1);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) vt.du[d] = -vD.du[d];  // var1 is linear: q_t = -D
-    vt.dp = -vD.dp;
-#pragma unroll
-    for (int c = 0; c < V; ++c) { qt[c] = -D[c]; qtt[c] = R(0); }
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      Var<DIM, R> vq = var1<DIM, R>(s, gq[d], gm1);
-      Var<DIM, R> vg = var1<DIM, R>(s, gD[d], gm1);
-      R d2p = d2p_of<DIM, R>(s, vq, vD, gm1);
-      R H[V], A[V];
-      d2flux<DIM, R>(s, d, gq[d], vq, D, vD, d2p, H);
-      dflux<DIM, R>(s, d, gD[d], vg, A);
-#pragma unroll
-      for (int c = 0; c < V; ++c) qtt[c] += H[c] + A[c];
-    }
-  };
-  // In 3D the state and q_t's variation are formed again from q and q_t instead of being held across
-  // the call: at one wave per SIMD the float64 tetrahedron kernel then spills less (820 instead of
-  // 924 bytes per lane).
-  auto point = [&](int p, R* q, R* qt, R* qtt, R FT[DIM][V]) {
-    St<DIM, R> s;
-    Var<DIM, R> vt;
-    derivs(p, q, qt, qtt, s, vt);
-    if constexpr (DIM == 3) ft_from<DIM, R>(q, qt, qtt, gm1, dt, FT);
-    else ft_core<DIM, R>(s, qt, vt, qtt, gm1, dt, FT);
+    for (int c = 0; c < V; ++c) qt[c] = -D[c];
+    const Pt2<DIM, R> s = pt2_of<DIM, R>(q, qt, gm1);
+    qtt_of<DIM, R>(s, q, qt, gq, gD, gm1, qtt);
+    return s;
   };
 
   // interior points: volume term V_l = sum_m w_m grad phi_l . F_T
   for (int m = 0; m < NI; ++m) {
     R q[V], qt[V], qtt[V], FT[DIM][V];
-    point(m, q, qt, qtt, FT);
+    const Pt2<DIM, R> s = derivs(m, q, qt, qtt);
+    ft2<DIM, R>(s, q, qt, qtt, gm1, FT);
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -1125,7 +1579,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   for (int c = 0; c < V; ++c)
 #pragma unroll
     for (int l = 1; l < ML; ++l)
-      v.Qh[(c * (ML - 1) + l - 1) * N + i] = idle ? Qr[c][l - 1] : thR * Qr[c][l - 1] + dt * vol[c][l - 1];
+      at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i) = idle ? Qr[c][l - 1] : thR * Qr[c][l - 1] + dt * vol[c][l - 1];
   if (v.dbg_vol) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
@@ -1138,36 +1592,20 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
   const double hs0 = 0.5 * v.sc[mid].s;
   for (int k = 0; k < K; ++k) {
-    const int slot = v.eslot[k * N + i];
+    const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
-    const int perm = (DIM == 3) ? v.fperm[k * N + i] : 0;
     R n[DIM], len2 = R(0);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) { n[d] = v.nout[(k * DIM + d) * N + i]; len2 += n[d] * n[d]; }
+    for (int d = 0; d < DIM; ++d) { n[d] = at(v.nout + (size_t)(k * DIM + d) * N, i); len2 += n[d] * n[d]; }
     // s |n_e| / 2: both elements of an edge hold the same normal up to sign, so they form it alike
     const R hs = R(hs0 * double(sqrt(len2)));
     for (int jl = 0; jl < NQE; ++jl) {
       const int p = NI + k * NQE + jl;
-      // point order of i_e along the edge (reversed on the other side), or on the face
-      const int jj = (DIM == 3) ? T.pperm[perm][jl] : (side ? (NQE - 1 - jl) : jl);
-      // the normal flux directly (3D: 5% faster), or both directions and a dot product (1D/2D:
-      // measured faster there, the two directions' independent chains hide latency at two waves)
+      // point order of i_e along the edge (reversed on the other side)
+      const int jj = side ? (NQE - 1 - jl) : jl;
       R q[V], qt[V], qtt[V], fn[V];
-      if constexpr (DIM == 3) {
-        St<DIM, R> s;
-        Var<DIM, R> vt;
-        derivs(p, q, qt, qtt, s, vt);
-        ftn_from<DIM, R>(q, qt, qtt, n, gm1, dt, fn);
-      } else {
-        R FT[DIM][V];
-        point(p, q, qt, qtt, FT);
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-          fn[c] = R(0);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) fn[c] += n[d] * FT[d][c];
-        }
-      }
+      const Pt2<DIM, R> s = derivs(p, q, qt, qtt);
+      ftn2<DIM, R>(s, q, qt, qtt, n, gm1, fn);
       R b[V];
 #pragma unroll
       for (int c = 0; c < V; ++c) b[c] = R(0.5) * fn[c] + hs * q[c];
@@ -1186,13 +1624,13 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
           reflect<DIM, R>(q, nh, qg);
           reflect<DIM, R>(qt, nh, qtg);
           reflect<DIM, R>(qtt, nh, qttg);
-          ftn_from<DIM, R>(qg, qtg, qttg, n, gm1, dt, fgn);
+          ftn_from<DIM, R>(qg, qtg, qttg, n, gm1, fgn);
         } else {
           R z[V];
 #pragma unroll
           for (int c = 0; c < V; ++c) z[c] = R(0);
           inflow_state<DIM, R>(v.inflow, qg);
-          ftn_from<DIM, R>(qg, z, z, n, gm1, dt, fgn);
+          ftn_from<DIM, R>(qg, z, z, n, gm1, fgn);
         }
         // the ghost is side 1: its outward normal is -n
         R bg[V];
@@ -1232,15 +1670,15 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
     qb[c] = v.Qbar[(size_t)i * V + c];
     v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
-    for (int l = 1; l < ML; ++l) Qr[c][l - 1] = v.Qh[(c * (ML - 1) + l - 1) * N + i];
+    for (int l = 1; l < ML; ++l) Qr[c][l - 1] = at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i);
   }
-  const double th = v.theta[i];
+  const double th = at(v.theta, i);
   const R thR = R(th);
   R Ji[DIM][DIM];
 #pragma unroll
   for (int a = 0; a < DIM; ++a)
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) Ji[a][d] = v.Jinv[(a * DIM + d) * N + i];
+    for (int d = 0; d < DIM; ++d) Ji[a][d] = at(v.Jinv + (size_t)(a * DIM + d) * N, i);
 
   auto state_at = [&](int p, R* q) {
 #pragma unroll
@@ -1508,7 +1946,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
   for (int c = 0; c < V; ++c)
 #pragma unroll
     for (int l = 1; l < ML; ++l)
-      v.Qh[(c * (ML - 1) + l - 1) * N + i] = idle ? Qr[c][l - 1] : thR * Qr[c][l - 1] + dt * vol[c][l - 1];
+      at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i) = idle ? Qr[c][l - 1] : thR * Qr[c][l - 1] + dt * vol[c][l - 1];
   if (v.dbg_vol) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
@@ -1521,11 +1959,11 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
   // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
   const double hs0 = 0.5 * v.sc[mid].s;
   for (int k = 0; k < K; ++k) {
-    const int slot = v.eslot[k * N + i];
+    const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
     R n[DIM], len2 = R(0);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) { n[d] = v.nout[(k * DIM + d) * N + i]; len2 += n[d] * n[d]; }
+    for (int d = 0; d < DIM; ++d) { n[d] = at(v.nout + (size_t)(k * DIM + d) * N, i); len2 += n[d] * n[d]; }
     const R hs = R(hs0 * double(sqrt(len2)));
     for (int jl = 0; jl < NQE; ++jl) {
       const int p = NI + k * NQE + jl;
@@ -1587,11 +2025,12 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 template <class E, class R>
 __device__ __forceinline__ void elem_item(View<R> v, const int i) {
   if constexpr (E::DEG == 3) elem_item3<E, R>(v, i);
+  else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i);
   else elem_item2<E, R>(v, i);
 }
 
 template <class E, class R>
-__global__ __launch_bounds__(256, (ElemOcc<E, R>::waves)) void k_elem(View<R> v) {
+__global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_elem(View<R> v) {
   elem_item<E, R>(v, xcd_item());
 }
 
@@ -1605,20 +2044,6 @@ __global__ __launch_bounds__(256, (ElemOcc<E, R>::waves)) void k_elem(View<R> v)
 // f^LxW are formed in the first element's orientation and point order, and every operation of f^LxF
 // is written out, changes sign with the normal and is symmetric in the two states.
 // ---------------------------------------------------------------------------------------------
-// V values of one record at p (consecutive)
-template <class R, int V>
-__device__ __forceinline__ void load_rec(const R* p, R (&x)[V]) {
-  if constexpr ((V * sizeof(R)) % 16 == 0) {
-    typedef R vec __attribute__((ext_vector_type(V)));
-    const vec t = *reinterpret_cast<const vec*>(p);
-#pragma unroll
-    for (int c = 0; c < V; ++c) x[c] = t[c];
-  } else {
-#pragma unroll
-    for (int c = 0; c < V; ++c) x[c] = p[c];
-  }
-}
-
 // F* at the points of edge e in the first element's order
 template <class E, class R>
 __device__ __forceinline__ void edge_points(const View<R>& v, int e, R (&fs)[E::NQE][E::V]) {
@@ -1796,6 +2221,7 @@ __device__ double mu_solve(const double* qL, const double* qa, double gam, doubl
 template <class E, class R>
 struct FluxShape {
   static constexpr bool roll = E::DIM > 1 && !(E::kind == ElTri::kind && E::DEG == 2 && sizeof(R) == 4);
+  static constexpr int lds = roll ? E::K * 2 * E::V * 8 : 0;  // bytes per lane
 };
 
 template <class E, class R>
@@ -1862,20 +2288,21 @@ __device__ __forceinline__ void flux_item(View<R> v, const int i) {
   if constexpr (FluxShape<E, R>::roll) {
     // one face at a time: the lane's fluxes wait in LDS (columns of consecutive lanes) until the modes are
     // stored
-    __shared__ double sf[K * 2 * V][256];
-    const int t = (int)threadIdx.x;
+    extern __shared__ __align__(16) unsigned char dyn[];
+    double* sf = reinterpret_cast<double*>(dyn) + threadIdx.x;
+    const int bs = (int)blockDim.x;
 #pragma unroll 1
     for (int k = 0; k < K; ++k) {
       double W[V], F[V];
       face(k, W, F);
 #pragma unroll
-      for (int c = 0; c < V; ++c) { sf[(2 * k) * V + c][t] = W[c]; sf[(2 * k + 1) * V + c][t] = F[c]; }
+      for (int c = 0; c < V; ++c) { sf[((2 * k) * V + c) * bs] = W[c]; sf[((2 * k + 1) * V + c) * bs] = F[c]; }
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       slot[k] = at(v.eslot + (size_t)k * N, i);
 #pragma unroll
-      for (int c = 0; c < V; ++c) { fW[k][c] = sf[(2 * k) * V + c][t]; fF[k][c] = sf[(2 * k + 1) * V + c][t]; }
+      for (int c = 0; c < V; ++c) { fW[k][c] = sf[((2 * k) * V + c) * bs]; fF[k][c] = sf[((2 * k + 1) * V + c) * bs]; }
     }
   } else {
 #pragma unroll
@@ -2059,7 +2486,7 @@ __global__ __launch_bounds__(256) void k_update(View<R> v) {
 // and the tiles of each XCD are one contiguous range of the space-filling-curve order.
 // ---------------------------------------------------------------------------------------------
 template <class E, class R, int pmode>
-__global__ __launch_bounds__(256, (ElemOcc<E, R>::waves)) void k_persist(View<R> v, int n_mesh, int n_steps) {
+__global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_persist(View<R> v, int n_mesh, int n_steps) {
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int bs = (int)blockDim.x, nb = (int)gridDim.x;
   const int x = (int)blockIdx.x & 7, r = (int)blockIdx.x >> 3, per = nb >> 3;
@@ -2097,14 +2524,16 @@ hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mes
   hipDeviceProp_t prop;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, bs, 0);
+  // the phases take turns with the workgroup's LDS
+  const int lds = std::max(ElemShape<E, R>::lds, FluxShape<E, R>::lds) * bs;
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, bs, lds);
   if (e != hipSuccess) return e;
   // every workgroup must be resident for the grid barriers; a multiple of 8 for the XCD mapping
   const int nb = per_cu * prop.multiProcessorCount / 8 * 8;
   if (nb < 8) return hipErrorCooperativeLaunchTooLarge;
   View<R> vv = v;
   void* args[] = {&vv, &n_mesh, &n_steps};
-  return hipLaunchCooperativeKernel(fn, dim3((unsigned)nb), dim3((unsigned)bs), args, 0, st);
+  return hipLaunchCooperativeKernel(fn, dim3((unsigned)nb), dim3((unsigned)bs), args, lds, st);
 }
 
 #if LXW_PART == 0
@@ -2162,10 +2591,10 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
                               v.N > 0 ? egrid_blocks(v.N, cfg.bs[K_PRE]) : 0);
       break;
     case K_ELEM:
-      if (v.N > 0) hipLaunchKernelGGL((k_elem<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);
+      if (v.N > 0) hipLaunchKernelGGL((k_elem<E, R>), egrid(v.N, bs), dim3(bs), (ElemShape<E, R>::lds * bs), st, v);
       break;
     case K_FLUX:
-      if (v.N > 0) hipLaunchKernelGGL((k_flux<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);
+      if (v.N > 0) hipLaunchKernelGGL((k_flux<E, R>), egrid(v.N, bs), dim3(bs), (FluxShape<E, R>::lds * bs), st, v);
       break;
     case K_UPDATE:
       if (v.N > 0) hipLaunchKernelGGL((k_update<E, R>), egrid(v.N, bs), dim3(bs), 0, st, v);

@@ -460,6 +460,12 @@ void fill_tab(RefTab<E, R>& T) {
   for (int m = 0; m < E::NI; ++m) {
     T.wm[m][0] = R(r.w[m]);
     for (int d = 0; d < E::DIM; ++d) T.wm[m][1 + d] = R(r.w[m] * pts[m * E::DIM + d]);
+    if constexpr (E::DEG == 3 && E::DIM == 2) {
+      const double x = pts[m * 2], y = pts[m * 2 + 1];
+      T.wm[m][3] = R(r.w[m] * x * x);
+      T.wm[m][4] = R(r.w[m] * x * y);
+      T.wm[m][5] = R(r.w[m] * y * y);
+    }
   }
   if constexpr (E::kind == LXW_TRI || E::kind == LXW_TET)
     for (int l = 0; l < E::ML; ++l)

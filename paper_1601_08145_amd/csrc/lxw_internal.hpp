@@ -64,7 +64,8 @@ struct RefTab {
                                    // complete P2 on the line and the triangle)
   R d3c[E::ND3][E::ML];            // reference third derivatives (xxx[, xxy, xyy, yyy]): constant
                                    // for complete P3, unused at degree 2
-  R wm[E::NI][1 + E::DIM];         // w_m (1, xi_m): moments of the volume term
+  R wm[E::NI][E::DEG == 3 && E::DIM == 2 ? 6 : 1 + E::DIM];  // w_m (1, xi_m), at degree 3 on the
+                                   // triangle with the products xi^2, xi eta, eta^2: moments of the volume term
   R cm[E::ML][E::ML];              // basis in monomials (triangle, tetrahedron; the order of lxw.h):
                                    // phi_l = sum_{j <= l} cm[l][j] monomial_j
   int pperm[6][E::NQE];            // tetrahedron faces: point jl of a face whose vertices are those
@@ -159,15 +160,20 @@ struct View {
 // vector address from the last one's, a serial chain of additions, and where the columns are read again
 // (or written) later in the kernel it keeps those addresses, two registers a column, across everything in
 // between (48 of the 216 registers of the float32 triangle's k_elem).
+// (The pointer comes back from the asm as global memory: a generic one would be read by flat loads.)
 template <class T>
-__device__ __forceinline__ T& at(T* col, int i) {
-  asm("" : "+s"(col));
-  return *reinterpret_cast<T*>(reinterpret_cast<char*>(col) + (unsigned)i * (unsigned)sizeof(T));
+using Global = __attribute__((address_space(1))) T;
+template <class T>
+__device__ __forceinline__ Global<T>& at(T* col, int i) {
+  Global<T>* g = (Global<T>*)col;
+  asm("" : "+s"(g));
+  return *(Global<T>*)((Global<char>*)g + (unsigned)i * (unsigned)sizeof(T));
 }
 template <class T>
-__device__ __forceinline__ const T& at(const T* col, int i) {
-  asm("" : "+s"(col));
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(col) + (unsigned)i * (unsigned)sizeof(T));
+__device__ __forceinline__ const Global<T>& at(const T* col, int i) {
+  const Global<T>* g = (const Global<T>*)col;
+  asm("" : "+s"(g));
+  return *(const Global<T>*)((const Global<char>*)g + (unsigned)i * (unsigned)sizeof(T));
 }
 
 // All reference tables in both precisions (built on the host by lxw_host.cpp).

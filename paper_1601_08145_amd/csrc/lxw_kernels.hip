@@ -948,14 +948,6 @@ __device__ __forceinline__ R here(R x) {
   return x;
 }
 
-// Index of the second reference derivative d/dxi_a d/dxi_b in the tables (2D: xx, xy, yy; 3D:
-// xx, xy, xz, yy, yz, zz).
-template <int DIM>
-__device__ __forceinline__ constexpr int sidx(int a, int b) {
-  if (a > b) { const int t = a; a = b; b = t; }
-  return DIM == 3 ? (a == 0 ? b : (a == 1 ? 2 + b : 5)) : a + b;
-}
-
 // P2 on triangles and tetrahedra (affine elements): everything at a point comes from polynomial
 // coefficients formed once per element.
 //  * The limited state q_bar + theta sum_l Q_l phi_l as monomial coefficients a in float64 (the basis in
@@ -977,13 +969,14 @@ template <class E, class R>
 struct ElemShape {
   // interior states kept in LDS per lane, where four wavefronts per CU still fit (float64 tetrahedra form
   // them twice)
-  static constexpr bool keep = (E::kind == ElTri::kind && E::DEG == 2) || (E::DIM == 3 && sizeof(R) == 4);
+  static constexpr bool keep = E::kind == ElTri::kind || (E::DIM == 3 && sizeof(R) == 4);
   static constexpr int lds = keep ? E::NI * E::V * (int)sizeof(R) : 0;
   // Waves per SIMD the register allocation targets, the most that spill next to nothing: three for float32
   // triangles (168 registers, 8 bytes of scratch a lane; 129 us on 999,698 against 138 at two), two for
-  // float64 triangles (58 / 65 us on 250k) and the float32 square (111 / 153 us on 262k), one elsewhere
+  // float64 triangles (58 / 65 us on 250k), float32 P3 triangles (138 / 184 us on 250k) and the float32
+  // square (111 / 153 us on 262k), one elsewhere
   // (float32 tetrahedra: their states fill the LDS with one; 307 us on 280k, 463 at two without them).
-  static constexpr int waves = E::DEG == 3 || E::DIM != 2 ? 1 : (E::kind == ElTri::kind ? (sizeof(R) == 4 ? 3 : 2) : (sizeof(R) == 4 ? 2 : 1));
+  static constexpr int waves = E::DIM != 2 || (sizeof(R) == 8 && E::ML > ElTri::ML) ? 1 : (sizeof(R) == 4 && E::ML == ElTri::ML ? 3 : 2);
 };
 
 template <class E, class R>
@@ -1642,7 +1635,502 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   }
 }
 
-// k_elem at degree 3 (P3 on the line and on triangles, affine elements).  The same steps as above
+// P3 on triangles.  The Taylor series of Sec. 2.2 one term further: F_T needs q_ttt = -div F_tt, which takes
+// the gradient of q_tt, hence the Hessians of q and of D = div F^h (constant: F^h is cubic).  As at degree
+// 2 everything goes through the variations of u, p and H = E + p (product rule on F_d = (M_d, M_k u_d +
+// p e_d, u_d H)), here with derivatives along the reference coordinates (indices a, e) and the
+// contravariant velocity W_a = (dt/3) grad xi_a . u, so that no gradient or Hessian is mapped at a point.
+// Scaled time derivatives q1 = c1 q_t, q2 = c2 q_tt, q3 = c3 q_ttt, c1 = dt/2, c2 = dt^2/6, c3 = dt^3/24:
+//   u_a = (M_a - u rho_a)/rho,  p_a = (gamma-1)(E_a + |u|^2 rho_a/2 - u.M_a),  and so on (product rule);
+//   a transported quantity f (M_k or H) contributes to f2
+//     S(f) = -(W.grad f1 + f1 div W + W1.grad f + f div W1),   S_e its derivative along xi_e,
+//   M2_k = S(M_k) - grad_k p1,  E2 = S(H),  rho2 = -div M1 (its gradient is constant), and
+//   f3 = -(3/4)(W.grad f2 + f2 div W + 4/3 (W1.grad f1 + f1 div W1) + W2.grad f + f div W2);
+// a product's time average is a (b + b1 + b2 + b3) + a1 (b + 4/3 b1 + 3/2 b2) + a2 (b + 3/2 b1) + a3 b.
+// Second reference derivatives are indexed by their number of eta (0 xx, 1 xy, 2 yy), third ones likewise.
+//
+// Bound by instruction issue.  250,632 triangles: FP32-mixed 321 -> 138 us, with third variations of the
+// flux per direction and every gradient and Hessian mapped at every point before; float64 spilled 780 bytes a
+// lane and now nothing.
+template <class R>
+struct Pt3 {  // what F_T needs of a point besides q and its time derivatives
+  R u2[2], p2, H2;  // c2 times the second time derivatives of u, p and H
+};
+template <class R>
+__device__ __forceinline__ Pt3<R> pt3_of(const Pt2<2, R>& s, const R* q1, const R* q2, R gm1) {
+  Pt3<R> t;
+  R x = q2[3] + s.u2h * q2[0], ww = R(0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    t.u2[k] = (q2[1 + k] - s.u[k] * q2[0] - R(4.0 / 3.0) * s.ut[k] * q1[0]) * s.r;
+    x -= s.u[k] * q2[1 + k];
+    ww += s.w[k] * s.ut[k];
+  }
+  t.p2 = gm1 * (x - R(2.0 / 3.0) * ww);
+  t.H2 = q2[3] + t.p2;
+  return t;
+}
+// velocity's third derivative and p3, H3
+template <class R>
+__device__ __forceinline__ void third(const Pt2<2, R>& s, const Pt3<R>& t, const R* q1, const R* q2, const R* q3, R gm1,
+                                      R* u3, R& p3, R& H3) {
+  R x = q3[3] + s.u2h * q3[0], w2 = R(0), uu = R(0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    u3[k] = (q3[1 + k] - s.u[k] * q3[0] - R(1.5) * (s.ut[k] * q2[0] + t.u2[k] * q1[0])) * s.r;
+    x -= s.u[k] * q3[1 + k];
+    w2 += s.w[k] * t.u2[k];
+    uu += s.ut[k] * s.ut[k];
+  }
+  p3 = gm1 * (x - R(1.5) * w2 - q1[0] * uu);
+  H3 = q3[3] + p3;
+}
+template <class R>
+__device__ __forceinline__ void ft3(const Pt2<2, R>& s, const Pt3<R>& t, const R* q, const R* q1, const R* q2, const R* q3,
+                                    R gm1, R FT[2][4]) {
+  R u3[2], p3, H3;
+  third<R>(s, t, q1, q2, q3, gm1, u3, p3, H3);
+  const R pb = s.p + s.pt + t.p2 + p3;
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    const R B = s.u[d] + s.ut[d] + t.u2[d] + u3[d], X = s.u[d] + R(4.0 / 3.0) * s.ut[d] + R(1.5) * t.u2[d];
+    const R Y = s.u[d] + R(1.5) * s.ut[d], Z = s.u[d];
+    FT[d][0] = q[1 + d] + q1[1 + d] + q2[1 + d] + q3[1 + d];
+#pragma unroll
+    for (int k = d; k < 2; ++k) {
+      R f = q[1 + k] * B + q1[1 + k] * X + q2[1 + k] * Y + q3[1 + k] * Z;
+      if (k == d) f += pb;
+      FT[d][1 + k] = f;
+      FT[k][1 + d] = f;
+    }
+    FT[d][3] = s.H * B + s.Ht * X + t.H2 * Y + H3 * Z;
+  }
+}
+template <class R>
+__device__ __forceinline__ void ftn3(const Pt2<2, R>& s, const Pt3<R>& t, const R* q, const R* q1, const R* q2, const R* q3,
+                                     const R* n, R gm1, R* FTn) {
+  R u3[2], p3, H3;
+  third<R>(s, t, q1, q2, q3, gm1, u3, p3, H3);
+  const R pb = s.p + s.pt + t.p2 + p3;
+  const R un = s.u[0] * n[0] + s.u[1] * n[1], u1n = s.ut[0] * n[0] + s.ut[1] * n[1];
+  const R u2n = t.u2[0] * n[0] + t.u2[1] * n[1], u3n = u3[0] * n[0] + u3[1] * n[1];
+  const R B = un + u1n + u2n + u3n, X = un + R(4.0 / 3.0) * u1n + R(1.5) * u2n, Y = un + R(1.5) * u1n;
+  FTn[0] = R(0);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    FTn[0] += (q[1 + k] + q1[1 + k] + q2[1 + k] + q3[1 + k]) * n[k];
+    FTn[1 + k] = q[1 + k] * B + q1[1 + k] * X + q2[1 + k] * Y + q3[1 + k] * un + pb * n[k];
+  }
+  FTn[3] = s.H * B + s.Ht * X + t.H2 * Y + H3 * un;
+}
+
+// q2 and q3 at a point from q, q1 and their reference derivatives (h1, the Hessian of q1, and r2e, the
+// gradient of rho2, are the element's constants)
+template <class R>
+__device__ __forceinline__ void evolve3(const Pt2<2, R>& s, const R* q, const R (&gq)[2][4], const R (&hq)[3][4],
+                                        const R* q1, const R (&g1)[2][4], const R (&h1)[3][4], const R (&JG)[2][2],
+                                        const R* r2e, R gm1, R* q2, R* q3, Pt3<R>& t) {
+  R ua[2][2], u1a[2][2], y[2][2], uab[3][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      ua[a][k] = (gq[a][1 + k] - s.u[k] * gq[a][0]) * s.r;
+      y[a][k] = g1[a][1 + k] - s.u[k] * g1[a][0];
+      u1a[a][k] = (y[a][k] - ua[a][k] * q1[0] - s.ut[k] * gq[a][0]) * s.r;
+    }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = a; b < 2; ++b)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        uab[a + b][k] = (hq[a + b][1 + k] - s.u[k] * hq[a + b][0] - ua[b][k] * gq[a][0] - ua[a][k] * gq[b][0]) * s.r;
+  // p, p1 and with them H, H1: gradients and Hessians
+  R Ha[2], H1a[2], p1a[2], Hab[3], H1ab[3], p1ab[3];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    Ha[a] = gq[a][3] + gm1 * (gq[a][3] + s.u2h * gq[a][0] - s.u[0] * gq[a][1] - s.u[1] * gq[a][2]);
+    p1a[a] = gm1 * (g1[a][3] + s.u2h * g1[a][0] - s.u[0] * g1[a][1] - s.u[1] * g1[a][2] - ua[a][0] * s.w[0] -
+                    ua[a][1] * s.w[1]);
+    H1a[a] = g1[a][3] + p1a[a];
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = a; b < 2; ++b) {
+      const int j = a + b;
+      const R uu = ua[a][0] * ua[b][0] + ua[a][1] * ua[b][1];
+      Hab[j] = hq[j][3] + gm1 * (hq[j][3] + s.u2h * hq[j][0] - s.u[0] * hq[j][1] - s.u[1] * hq[j][2] - q[0] * uu);
+      p1ab[j] = gm1 * (h1[j][3] + s.u2h * h1[j][0] - s.u[0] * h1[j][1] - s.u[1] * h1[j][2] - ua[b][0] * y[a][0] -
+                       ua[b][1] * y[a][1] - ua[a][0] * y[b][0] - ua[a][1] * y[b][1] + uu * q1[0] -
+                       uab[j][0] * s.w[0] - uab[j][1] * s.w[1]);
+      H1ab[j] = h1[j][3] + p1ab[j];
+    }
+  // contravariant velocities, their divergences and the divergences' gradients
+  R W[2], W1[2], Wa[2][2], W1a[2][2], dW[2], dW1[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    W[c] = JG[c][0] * s.u[0] + JG[c][1] * s.u[1];
+    W1[c] = JG[c][0] * s.ut[0] + JG[c][1] * s.ut[1];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      Wa[a][c] = JG[c][0] * ua[a][0] + JG[c][1] * ua[a][1];
+      W1a[a][c] = JG[c][0] * u1a[a][0] + JG[c][1] * u1a[a][1];
+    }
+  }
+  const R divW = Wa[0][0] + Wa[1][1], divW1 = W1a[0][0] + W1a[1][1];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    dW[e] = JG[0][0] * uab[e][0] + JG[0][1] * uab[e][1] + JG[1][0] * uab[1 + e][0] + JG[1][1] * uab[1 + e][1];
+    R x = -r2e[e];
+    x -= W[0] * h1[e][0] + W[1] * h1[1 + e][0] + divW * g1[e][0] + Wa[e][0] * g1[0][0] + Wa[e][1] * g1[1][0] + dW[e] * q1[0];
+    x -= divW1 * gq[e][0] + W1a[e][0] * gq[0][0] + W1a[e][1] * gq[1][0] + W1[0] * hq[e][0] + W1[1] * hq[1 + e][0];
+    dW1[e] = x * s.r;
+  }
+  // q2 and its gradient
+  R q2a[2][4];
+  q2[0] = R(0);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    q2[0] -= JG[a][0] * g1[a][1] + JG[a][1] * g1[a][2];
+    q2a[a][0] = r2e[a];
+  }
+#pragma unroll
+  for (int c = 1; c < 4; ++c) {
+    const R f = c == 3 ? s.H : q[c], f1 = c == 3 ? s.Ht : q1[c];
+    R fa[2], f1a[2], fab[3], f1ab[3];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) { fa[a] = c == 3 ? Ha[a] : gq[a][c]; f1a[a] = c == 3 ? H1a[a] : g1[a][c]; }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) { fab[j] = c == 3 ? Hab[j] : hq[j][c]; f1ab[j] = c == 3 ? H1ab[j] : h1[j][c]; }
+    R x = W[0] * f1a[0] + W[1] * f1a[1] + f1 * divW + W1[0] * fa[0] + W1[1] * fa[1] + f * divW1;
+    if (c < 3) x += JG[0][c - 1] * p1a[0] + JG[1][c - 1] * p1a[1];
+    q2[c] = -x;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      R z = Wa[e][0] * f1a[0] + Wa[e][1] * f1a[1] + W[0] * f1ab[e] + W[1] * f1ab[1 + e] + f1a[e] * divW + f1 * dW[e];
+      z += W1a[e][0] * fa[0] + W1a[e][1] * fa[1] + W1[0] * fab[e] + W1[1] * fab[1 + e] + fa[e] * divW1 + f * dW1[e];
+      if (c < 3) z += JG[0][c - 1] * p1ab[e] + JG[1][c - 1] * p1ab[1 + e];
+      q2a[e][c] = -z;
+    }
+  }
+  t = pt3_of<R>(s, q1, q2, gm1);
+  // q3
+  const R uu = s.ut[0] * s.ut[0] + s.ut[1] * s.ut[1];
+  const R z0 = q2[1] - s.u[0] * q2[0], z1 = q2[2] - s.u[1] * q2[0];
+  R p2a[2], H2a[2], W2[2];
+  R divN = R(0);
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    p2a[a] = gm1 * (q2a[a][3] + s.u2h * q2a[a][0] - s.u[0] * q2a[a][1] - s.u[1] * q2a[a][2] - ua[a][0] * z0 - ua[a][1] * z1 -
+                    R(2.0 / 3.0) * gq[a][0] * uu - R(4.0 / 3.0) * (s.w[0] * u1a[a][0] + s.w[1] * u1a[a][1]));
+    H2a[a] = q2a[a][3] + p2a[a];
+    W2[a] = JG[a][0] * t.u2[0] + JG[a][1] * t.u2[1];
+    divN += JG[a][0] * q2a[a][1] + JG[a][1] * q2a[a][2];
+  }
+  const R divW2 = (divN - W[0] * q2a[0][0] - W[1] * q2a[1][0] - divW * q2[0] -
+                   R(4.0 / 3.0) * (W1[0] * g1[0][0] + W1[1] * g1[1][0] + divW1 * q1[0]) - W2[0] * gq[0][0] - W2[1] * gq[1][0]) * s.r;
+  q3[0] = R(-0.75) * divN;
+#pragma unroll
+  for (int c = 1; c < 4; ++c) {
+    const R f = c == 3 ? s.H : q[c], f1 = c == 3 ? s.Ht : q1[c], f2 = c == 3 ? t.H2 : q2[c];
+    R x = W[0] * (c == 3 ? H2a[0] : q2a[0][c]) + W[1] * (c == 3 ? H2a[1] : q2a[1][c]) + f2 * divW;
+    x += R(4.0 / 3.0) * (W1[0] * (c == 3 ? H1a[0] : g1[0][c]) + W1[1] * (c == 3 ? H1a[1] : g1[1][c]) + f1 * divW1);
+    x += W2[0] * (c == 3 ? Ha[0] : gq[0][c]) + W2[1] * (c == 3 ? Ha[1] : gq[1][c]) + f * divW2;
+    if (c < 3) x += JG[0][c - 1] * p2a[0] + JG[1][c - 1] * p2a[1];
+    q3[c] = R(-0.75) * x;
+  }
+}
+
+template <class E, class R>
+__device__ __forceinline__ void elem_tri3(View<R> v, const int i) {
+  constexpr int V = 4, ML = 10, NI = E::NI, K = E::K, NQE = E::NQE;
+  const RefTab<E, R>& T = TabSel<E, R>::get();
+  const RefTab<E, double>& TD = TabSel<E, double>::get();
+  const int N = v.N;
+  if (i >= N) return;
+  const int mid = mesh_id<R>(v.mesh_of, i);
+  const bool idle = v.sc[mid].idle;  // applied at the store: at the end time the step changes nothing
+  const R dt = R(v.sc[mid].dt);
+  const R gm1 = R(v.gamma - 1.0);
+  extern __shared__ __align__(16) unsigned char dyn[];
+  R* sq = reinterpret_cast<R*>(dyn);
+
+  // monomial coefficients of the limited state (float64), and from them the Taylor coefficients at the
+  // reference origin: gradient, Hessian and third derivatives
+  const double th = at(v.theta, i);
+  double a[V][ML];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    const double qb = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb;  // the step's averages, for the edge fluxes (k_flux, k_update)
+    double Q[ML - 1];
+#pragma unroll
+    for (int l = 1; l < ML; ++l) Q[l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
+#pragma unroll
+    for (int m = 0; m < ML; ++m) {
+      double acc = 0.0;
+#pragma unroll
+      for (int l = (m > 1 ? m : 1); l < ML; ++l) acc += Q[l - 1] * TD.cm[l][m];
+      a[c][m] = m == 0 ? qb + th * acc : th * acc;
+    }
+  }
+  R JG[2][2], JC[2][2];  // dt/3 and -dt/2 times the map's gradient
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const R J = at(v.Jinv + (size_t)(x * 2 + d) * N, i);
+      JG[x][d] = dt * R(1.0 / 3.0) * J;
+      JC[x][d] = R(-0.5) * dt * J;
+    }
+  R g0[2][V], h0[3][V], t3[4][V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    g0[0][c] = R(a[c][1]); g0[1][c] = R(a[c][2]);
+    h0[0][c] = R(2) * R(a[c][3]); h0[1][c] = R(a[c][4]); h0[2][c] = R(2) * R(a[c][5]);
+    t3[0][c] = R(6) * R(a[c][6]); t3[1][c] = R(2) * R(a[c][7]); t3[2][c] = R(2) * R(a[c][8]); t3[3][c] = R(6) * R(a[c][9]);
+  }
+  // Sec. 2.3 Step 1 composed with -c1 div and its derivatives at the origin (kd0, kd1, kd2): the Taylor
+  // coefficients of q1, a quadratic; M is its own projection, so rho's come from the gradients of M
+  R b0[V], b1[2][V], h1[3][V];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    b0[c] = R(0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) b1[x][c] = R(0);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) h1[j][c] = R(0);
+  }
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const R J = R(-1.5) * JG[x][d];
+      b0[0] += J * g0[x][1 + d];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) b1[y][0] += J * h0[x + y][1 + d];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) h1[j][0] += J * t3[x + j][1 + d];
+    }
+#pragma unroll 1
+  for (int m = 0; m < NI; ++m) {
+    const double x = TD.xr[m][0], y = TD.xr[m][1];
+    R q[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      const double* A = a[c];
+      const double p2 = A[5] + x * A[8] + y * A[9], p1 = A[2] + x * (A[4] + x * A[7]);
+      q[c] = R(A[0] + x * (A[1] + x * (A[3] + x * A[6])) + y * (p1 + y * p2));
+    }
+    store_rec<R, V>(sq + ((size_t)m * blockDim.x + threadIdx.x) * V, q);
+    const St<2, R> s = base_state<2, R>(q, gm1);
+    R F[2][V];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) flux<2, R>(s, d, F[d]);
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+      for (int c = 1; c < V; ++c) {
+        const R fc = JC[z][0] * F[0][c] + JC[z][1] * F[1][c];
+        b0[c] += T.kd0[m][z] * fc;
+#pragma unroll
+        for (int w = 0; w < 2; ++w) b1[w][c] += T.kd1[m][z][w] * fc;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) h1[j][c] += T.kd2[m][z][j] * fc;
+      }
+  }
+  R r2e[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e)
+    r2e[e] = -(JG[0][0] * h1[e][1] + JG[0][1] * h1[e][2] + JG[1][0] * h1[1 + e][1] + JG[1][1] * h1[1 + e][2]);
+
+  // edges (before the volume term: its accumulators and the coefficients a are then not live together)
+  {
+    const double hs0 = 0.5 * v.sc[mid].s;
+    int slots[K];
+    R nk[K][2];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      slots[k] = at(v.eslot + (size_t)k * N, i);
+#pragma unroll
+      for (int d = 0; d < 2; ++d) nk[k][d] = at(v.nout + (size_t)(k * 2 + d) * N, i);
+    }
+    // along edge k the reference point is (t, 0), (1 - t, t), (0, t); edge 1, whose coefficients are sums,
+    // last
+#pragma unroll
+    for (int x = 0; x < K; ++x) {
+      const int k = x == 0 ? 0 : 3 - x;
+      const int slot = slots[k];
+      const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
+      R* n = nk[k];
+      R len2 = n[0] * n[0] + n[1] * n[1];
+      const R hs = R(hs0 * double(sqrt(len2)));  // s |n_e| / 2; then half the normal, for the trace
+      len2 *= R(0.25);
+      n[0] *= R(0.5);
+      n[1] *= R(0.5);
+#pragma unroll 1
+      for (int jl = 0; jl < NQE; ++jl) {
+        const int p = NI + k * NQE + jl;
+        const double td = TD.xr[p][k == 0 ? 0 : 1];
+        const R tt = T.xr[p][k == 0 ? 0 : 1];
+        R q[V], q1[V], gq[2][V], g1[2][V], hq[3][V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) {
+          const double* A = a[c];
+          const double e0 = k == 1 ? A[0] + A[1] + A[3] + A[6] : A[0];
+          const double e1 = k == 0 ? A[1] : (k == 2 ? A[2] : A[2] - A[1] - 2.0 * A[3] + A[4] - 3.0 * A[6] + A[7]);
+          const double e2 = k == 0 ? A[3] : (k == 2 ? A[5] : A[3] - A[4] + A[5] + 3.0 * A[6] - 2.0 * A[7] + A[8]);
+          const double e3 = k == 0 ? A[6] : (k == 2 ? A[9] : A[7] - A[6] - A[8] + A[9]);
+          q[c] = R(e0 + td * (e1 + td * (e2 + td * e3)));
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            const R l0 = k == 1 ? g0[w][c] + h0[w][c] + R(0.5) * t3[w][c] : g0[w][c];
+            const R l1 = k == 0 ? h0[w][c] : (k == 2 ? h0[w + 1][c] : h0[w + 1][c] - h0[w][c] - t3[w][c] + t3[w + 1][c]);
+            const R l2 = R(0.5) * (k == 0 ? t3[w][c] : (k == 2 ? t3[w + 2][c] : t3[w][c] + t3[w + 2][c])) -
+                         (k == 1 ? t3[w + 1][c] : R(0));
+            gq[w][c] = l0 + tt * (l1 + tt * l2);
+            const R m0 = k == 1 ? b1[w][c] + h1[w][c] : b1[w][c];
+            const R m1 = k == 0 ? h1[w][c] : (k == 2 ? h1[w + 1][c] : h1[w + 1][c] - h1[w][c]);
+            g1[w][c] = m0 + tt * m1;
+          }
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            hq[j][c] = (k == 1 ? h0[j][c] + t3[j][c] : h0[j][c]) +
+                       tt * (k == 0 ? t3[j][c] : (k == 2 ? t3[j + 1][c] : t3[j + 1][c] - t3[j][c]));
+          const R d0 = k == 1 ? b0[c] + b1[0][c] + R(0.5) * h1[0][c] : b0[c];
+          const R d1 = k == 0 ? b1[0][c] : (k == 2 ? b1[1][c] : b1[1][c] - b1[0][c] - h1[0][c] + h1[1][c]);
+          const R d2 = R(0.5) * (k == 0 ? h1[0][c] : (k == 2 ? h1[2][c] : h1[0][c] + h1[2][c])) - (k == 1 ? h1[1][c] : R(0));
+          q1[c] = d0 + tt * (d1 + tt * d2);
+        }
+        const Pt2<2, R> s = pt2_of<2, R>(q, q1, gm1);
+        Pt3<R> t;
+        R q2[V], q3[V], fn[V], b[V];
+        evolve3<R>(s, q, gq, hq, q1, g1, h1, JG, r2e, gm1, q2, q3, t);
+        ftn3<R>(s, t, q, q1, q2, q3, n, gm1, fn);
+#pragma unroll
+        for (int c = 0; c < V; ++c) b[c] = fn[c] + hs * q[c];
+        const int jj = side ? NQE - 1 - jl : jl;  // point order of i_e along the edge
+        store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
+        if (bc != SB_INTERIOR) {
+          R qg[V], fgn[V], nb[2] = {here(n[0]), here(n[1])};
+          if (bc == SB_TRANSPARENT) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) { qg[c] = q[c]; fgn[c] = fn[c]; }
+          } else {
+            R q1g[V], q2g[V], q3g[V];
+            if (bc == SB_REFLECTIVE) {
+              const R il = R(1) / sqrt(here(len2));
+              const R nh[2] = {nb[0] * il, nb[1] * il};
+              reflect<2, R>(q, nh, qg);
+              reflect<2, R>(q1, nh, q1g);
+              reflect<2, R>(q2, nh, q2g);
+              reflect<2, R>(q3, nh, q3g);
+            } else {
+              inflow_state<2, R>(v.inflow, qg);
+              qg[0] = here(qg[0]);
+#pragma unroll
+              for (int c = 0; c < V; ++c) q1g[c] = q2g[c] = q3g[c] = R(0);
+            }
+            const Pt2<2, R> sg = pt2_of<2, R>(qg, q1g, gm1);
+            ftn3<R>(sg, pt3_of<R>(sg, q1g, q2g, gm1), qg, q1g, q2g, q3g, nb, gm1, fgn);
+          }
+          R bg[V];  // the ghost is side 1: its outward normal is -n
+#pragma unroll
+          for (int c = 0; c < V; ++c) bg[c] = hs * qg[c] - fgn[c];
+          store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
+        }
+      }
+    }
+  }
+
+  // interior points: moments sum_m w_m (1, xi, eta, xi^2, xi eta, eta^2) F_T of the volume term
+  constexpr int NM = 6;
+  R S[NM][2][V];
+#pragma unroll
+  for (int y = 0; y < NM; ++y)
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int c = 0; c < V; ++c) S[y][d][c] = R(0);
+#pragma unroll 1
+  for (int m = 0; m < NI; ++m) {
+    const R x = T.xr[m][0], y = T.xr[m][1];
+    const R xx = R(0.5) * x * x, xy = x * y, yy = R(0.5) * y * y;
+    R q[V], q1[V], gq[2][V], g1[2][V], hq[3][V];
+    load_rec<R, V>(sq + ((size_t)m * blockDim.x + threadIdx.x) * V, q);
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+#pragma unroll
+      for (int w = 0; w < 2; ++w) {
+        gq[w][c] = g0[w][c] + h0[w][c] * x + h0[w + 1][c] * y + t3[w][c] * xx + t3[w + 1][c] * xy + t3[w + 2][c] * yy;
+        g1[w][c] = b1[w][c] + h1[w][c] * x + h1[w + 1][c] * y;
+      }
+#pragma unroll
+      for (int j = 0; j < 3; ++j) hq[j][c] = h0[j][c] + t3[j][c] * x + t3[j + 1][c] * y;
+      q1[c] = b0[c] + b1[0][c] * x + b1[1][c] * y + h1[0][c] * xx + h1[1][c] * xy + h1[2][c] * yy;
+    }
+    const Pt2<2, R> s = pt2_of<2, R>(q, q1, gm1);
+    Pt3<R> t;
+    R q2[V], q3[V], FT[2][V];
+    evolve3<R>(s, q, gq, hq, q1, g1, h1, JG, r2e, gm1, q2, q3, t);
+    ft3<R>(s, t, q, q1, q2, q3, gm1, FT);
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int c = 0; c < V; ++c)
+        if (d == 1 || c != 2)  // F_T's momentum part is symmetric
+#pragma unroll
+          for (int z = 0; z < NM; ++z) S[z][d][c] += T.wm[m][z] * FT[d][c];
+  }
+#pragma unroll
+  for (int z = 0; z < NM; ++z) S[z][0][2] = S[z][1][1];
+
+  // Sec. 2.3 Step 3 / Sec. 3.3 Step 6, volume part: Q^(l) += dt V_l for l >= 2
+  const R thR = R(th);
+  R old[V][ML - 1], Ji[2][2], vol[V][ML - 1];
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int l = 0; l < ML - 1; ++l) old[c][l] = at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i);
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int d = 0; d < 2; ++d) Ji[x][d] = at(v.Jinv + (size_t)(x * 2 + d) * N, i);
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    R C[NM][2];  // contravariant moments; then the monomials' volume terms, then the basis functions'
+#pragma unroll
+    for (int z = 0; z < NM; ++z)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) C[z][x] = Ji[x][0] * S[z][0][c] + Ji[x][1] * S[z][1][c];
+    const R mono[ML - 1] = {C[0][0], C[0][1], R(2) * C[1][0], C[2][0] + C[1][1], R(2) * C[2][1], R(3) * C[3][0],
+                            R(2) * C[4][0] + C[3][1], C[5][0] + R(2) * C[4][1], R(3) * C[5][1]};
+#pragma unroll
+    for (int l = 1; l < ML; ++l) {
+      R t = R(0);
+#pragma unroll
+      for (int z = 1; z <= l; ++z) t += T.cm[l][z] * mono[z - 1];
+      vol[c][l - 1] = t;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int l = 0; l < ML - 1; ++l)
+      at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = idle ? old[c][l] : thR * old[c][l] + dt * vol[c][l];
+  if (v.dbg_vol) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      v.dbg_vol[(c * ML) * N + i] = 0.0;
+#pragma unroll
+      for (int l = 1; l < ML; ++l) v.dbg_vol[(c * ML + l) * N + i] = double(vol[c][l - 1]);
+    }
+  }
+}
+
+// k_elem at degree 3 on the line.  The same steps as above
 // with the Taylor series of Sec. 2.2 carried one term further: F_T needs q_ttt = -div F_tt, which
 // takes the gradient of q_tt, hence the Hessians of q and of D = div F^h (constant for cubic F^h).
 // With D_e = d/dx_e D and q_e = d/dx_e q:
@@ -1704,30 +2192,16 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
       }
   };
 
-  // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m).  Only D = div F^h is needed, and
-  // it is quadratic: on triangles its value, gradient and Hessian at the reference origin accumulate
-  // straight from the quadrature values through the tables kd0, kd1, kd2 (the projection composed
-  // with div and its derivatives); in 1D F^h is formed.
+  // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m)
   constexpr int N2 = 2 * DIM - 1;
-  constexpr bool KD = DIM >= 2;
   R Fh[DIM][V][ML];
   R D0[V], gD0[V][DIM], HDr[V][N2];
 #pragma unroll
-  for (int c = 0; c < V; ++c) {
-    D0[c] = R(0);
+  for (int a = 0; a < DIM; ++a)
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) gD0[c][a] = R(0);
+    for (int c = 0; c < V; ++c)
 #pragma unroll
-    for (int j = 0; j < N2; ++j) HDr[c][j] = R(0);
-  }
-  if constexpr (!KD) {
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-      for (int c = 0; c < V; ++c)
-#pragma unroll
-        for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
-  }
+      for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
   for (int m = 0; m < NI; ++m) {
     R q[V];
     state_at(m, q);
@@ -1742,16 +2216,8 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
         R fc = R(0);
 #pragma unroll
         for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * F[d][c];
-        if constexpr (KD) {
-          D0[c] += T.kd0[m][a] * fc;
 #pragma unroll
-          for (int b = 0; b < DIM; ++b) gD0[c][b] += T.kd1[m][a][b] * fc;
-#pragma unroll
-          for (int j = 0; j < N2; ++j) HDr[c][j] += T.kd2[m][a][j] * fc;
-        } else {
-#pragma unroll
-          for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
-        }
+        for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
       }
   }
 
@@ -1771,13 +2237,11 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 #pragma unroll
       for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.dphi0[a][l];
       qg0[c][a] = thR * t;
-      if constexpr (!KD) {
 #pragma unroll
-        for (int l = 0; l < ML; ++l)
+      for (int l = 0; l < ML; ++l)
 #pragma unroll
-          for (int b = 0; b < DIM; ++b) u += Fh[b][c][l] * T.d2c[a + b][l];
-        gD0[c][a] = u;
-      }
+        for (int b = 0; b < DIM; ++b) u += Fh[b][c][l] * T.d2c[a + b][l];
+      gD0[c][a] = u;
     }
 #pragma unroll
     for (int j = 0; j < N2; ++j) {
@@ -1785,13 +2249,11 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 #pragma unroll
       for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.d2c[j][l];
       qH0[c][j] = thR * t;
-      if constexpr (!KD) {
 #pragma unroll
-        for (int l = 0; l < ML; ++l)
+      for (int l = 0; l < ML; ++l)
 #pragma unroll
-          for (int a = 0; a < DIM; ++a) u += Fh[a][c][l] * T.d3c[a + j][l];
-        HDr[c][j] = u;
-      }
+        for (int a = 0; a < DIM; ++a) u += Fh[a][c][l] * T.d3c[a + j][l];
+      HDr[c][j] = u;
     }
 #pragma unroll
     for (int j = 0; j < E::ND3; ++j) {
@@ -1800,14 +2262,12 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
       for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.d3c[j][l];
       qT3[c][j] = thR * t;
     }
-    if constexpr (!KD) {
-      R t = R(0);
+    R t0 = R(0);
 #pragma unroll
-      for (int l = 0; l < ML; ++l)
+    for (int l = 0; l < ML; ++l)
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) t += Fh[a][c][l] * T.dphi0[a][l];
-      D0[c] = t;
-    }
+      for (int a = 0; a < DIM; ++a) t0 += Fh[a][c][l] * T.dphi0[a][l];
+    D0[c] = t0;
     R h[DIM][DIM];
     map2(HDr[c], h);
 #pragma unroll
@@ -2024,7 +2484,8 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 
 template <class E, class R>
 __device__ __forceinline__ void elem_item(View<R> v, const int i) {
-  if constexpr (E::DEG == 3) elem_item3<E, R>(v, i);
+  if constexpr (E::DEG == 3 && E::DIM == 2) elem_tri3<E, R>(v, i);
+  else if constexpr (E::DEG == 3) elem_item3<E, R>(v, i);
   else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i);
   else elem_item2<E, R>(v, i);
 }

@@ -457,14 +457,43 @@ void fill_tab(RefTab<E, R>& T) {
         }
     }
   }
-  for (int m = 0; m < E::NI; ++m) {
-    T.wm[m][0] = R(r.w[m]);
-    for (int d = 0; d < E::DIM; ++d) T.wm[m][1 + d] = R(r.w[m] * pts[m * E::DIM + d]);
-    if constexpr (E::DEG == 3 && E::DIM == 2) {
-      const double x = pts[m * 2], y = pts[m * 2 + 1];
-      T.wm[m][3] = R(r.w[m] * x * x);
-      T.wm[m][4] = R(r.w[m] * x * y);
-      T.wm[m][5] = R(r.w[m] * y * y);
+  {
+    const double ctr = E::kind == LXW_TRI ? 1.0 / 3.0 : (E::kind == LXW_TET ? 0.25 : 0.0);
+    const double cp[3] = {ctr, E::DIM >= 2 ? ctr : 0.0, E::DIM == 3 ? ctr : 0.0};
+    for (int m = 0; m < E::NI; ++m) {
+      T.wm[m][0] = R(r.w[m]);
+      for (int d = 0; d < E::DIM; ++d) T.wm[m][1 + d] = R(r.w[m] * (pts[m * E::DIM + d] - ctr));
+      if constexpr (E::DEG == 3 && E::DIM == 2) {
+        const double x = pts[m * 2] - ctr, y = pts[m * 2 + 1] - ctr;  // their means: 1/18, -1/36, 1/18
+        T.wm[m][3] = R(r.w[m] * (x * x - 1.0 / 18.0));
+        T.wm[m][4] = R(r.w[m] * (x * y + 1.0 / 36.0));
+        T.wm[m][5] = R(r.w[m] * (y * y - 1.0 / 18.0));
+      }
+    }
+    // the moments of a constant as the rounded weights give them
+    double s1[sizeof(T.wm[0]) / sizeof(R)] = {};
+    for (int m = 0; m < E::NI; ++m)
+      for (size_t z = 0; z < sizeof(T.wm[0]) / sizeof(R); ++z) s1[z] += double(T.wm[m][z]);
+    for (int l = 0; l < E::ML; ++l) {
+      for (int z = 0, a = 0; a < E::DIM; ++a)
+        for (int b2 = a; b2 < E::DIM; ++b2)
+          T.hcen[z++][l] = R(B(l, cp, (a == 0) + (b2 == 0), (a == 1) + (b2 == 1), (a == 2) + (b2 == 2)));
+      for (int a = 0; a < E::DIM; ++a) {
+        double g = 0.0;
+        for (int m = 0; m < E::NI; ++m) g += r.w[m] * B(l, &pts[m * E::DIM], a == 0, a == 1, a == 2);
+        for (int z = 0, x = 0; x < E::DIM; ++x)
+          for (int y = x; y < E::DIM; ++y, ++z) {
+            if (x == a) g -= double(T.hcen[z][l]) * s1[1 + y];
+            else if (y == a) g -= double(T.hcen[z][l]) * s1[1 + x];
+          }
+        if constexpr (E::DEG == 3 && E::DIM == 2) {  // what d3c multiplies: x^2/2, x y, y^2/2 of the direction
+          g -= a == 0 ? double(T.d3c[0][l]) * 0.5 * s1[3] + double(T.d3c[1][l]) * s1[4] + double(T.d3c[2][l]) * 0.5 * s1[5]
+                      : double(T.d3c[1][l]) * 0.5 * s1[3] + double(T.d3c[2][l]) * s1[4] + double(T.d3c[3][l]) * 0.5 * s1[5];
+        }
+        g /= s1[0];
+        T.gmean[a][l] = R(g);
+        T.gmlo[a][l] = R(g - double(T.gmean[a][l]));
+      }
     }
   }
   if constexpr (E::kind == LXW_TRI || E::kind == LXW_TET)

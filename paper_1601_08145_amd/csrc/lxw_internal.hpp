@@ -64,8 +64,12 @@ struct RefTab {
                                    // complete P2 on the line and the triangle)
   R d3c[E::ND3][E::ML];            // reference third derivatives (xxx[, xxy, xyy, yyy]): constant
                                    // for complete P3, unused at degree 2
-  R wm[E::NI][E::DEG == 3 && E::DIM == 2 ? 6 : 1 + E::DIM];  // w_m (1, xi_m), at degree 3 on the
-                                   // triangle with the products xi^2, xi eta, eta^2: moments of the volume term
+  R wm[E::NI][E::DEG == 3 && E::DIM == 2 ? 6 : 1 + E::DIM];  // w_m (1, xi_m - centroid), at degree 3 on
+                                   // the triangle with the products x^2, x y, y^2 less their means: moments of
+                                   // the volume term
+  R gmean[E::DIM][E::ML];          // mean reference gradient (with the moments wm leaves of a constant taken
+  R gmlo[E::DIM][E::ML];           // out) and what its rounding lost; second derivatives at the centroid
+  R hcen[E::ND2][E::ML];
   R cm[E::ML][E::ML];              // basis in monomials (triangle, tetrahedron; the order of lxw.h):
                                    // phi_l = sum_{j <= l} cm[l][j] monomial_j
   int pperm[6][E::NQE];            // tetrahedron faces: point jl of a face whose vertices are those

@@ -1,13 +1,12 @@
 // HIP kernels (gfx950) of the positivity-preserving Lax-Wendroff DG step
 // (Moe, Rossmanith, Seal, arXiv:1601.08145).
 //
-// One step is five launches on one stream (grid-wide dependencies separate them):
+// One step is four or five launches on one stream (grid-wide dependencies separate them):
 //   k_pre    per element: pending shock-capturing limiter of the previous step (Sec. 1.5 Step 5),
 //            moment limiter (Sec. 3.1), cell-average checks, and the global wave speed s
-//            (one partial maximum per workgroup for a single mesh; in a batch one atomic maximum
-//            per wavefront and mesh);
-//   k_dt     per mesh: dt = CFL / (s max_i |dT_i|/(2|T_i|)), clipped to reach T (for a single
-//            mesh it first reduces the workgroup partials);
+//            (one atomic maximum per workgroup for a single mesh, or a partial one where there are many
+//            workgroups; in a batch one atomic maximum per wavefront and mesh);
+//   k_dt     a single mesh of many workgroups: reduces the workgroups' partials;
 //   k_elem   per element: Galerkin projection of F (Sec. 2.3 Step 1), the time-averaged flux F_T
 //            of Eq. (taylor3-flux) at every interior and edge point (Sec. 2.2, 2.3 Step 2), the
 //            volume term (Sec. 2.3 Step 3) added to the higher modes, and the edge traces (each
@@ -459,6 +458,30 @@ __device__ __forceinline__ void inflow_state(const double* inflow, T* out) {
   else { out[0] = T(inflow[0]); out[1] = T(inflow[1]); out[2] = T(inflow[2]); out[3] = T(0); out[4] = T(inflow[3]); }  // not used: no inflow sides on tetrahedra
 }
 
+// Wave speed, time step and end-of-run flag of a step
+struct StepDt {
+  double s, dt;
+  bool idle;  // the end time is reached: the step changes nothing
+};
+// from the mesh's wave speed (k_pre's maximum): dt from the CFL condition (reading of Sec. 4.1, "CFL 0.08"),
+// clipped to T; 0 for a wave speed that is no positive number
+__device__ __forceinline__ StepDt step_dt(const Scalars& S, double s, double t) {
+  StepDt D;
+  D.s = s;
+  D.idle = !(t < S.T);
+  D.dt = 0.0;
+  if (s > 0.0 && isfinite(s)) {
+    D.dt = S.cfl / (s * S.geo);
+    if (t + D.dt > S.T) D.dt = S.T - t;
+  }
+  return D;
+}
+__device__ __forceinline__ StepDt step_dt(const Scalars& S) {
+  return step_dt(S, __longlong_as_double((long long)S.s_bits), S.t);
+}
+// as k_elem left it for the kernels after it
+__device__ __forceinline__ StepDt stored_dt(const Scalars& S) { return {S.s, S.dt, S.idle != 0}; }
+
 template <class R>
 __device__ __forceinline__ int mesh_id(const int* mesh_of, int i) { return mesh_of ? mesh_of[i] : 0; }
 
@@ -519,30 +542,68 @@ __device__ __forceinline__ double pressure_r(const double* q, double r, double g
   return (gam - 1.0) * (q[DIM + 1] - 0.5 * k * r);
 }
 
-// |u| + c from u2 = |u|^2 and c2 = gamma p / rho (both float64) for the global wave speed s.
-// Float64 form: in float64.  FP32-mixed form: both square roots by the hardware float32 square
-// root (a float64 square root, or a correctly rounded float32 one, is a sequence of a dozen
-// instructions, and k_pre takes two per limiter point), the sum enlarged by a relative 2^-21 in
+// max and min of float64 values that are no signalling NaNs (results of arithmetic, checked inputs): one
+// instruction each.  fmax and fmin come with a second one per operand that would quiet a signalling NaN (11 of
+// the 71 instructions per point of k_pre's pass).
+__device__ __forceinline__ double max_num(double a, double b) {
+  double d;
+  asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ double min_num(double a, double b) {
+  double d;
+  asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ float max_num(float a, float b) {
+  float d;
+  asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
+// sqrt(x) in float64 for x >= 0 within the normal range (0 gives 1e-140, nothing beside a sound speed):
+// the hardware's reciprocal square root and two coupled Newton steps on sqrt(x) and 1/(2 sqrt(x)), to within
+// an ulp, in half the instructions of the correctly rounded root with its scaling.
+__device__ __forceinline__ double sqrt_nr(double x) {
+  const double z = max_num(x, 1e-280);
+  const double y = __builtin_amdgcn_rsq(z);
+  double g = z * y, h = 0.5 * y;
+  double r = __fma_rn(-h, g, 0.5);
+  g = __fma_rn(g, r, g);
+  h = __fma_rn(h, r, h);
+  r = __fma_rn(-g, g, z);
+  return __fma_rn(r, h, g);
+}
+
+// Largest |u| + c over states given by u2 = |u|^2 and c2 = gamma p / rho (both float64), for the global
+// wave speed s.  Float64 form: in float64.  FP32-mixed form: both square roots by the hardware float32
+// square root (a float64 square root, or a correctly rounded float32 one, is a sequence of a dozen
+// instructions, and k_pre takes two per limiter point), the largest sum enlarged by a relative 2^-21 in
 // float64.  The float32 rounding of u2 and c2 (2^-24 each, halved by the root), the roots (up to
 // two ulp, 2^-22) and the sum (2^-24) stay below that margin for u2 and c2 within the float32
 // normal range, so the result is never below the float64 value: the condition on s of the
 // positivity argument (s at least the largest |u| + c) still holds.
 template <class R>
-__device__ __forceinline__ double speed_of(double u2, double c2) {
-  if constexpr (sizeof(R) == sizeof(double)) {
-    return sqrt(u2) + sqrt(c2);
-  } else {
-    return double(__builtin_amdgcn_sqrtf(float(u2)) + __builtin_amdgcn_sqrtf(float(c2))) * (1.0 + 0x1p-21);
+struct Speed {
+  R m = R(0);
+  __device__ __forceinline__ void add(double u2, double c2) {
+    if constexpr (sizeof(R) == sizeof(double)) m = max_num(m, sqrt_nr(u2) + sqrt_nr(c2));
+    else m = max_num(m, __builtin_amdgcn_sqrtf(float(u2)) + __builtin_amdgcn_sqrtf(float(c2)));
   }
-}
+  __device__ __forceinline__ double get() const {
+    if constexpr (sizeof(R) == sizeof(double)) return m;
+    else return double(m) * (1.0 + 0x1p-21);
+  }
+};
 
+// the same of a whole state
 template <int DIM, class R>
-__device__ __forceinline__ double speed_r(const double* q, double gam) {
+__device__ __forceinline__ void add_speed(Speed<R>& S, const double* q, double gam) {
   const double r = rcp_nr(q[0]);
   double u2 = 0.0;
 #pragma unroll
   for (int d = 0; d < DIM; ++d) u2 += (q[1 + d] * r) * (q[1 + d] * r);
-  return speed_of<R>(u2, gam * pressure_r<DIM>(q, r, gam) * r);
+  S.add(u2, gam * pressure_r<DIM>(q, r, gam) * r);
 }
 
 // deviation of variable c from the cell average at point p, float64, from the stored modes
@@ -597,22 +658,19 @@ __device__ __forceinline__ double exact_segment(const double* qb, const double* 
 // 1 read-out (pending shock-capturing limiter applied), 2 collection (its factor recorded), 3 step
 // with the exact pressure factor of the moment limiter, 4 step with the wave speed from the cell
 // averages only, 5 both.
-// Element i of k_pre (i may be past the last element: every lane of a wavefront takes part in the
-// wave-speed reduction).
+// Element i; returns its wave speed.  mid and pending: its mesh, and whether the shock-capturing limiter of
+// the mesh's last step is due.
 template <class E, class R, int mode>
-__device__ __forceinline__ void pre_item(View<R> v, const int i) {
+__device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const int mid, const bool pending) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NP = E::NP, K = E::K;
   constexpr bool kStep = mode == 0 || mode >= 3;
   constexpr bool kExact = mode == 3 || mode == 5;  // exact pressure factor of the moment limiter
   constexpr bool kSavg = mode >= 4;                // wave speed from the cell averages only
   const RefTab<E, double>& T = TabSel<E, double>::get();
   const int N = v.N;
-  const bool valid = i < N;
   const double gam = v.gamma, eps0 = v.eps0;
   double smax = 0.0;
-  int mid = 0;
-  if (valid) {
-    mid = mesh_id<R>(v.mesh_of, i);
+  {
     double qb[V];
     R Qh[V][ML - 1];
 #pragma unroll
@@ -638,12 +696,13 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
     // smallest point density and pressure and the largest wave speed, which settle the moment
     // limiter and the wave speed at once when nothing needs limiting
     double th_sc = 1.0;
-    double rmin = INFINITY;  // smallest point density of the unlimited state
-    double pmin = INFINITY;  // smallest point pressure of the unlimited state (points with rho > 0)
-    double smax0 = 0.0;      // largest point wave speed of the unlimited state (points with rho > 0)
+    // smallest density and pressure over the average and the points of the unlimited state (points with
+    // rho > 0; the average itself passes both tests below), largest point wave speed of it
+    double rmin = INFINITY, pmin = INFINITY;
+    Speed<R> S0;
     bool have_rmin = false;
     const bool detect = mode == 2 || !v.ind_flag || at(v.ind_flag, i) != 0;
-    const bool shock_on = v.shock && v.sc[mid].shock_pending && ok && detect;
+    const bool shock_on = v.shock && pending && ok && detect;
     if (shock_on || (kStep && ok)) {
       have_rmin = true;
       // primitive variables of the average (formed again after the point pass, so that they are
@@ -667,26 +726,26 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
         double q[V];
 #pragma unroll
         for (int c = 0; c < V; ++c) q[c] = qb[c] + point_dev<E, R>(T, Qh, p, c);
-        wmax[0] = fmax(wmax[0], q[0]);
-        wmin[0] = fmin(wmin[0], q[0]);
-        rmin = fmin(rmin, q[0]);
+        wmax[0] = max_num(wmax[0], q[0]);
+        wmin[0] = min_num(wmin[0], q[0]);
         if (q[0] > 0.0) {
           const double r = rcp_nr(q[0]);
           double u2 = 0.0;
 #pragma unroll
           for (int d = 0; d < DIM; ++d) {
             const double u = q[1 + d] * r;
-            wmax[1 + d] = fmax(wmax[1 + d], u);
-            wmin[1 + d] = fmin(wmin[1 + d], u);
+            wmax[1 + d] = max_num(wmax[1 + d], u);
+            wmin[1 + d] = min_num(wmin[1 + d], u);
             u2 += u * u;
           }
           const double pp = pressure_r<DIM>(q, r, gam);
-          wmax[DIM + 1] = fmax(wmax[DIM + 1], pp);
-          wmin[DIM + 1] = fmin(wmin[DIM + 1], pp);
-          pmin = fmin(pmin, pp);
-          smax0 = fmax(smax0, speed_of<R>(u2, gam * pp * r));  // = speed_r of this point
+          wmax[DIM + 1] = max_num(wmax[DIM + 1], pp);
+          wmin[DIM + 1] = min_num(wmin[DIM + 1], pp);
+          S0.add(u2, gam * pp * r);
         }
       }
+      rmin = wmin[0];
+      pmin = wmin[DIM + 1];
       double wb[V], Mx[V], Mn[V];
       prim_avg(wb);
       const double dl = at(v.delta, i);
@@ -722,7 +781,7 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
         for (int d = 0; d < DIM; ++d) wn[1 + d] = qn[1 + d] * rn;
         wn[DIM + 1] = pressure_r<DIM>(qn, rn, gam);
 #pragma unroll
-        for (int c = 0; c < V; ++c) { Mx[c] = fmax(Mx[c], wn[c]); Mn[c] = fmin(Mn[c], wn[c]); }
+        for (int c = 0; c < V; ++c) { Mx[c] = max_num(Mx[c], wn[c]); Mn[c] = min_num(Mn[c], wn[c]); }
       }
       if (shock_on) {
 #pragma unroll
@@ -743,7 +802,7 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
 #pragma unroll
           for (int l = 0; l < ML - 1; ++l) at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = R(th_sc * double(Qh[c][l]));
       }
-      if (v.dbg_theta_sc && v.shock && v.sc[mid].shock_pending) v.dbg_theta_sc[i] = th_sc;
+      if (v.dbg_theta_sc && v.shock && pending) v.dbg_theta_sc[i] = th_sc;
     } else {
       // ---- moment limiter (Sec. 3.1): Step 0 flattens cells below eps0 or with p_bar <= 0;
       // Step 1 density (closed form of the largest theta); Step 2 pressure by concavity, target
@@ -752,14 +811,14 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
       // states of the density, pressure and wave-speed passes are the same; those passes then share
       // one loop.  Every value is computed by the same operations as in the separate passes.
       double th = 1.0;
-      double smax1 = 0.0;
+      Speed<R> S1;
       bool fused = false;
       if (!ok) {
         th = 0.0;
       } else if (have_rmin && th_sc == 1.0 && rmin >= eps0 && pmin >= fmin(eps0, pb)) {
         // nothing limits: the shock pass already evaluated every point's pressure and speed
         fused = true;
-        smax1 = smax0;
+        S1 = S0;
       } else {
         double thr = 1.0;
         if (have_rmin && th_sc == 1.0) {
@@ -787,33 +846,35 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
             if (kExact) th = fmin(th, thr * exact_segment<DIM>(qb, q, epsp, gam, (pb - epsp) / (pb - pt)));
             else th = fmin(th, thr * (pb - epsp) / (pb - pt));
           }
-          if (fused) smax1 = fmax(smax1, speed_r<DIM, R>(q, gam));
+          if (fused) add_speed<DIM, R>(S1, q, gam);
         }
       }
       const double tt = th_sc * th;
       at(v.theta, i) = tt;
       if (finite && qb[0] > 0.0 && pb > 0.0) {
-        smax = speed_r<DIM, R>(qb, gam);
+        Speed<R> S;
+        add_speed<DIM, R>(S, qb, gam);
         if (kSavg) {
           // the cell average's speed only
         } else if (fused && tt == 1.0) {
-          smax = fmax(smax, smax1);
+          S.m = max_num(S.m, S1.m);
         } else if (tt > 0.0) {
 #pragma unroll
           for (int p = 0; p < NP; ++p) {
             double q[V];
 #pragma unroll
             for (int c = 0; c < V; ++c) q[c] = qb[c] + tt * point_dev<E, R>(T, Qh, p, c);
-            smax = fmax(smax, speed_r<DIM, R>(q, gam));
+            add_speed<DIM, R>(S, q, gam);
           }
         }
+        smax = S.get();
       }
       if (!isfinite(smax)) {  // fmax-based reductions would drop a NaN: report it here
         report(v.err, E_NONFINITE, i);
         smax = INFINITY;
       }
       if (v.dbg_theta) v.dbg_theta[i] = th;
-      if (v.dbg_theta_sc && v.shock && v.sc[mid].shock_pending) v.dbg_theta_sc[i] = th_sc;
+      if (v.dbg_theta_sc && v.shock && pending) v.dbg_theta_sc[i] = th_sc;
       if (v.dbg_qlim) {
 #pragma unroll
         for (int c = 0; c < V; ++c) {
@@ -824,13 +885,35 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
       }
     }
   }
+  (void)mid;
+  return smax;
+}
+
+// Workgroups of k_pre up to which a single mesh's wave speed is one atomic maximum per workgroup, as a
+// batch's is (one per wavefront and mesh); above it the workgroups' maxima go to an array that
+// k_dt reduces.  One launch less is 4 to 5 us of a step (122,258 triangles, 480 workgroups: 71.6 -> 66.6 us
+// with the shorter point pass below); the atomics queue on one address at some 8 ns each, as long as a launch
+// at 512 workgroups.
+constexpr int DIRECT_BLOCKS = 512;
+
+// Element i of k_pre (i may be past the last element: every lane of a wavefront takes part in the
+// wave-speed reduction).
+template <class E, class R, int mode>
+__device__ __forceinline__ void pre_item(const View<R>& v, const int i) {
+  constexpr bool kStep = mode == 0 || mode >= 3;
+  const bool valid = i < v.N;
+  double smax = 0.0;
+  int mid = 0;
+  if (valid) {
+    mid = mesh_id<R>(v.mesh_of, i);
+    smax = pre_elem<E, R, mode>(v, i, mid, v.sc[mid].shock_pending != 0);
+  }
   if (kStep) {
     if (v.mesh_of) {
       atomic_max_per_mesh(v.sc, mid, smax, valid);
     } else {
-      // one partial maximum per block (k_dt reduces them): no contended atomics on one address
       __shared__ double red[4];
-      double x = valid ? smax : 0.0;
+      double x = smax;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
       if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
@@ -838,7 +921,8 @@ __device__ __forceinline__ void pre_item(View<R> v, const int i) {
       if (threadIdx.x == 0) {
         double m = red[0];
         for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmax(m, red[w]);
-        v.spart[blockIdx.x] = m;
+        if ((int)gridDim.x <= DIRECT_BLOCKS) atomicMax(&v.sc[0].s_bits, (unsigned long long)__double_as_longlong(m));
+        else v.spart[blockIdx.x] = m;
       }
     }
   }
@@ -853,10 +937,9 @@ __global__ __launch_bounds__(256) void k_pre(View<R> v) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_dt: per mesh, dt from the CFL condition (reading of Sec. 4.1, "CFL 0.08"), clipped to T.
+// k_dt: a single mesh of many workgroups: one workgroup of 1024 lanes reduces their maxima.
 // ---------------------------------------------------------------------------------------------
-// Single mesh: one workgroup of 1024 lanes reduces the per-workgroup maxima of k_pre.
-static __global__ __launch_bounds__(1024) void k_dt_single(Scalars* sc, DevError* err, const double* spart, int nparts) {
+static __global__ __launch_bounds__(1024) void k_dt_single(Scalars* sc, const double* spart, int nparts) {
   __shared__ double red[16];
   double x = 0.0;
   for (int b = threadIdx.x; b < nparts; b += blockDim.x) x = fmax(x, spart[b]);
@@ -864,42 +947,20 @@ static __global__ __launch_bounds__(1024) void k_dt_single(Scalars* sc, DevError
   for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x != 0 || !(sc[0].t < sc[0].T)) return;
   double s = red[0];
   for (int w = 1; w < (int)(blockDim.x >> 6); ++w) s = fmax(s, red[w]);
-  Scalars& S = sc[0];
-  S.idle = !(S.t < S.T);  // the end time is reached: this step changes nothing
-  if (S.idle) return;
-  S.s = s;
-  if (!(s > 0.0) || !isfinite(s)) {
-    report(err, E_NONFINITE, -1);
-    S.dt = 0.0;
-    return;
-  }
-  double dt = S.cfl / (s * S.geo);
-  if (S.t + dt > S.T) dt = S.T - S.t;
-  S.dt = dt;
+  sc[0].s_bits = (unsigned long long)__double_as_longlong(s);
 }
 
-__device__ __forceinline__ void dt_mesh(Scalars* sc, DevError* err, const int m) {
-  Scalars& S = sc[m];
-  S.idle = !(S.t < S.T);
-  if (S.idle) return;
-  const double s = __longlong_as_double((long long)S.s_bits);
-  S.s = s;
-  if (!(s > 0.0) || !isfinite(s)) {
-    report(err, E_NONFINITE, -1);
-    S.dt = 0.0;
-    return;
-  }
-  double dt = S.cfl / (s * S.geo);
-  if (S.t + dt > S.T) dt = S.T - S.t;
-  S.dt = dt;
-}
-
-static __global__ void k_dt(Scalars* sc, DevError* err, int n_mesh) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m < n_mesh) dt_mesh(sc, err, m);
+// The first element of each mesh keeps the step's values for the kernels after k_elem (which reads other
+// fields).
+__device__ __forceinline__ void store_dt(Scalars& S, DevError* err, const StepDt& D) {
+  S.idle = D.idle;
+  if (D.idle) return;
+  S.s = D.s;
+  S.dt = D.dt;
+  if (!(D.s > 0.0) || !isfinite(D.s)) report(err, E_NONFINITE, -1);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -980,18 +1041,17 @@ struct ElemShape {
 };
 
 template <class E, class R>
-__device__ __forceinline__ void elem_affine(View<R> v, const int i) {
+__device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
   constexpr bool keep = ElemShape<E, R>::keep;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
   // At the end time the step changes nothing: the stored modes are written back as they were.
   // The flag is applied at the store (not by an early return), so its load overlaps the others.
-  const bool idle = v.sc[mid].idle;
-  const R dt = R(v.sc[mid].dt);
+  const bool idle = D.idle;
+  const R dt = R(D.dt);
   const R gm1 = R(v.gamma - 1.0);
   extern __shared__ __align__(16) unsigned char dyn[];
   R* sq = reinterpret_cast<R*>(dyn);
@@ -1120,7 +1180,7 @@ __device__ __forceinline__ void elem_affine(View<R> v, const int i) {
     }
 
   // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
-  const double hs0 = 0.5 * v.sc[mid].s;
+  const double hs0 = 0.5 * D.s;
   auto edge_point = [&](const R* n, R hs, R len2, int slot, int jj, const R* q, const R (&gq)[DIM][V], const R* D) {
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
     R qt[V], qtt[V], fn[V];
@@ -1374,17 +1434,16 @@ __device__ __forceinline__ void elem_affine(View<R> v, const int i) {
 
 // P2 on the line and Q2 on the square.
 template <class E, class R>
-__device__ __forceinline__ void elem_item2(View<R> v, const int i) {
+__device__ __forceinline__ void elem_item2(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
   // At the end time the step changes nothing: the stored modes are written back as they were.
   // The flag is applied at the store (not by an early return), so its load overlaps the others.
-  const bool idle = v.sc[mid].idle;
-  const R dt = R(v.sc[mid].dt);
+  const bool idle = D.idle;
+  const R dt = R(D.dt);
   const R gm1 = R(v.gamma - 1.0);
 
   // stored modes (before the limiter) and the limiter factor theta of this step
@@ -1589,7 +1648,7 @@ __device__ __forceinline__ void elem_item2(View<R> v, const int i) {
   }
 
   // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
-  const double hs0 = 0.5 * v.sc[mid].s;
+  const double hs0 = 0.5 * D.s;
   for (int k = 0; k < K; ++k) {
     const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
@@ -1850,15 +1909,14 @@ __device__ __forceinline__ void evolve3(const Pt2<2, R>& s, const R* q, const R 
 }
 
 template <class E, class R>
-__device__ __forceinline__ void elem_tri3(View<R> v, const int i) {
+__device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = 4, ML = 10, NI = E::NI, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
-  const bool idle = v.sc[mid].idle;  // applied at the store: at the end time the step changes nothing
-  const R dt = R(v.sc[mid].dt);
+  const bool idle = D.idle;  // applied at the store: at the end time the step changes nothing
+  const R dt = R(D.dt);
   const R gm1 = R(v.gamma - 1.0);
   extern __shared__ __align__(16) unsigned char dyn[];
   R* sq = reinterpret_cast<R*>(dyn);
@@ -1954,7 +2012,7 @@ __device__ __forceinline__ void elem_tri3(View<R> v, const int i) {
 
   // edges (before the volume term: its accumulators and the coefficients a are then not live together)
   {
-    const double hs0 = 0.5 * v.sc[mid].s;
+    const double hs0 = 0.5 * D.s;
     int slots[K];
     R nk[K][2];
 #pragma unroll
@@ -2154,15 +2212,14 @@ __device__ __forceinline__ void elem_tri3(View<R> v, const int i) {
 // Gradients and Hessians are contracted per point from the reference tables (quadratic and linear
 // in the reference coordinates), the Hessian of D once per element.
 template <class E, class R>
-__device__ __forceinline__ void elem_item3(View<R> v, const int i) {
+__device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
-  const bool idle = v.sc[mid].idle;
-  const R dt = R(v.sc[mid].dt);
+  const bool idle = D.idle;
+  const R dt = R(D.dt);
   const R gm1 = R(v.gamma - 1.0);
 
   double qb[V];
@@ -2431,7 +2488,7 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
   }
 
   // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
-  const double hs0 = 0.5 * v.sc[mid].s;
+  const double hs0 = 0.5 * D.s;
   for (int k = 0; k < K; ++k) {
     const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
@@ -2497,11 +2554,26 @@ __device__ __forceinline__ void elem_item3(View<R> v, const int i) {
 }
 
 template <class E, class R>
-__device__ __forceinline__ void elem_item(View<R> v, const int i) {
-  if constexpr (E::DEG == 3 && E::DIM == 2) elem_tri3<E, R>(v, i);
-  else if constexpr (E::DEG == 3) elem_item3<E, R>(v, i);
-  else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i);
-  else elem_item2<E, R>(v, i);
+__device__ __forceinline__ void elem_step(const View<R>& v, const int i, const StepDt& D) {
+  if constexpr (E::DEG == 3 && E::DIM == 2) elem_tri3<E, R>(v, i, D);
+  else if constexpr (E::DEG == 3) elem_item3<E, R>(v, i, D);
+  else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i, D);
+  else elem_item2<E, R>(v, i, D);
+}
+
+// whether element i is the first of its mesh
+template <class R>
+__device__ __forceinline__ bool mesh_first(const View<R>& v, int i, int mid) {
+  return i == 0 || (v.mesh_of && at(v.mesh_of, i - 1) != mid);
+}
+
+template <class E, class R>
+__device__ __forceinline__ void elem_item(const View<R>& v, const int i) {
+  if (i >= v.N) return;
+  const int mid = mesh_id<R>(v.mesh_of, i);
+  const StepDt D = step_dt(v.sc[mid]);
+  if (mesh_first(v, i, mid)) store_dt(v.sc[mid], v.err, D);
+  elem_step<E, R>(v, i, D);
 }
 
 template <class E, class R>
@@ -2700,16 +2772,14 @@ struct FluxShape {
 };
 
 template <class E, class R>
-__device__ __forceinline__ void flux_item(View<R> v, const int i) {
+__device__ __forceinline__ void flux_step(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = E::V, ML = E::ML, DIM = E::DIM, K = E::K, NQE = E::NQE;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
-  const double dt = v.sc[mid].dt, s = v.sc[mid].s;
-  // at the end time the step changes nothing: the flag is read here and applied at the stores, and
-  // nothing is reported
-  const bool idle = v.sc[mid].idle;
+  const double dt = D.dt, s = D.s;
+  // at the end time the step changes nothing: applied at the stores, and nothing is reported
+  const bool idle = D.idle;
   const double gam = v.gamma;
   const double area = at(v.area, i);
   const double r = dt / area;
@@ -2874,6 +2944,11 @@ __device__ __forceinline__ void flux_item(View<R> v, const int i) {
 }
 
 template <class E, class R>
+__device__ __forceinline__ void flux_item(const View<R>& v, const int i) {
+  if (i < v.N) flux_step<E, R>(v, i, stored_dt(v.sc[mesh_id<R>(v.mesh_of, i)]));
+}
+
+template <class E, class R>
 __global__ __launch_bounds__(256) void k_flux(View<R> v) {
   flux_item<E, R>(v, xcd_item());
 }
@@ -2886,14 +2961,10 @@ __global__ __launch_bounds__(256) void k_flux(View<R> v) {
 // Then the positivity check of the new average.
 // ---------------------------------------------------------------------------------------------
 template <class E, class R>
-__device__ __forceinline__ void update_item(View<R> v, const int i) {
+__device__ __forceinline__ void update_step(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = E::V, DIM = E::DIM, K = E::K, NQE = E::NQE;
   const int N = v.N;
   if (i >= N) return;
-  const int mid = mesh_id<R>(v.mesh_of, i);
-  // at the end time the step changes nothing: the flag is read here and applied at the stores
-  const bool idle = v.sc[mid].idle;
-  const double dt = v.sc[mid].dt;
   double q[V];
 #pragma unroll
   for (int c = 0; c < V; ++c) q[c] = v.Qbar[(size_t)i * V + c];
@@ -2905,10 +2976,10 @@ __device__ __forceinline__ void update_item(View<R> v, const int i) {
     if (v.dbg_lame) v.dbg_lame[k * N + i] = th;
     low = fmin(low, th);
   }
-  if (idle) return;
+  if (D.idle) return;  // at the end time the step changes nothing
   if (low < 1.0) {
     const RefTab<E, R>& T = TabSel<E, R>::get();
-    const double s = v.sc[mid].s, r = dt / at(v.area, i);
+    const double s = D.s, r = D.dt / at(v.area, i);
     double qb[V];
 #pragma unroll
     for (int c = 0; c < V; ++c) q[c] = qb[c] = v.Qold[(size_t)i * V + c];
@@ -2935,12 +3006,20 @@ __device__ __forceinline__ void update_item(View<R> v, const int i) {
   for (int c = 0; c < V; ++c) finite = finite && isfinite(q[c]);
   if (!finite) report(v.err, E_NONFINITE, i);
   else if (!(q[0] > 0.0) || !(pressure<DIM>(q, v.gamma) > 0.0)) report(v.err, E_POSITIVITY, i);
+}
+
+template <class E, class R>
+__device__ __forceinline__ void update_item(const View<R>& v, const int i) {
+  if (i >= v.N) return;
+  const int mid = mesh_id<R>(v.mesh_of, i);
+  Scalars& S = v.sc[mid];
+  const StepDt D = stored_dt(S);
+  update_step<E, R>(v, i, D);
   // The first element of each mesh ends the mesh's step: t += dt, the wave-speed maximum is reset
-  // and the shock-capturing limiter becomes due.  Every lane has read dt above and no kernel of
-  // this step reads the fields written here.
-  if (i == 0 || (v.mesh_of && at(v.mesh_of, i - 1) != mid)) {
-    Scalars& S = v.sc[mid];
-    S.t += dt;
+  // and the shock-capturing limiter becomes due.  No kernel of this step reads the fields written here
+  // after this one has begun, and this one does not.
+  if (!D.idle && mesh_first(v, i, mid)) {
+    S.t += D.dt;
     S.steps += 1;
     S.s_bits = 0ull;
     S.shock_pending = v.shock ? 1 : 0;
@@ -2954,14 +3033,14 @@ __global__ __launch_bounds__(256) void k_update(View<R> v) {
 
 // ---------------------------------------------------------------------------------------------
 // k_persist: n_steps whole steps of a batch of meshes in one cooperative launch.  Every workgroup
-// stays resident and runs each phase of the step (the bodies of k_pre, k_dt, k_elem, k_flux,
+// stays resident and runs each phase of the step (the bodies of k_pre, k_elem, k_flux,
 // k_update) over tiles of elements, with a grid-wide barrier where the separate
 // launches have a kernel boundary; the arithmetic is that of the separate kernels, so the results
 // are the same bit for bit.  The grid is a multiple of 8 workgroups: workgroup b runs on XCD b mod 8,
 // and the tiles of each XCD are one contiguous range of the space-filling-curve order.
 // ---------------------------------------------------------------------------------------------
 template <class E, class R, int pmode>
-__global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_persist(View<R> v, int n_mesh, int n_steps) {
+__global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_persist(View<R> v, int n_steps) {
   cooperative_groups::grid_group grid = cooperative_groups::this_grid();
   const int bs = (int)blockDim.x, nb = (int)gridDim.x;
   const int x = (int)blockIdx.x & 7, r = (int)blockIdx.x >> 3, per = nb >> 3;
@@ -2972,8 +3051,6 @@ __global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_persist(View<
   };
   for (int step = 0; step < n_steps; ++step) {
     tiles(v.N, [&](int i) { pre_item<E, R, pmode>(v, i); });
-    grid.sync();
-    for (int m = (int)(blockIdx.x * blockDim.x + threadIdx.x); m < n_mesh; m += nb * bs) dt_mesh(v.sc, v.err, m);
     grid.sync();
     tiles(v.N, [&](int i) { elem_item<E, R>(v, i); });
     grid.sync();
@@ -3007,7 +3084,7 @@ hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mes
   const int nb = per_cu * prop.multiProcessorCount / 8 * 8;
   if (nb < 8) return hipErrorCooperativeLaunchTooLarge;
   View<R> vv = v;
-  void* args[] = {&vv, &n_mesh, &n_steps};
+  void* args[] = {&vv, &n_steps};
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)nb), dim3((unsigned)bs), args, lds, st);
 }
 
@@ -3061,9 +3138,8 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
     case K_IND:
       return hipErrorInvalidValue;  // launched through launch_indicator
     case K_DT:
-      if (v.mesh_of) hipLaunchKernelGGL(k_dt, grid(n_mesh, 64), dim3(64), 0, st, v.sc, v.err, n_mesh);
-      else hipLaunchKernelGGL(k_dt_single, dim3(1), dim3(1024), 0, st, v.sc, v.err, v.spart,
-                              v.N > 0 ? egrid_blocks(v.N, cfg.bs[K_PRE]) : 0);
+      if (!v.mesh_of && egrid_blocks(v.N, cfg.bs[K_PRE]) > DIRECT_BLOCKS)
+        hipLaunchKernelGGL(k_dt_single, dim3(1), dim3(1024), 0, st, v.sc, v.spart, egrid_blocks(v.N, cfg.bs[K_PRE]));
       break;
     case K_ELEM:
       if (v.N > 0) hipLaunchKernelGGL((k_elem<E, R>), egrid(v.N, bs), dim3(bs), (ElemShape<E, R>::lds * bs), st, v);

@@ -248,12 +248,13 @@ lxw_status lxw_advance(lxw_solver* s, double T, int64_t max_steps, lxw_stats* ou
 /* Enqueues n_steps steps with no final time (dt from the CFL condition each step) on the
  * solver's stream and returns without waiting; errors are reported by lxw_sync.  Unless per-kernel
  * timing or stage read-out is on, the steps are replays of one step captured in a HIP graph (on a
- * stream the library creates; the replays go to the solver's stream).  Results are identical
- * either way. */
+ * stream the library creates; the replays go to the solver's stream); a single mesh of at most 512
+ * cells in 1D or 256 triangles (degree 2) runs them in one workgroup of one kernel instead.  Results
+ * are identical either way. */
 lxw_status lxw_run_steps(lxw_solver* s, int64_t n_steps);
 
 /* lxw_set_graph(s, 0) makes lxw_run_steps launch every kernel itself instead of replaying the
- * captured graph; 1 (the default) restores graph replay. */
+ * captured graph (or running a small mesh in one workgroup); 1 (the default) restores that. */
 lxw_status lxw_set_graph(lxw_solver* s, int32_t enable);
 
 /* Waits for the solver's stream and reports any device error. */

@@ -1458,10 +1458,36 @@ lxw_status persistent_steps(lxw_solver* S, int64_t n_steps) {
   }
 }
 
-// Enqueues n steps: the persistent kernel (a batch with that launch shape), replays of the captured
+// Whether the steps run as one workgroup (a small single mesh, nothing recorded per kernel).
+int solo_max(const lxw_mesh& M) {
+  switch (ekind(M)) {
+    case EK_LINE: return SoloMax<ElLine>::n;
+    case EK_LINE3: return SoloMax<ElLine3>::n;
+    case EK_TRI: return SoloMax<ElTri>::n;
+    default: return 0;
+  }
+}
+bool solo(const lxw_solver* S) {
+  return !S->batch && !S->timing && !S->debug && !S->ind && S->use_graph && S->M->N <= solo_max(*S->M);
+}
+// n steps in one workgroup, at most 1024 per launch.
+lxw_status solo_steps(lxw_solver* S, int64_t n_steps) {
+  for (int64_t k = 0; k < n_steps; k += 1024) {
+    const int n = (int)std::min<int64_t>(1024, n_steps - k);
+    switch (ekind(*S->M)) {
+      case EK_LINE: HIPCHK((S->fp32 ? launch_solo<ElLine, float>(S->vf, S->st, n) : launch_solo<ElLine, double>(S->vd, S->st, n))); break;
+      case EK_LINE3: HIPCHK((S->fp32 ? launch_solo<ElLine3, float>(S->vf, S->st, n) : launch_solo<ElLine3, double>(S->vd, S->st, n))); break;
+      default: HIPCHK((S->fp32 ? launch_solo<ElTri, float>(S->vf, S->st, n) : launch_solo<ElTri, double>(S->vd, S->st, n))); break;
+    }
+  }
+  return LXW_OK;
+}
+
+// Enqueues n steps: one workgroup (a small mesh), the persistent kernel (a batch with that launch shape), replays of the captured
 // step graph, or eager launches while timing, stage read-out or graphs are off.
 lxw_status replay_steps(lxw_solver* S, int64_t n_steps) {
   if (S->batch && S->cfg.persistent && !S->timing && !S->debug && !S->ind) return persistent_steps(S, n_steps);
+  if (solo(S)) return solo_steps(S, n_steps);
   if (S->timing || S->debug || !S->use_graph) {
     for (int64_t k = 0; k < n_steps; ++k) {
       lxw_status s = enqueue_step(S);
@@ -1963,7 +1989,7 @@ lxw_status lxw_step(lxw_solver* S, double T, double* dt_taken) {
   if (S->batch) return fail(LXW_ERR_UNSUPPORTED, "a batch advances by step counts (lxw_batch_advance_steps)");
   if (!(S->hsc.t < T)) return fail(LXW_ERR_ARG, "t >= T");
   lxw_status s = set_end_time(S, T);
-  if (!s) s = enqueue_step(S);
+  if (!s) s = solo(S) ? solo_steps(S, 1) : enqueue_step(S);
   if (s) return s;
   s = sync_check(S);
   if (dt_taken) *dt_taken = S->hsc.dt;

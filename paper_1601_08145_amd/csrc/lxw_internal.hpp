@@ -223,6 +223,15 @@ inline int egrid_blocks(int n, int bs) { return ((n + bs - 1) / bs + 7) / 8 * 8;
 
 template <class E, class R>
 hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_t st, int n_mesh, int mode);
+// n_steps whole steps of a mesh of at most SoloMax elements in one workgroup; same results as the
+// separate kernels (0: not built for that element).
+template <class E>
+struct SoloMax { static constexpr int n = 0; };
+template <> struct SoloMax<ElLine> { static constexpr int n = 512; };
+template <> struct SoloMax<ElLine3> { static constexpr int n = 512; };
+template <> struct SoloMax<ElTri> { static constexpr int n = 256; };
+template <class E, class R>
+hipError_t launch_solo(const View<R>& v, hipStream_t st, int n_steps);
 // n_steps whole steps of a batch (v.mesh_of set) in one cooperative launch of workgroups of bs
 // lanes (64, 128 or 256), as many as stay resident together; same results as the separate kernels.
 template <class E, class R>

@@ -3088,6 +3088,75 @@ hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mes
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)nb), dim3((unsigned)bs), args, lds, st);
 }
 
+// ---------------------------------------------------------------------------------------------
+// k_solo: n_steps whole steps of a small mesh in one workgroup, its phases (the bodies of k_pre, k_elem,
+// k_flux, k_update) between workgroup barriers.  A step of separate launches takes 4 to 5 us per launch
+// whatever the mesh.  Per step, here against separate launches: 200 cells in float64 8.6 / 19.6 us (512:
+// 12.0 / 20.9, 1024: 22.2 / 21.2), P3 13.0 / 23.1 (512: 20.1 / 24.9, 1024: 36.8 / 25.0), 242 triangles 28.1 /
+// 40.4 us (512: 42.3 / 41.5); hence the limits in SoloMax.
+// The wave speed is reduced in LDS and t, dt and s stay in registers; the mesh's scalars are read once and
+// written once.
+// ---------------------------------------------------------------------------------------------
+template <class E, class R, int pmode>
+__global__ __launch_bounds__(512) void k_solo(View<R> v, int n_steps) {
+  __shared__ double red[8];
+  const int tid = (int)threadIdx.x, bs = (int)blockDim.x, N = v.N;
+  const Scalars S = v.sc[0];
+  double t = S.t;
+  bool pending = S.shock_pending != 0;
+  StepDt D = {S.s, S.dt, false};
+  long long done = 0;
+  for (int step = 0; step < n_steps; ++step) {
+    if (!(t < S.T)) { D.idle = true; break; }
+    double x = 0.0;
+    for (int i = tid; i < N; i += bs) x = fmax(x, pre_elem<E, R, pmode>(v, i, 0, pending));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o));
+    if ((tid & 63) == 0) red[tid >> 6] = x;
+    __syncthreads();
+    x = red[0];
+    for (int w = 1; w < (bs >> 6); ++w) x = fmax(x, red[w]);
+    D = step_dt(S, x, t);
+    if (tid == 0 && (!(x > 0.0) || !isfinite(x))) report(v.err, E_NONFINITE, -1);
+    for (int i = tid; i < N; i += bs) elem_step<E, R>(v, i, D);
+    __syncthreads();
+    for (int i = tid; i < N; i += bs) flux_step<E, R>(v, i, D);
+    __syncthreads();
+    for (int i = tid; i < N; i += bs) update_step<E, R>(v, i, D);
+    __syncthreads();
+    t += D.dt;
+    pending = v.shock != 0;
+    ++done;
+  }
+  if (tid == 0) {
+    Scalars& O = v.sc[0];
+    O.s = D.s;
+    O.dt = D.dt;
+    O.idle = D.idle;
+    O.t = t;
+    O.steps = S.steps + done;
+    O.shock_pending = pending;
+  }
+}
+
+template <class E, class R>
+hipError_t launch_solo(const View<R>& v, hipStream_t st, int n_steps) {
+  if constexpr (SoloMax<E>::n == 0) {
+    return hipErrorInvalidValue;
+  } else {
+    if (v.mesh_of || v.N < 1 || v.N > SoloMax<E>::n || n_steps < 1) return hipErrorInvalidValue;
+    const int bs = v.N <= 256 ? 256 : 512;
+    const int lds = std::max(ElemShape<E, R>::lds, FluxShape<E, R>::lds) * bs;
+    switch ((v.theta_exact ? 1 : 0) + (v.s_avg ? 2 : 0)) {
+      case 0: hipLaunchKernelGGL((k_solo<E, R, 0>), dim3(1), dim3(bs), lds, st, v, n_steps); break;
+      case 1: hipLaunchKernelGGL((k_solo<E, R, 3>), dim3(1), dim3(bs), lds, st, v, n_steps); break;
+      case 2: hipLaunchKernelGGL((k_solo<E, R, 4>), dim3(1), dim3(bs), lds, st, v, n_steps); break;
+      default: hipLaunchKernelGGL((k_solo<E, R, 5>), dim3(1), dim3(bs), lds, st, v, n_steps); break;
+    }
+    return hipGetLastError();
+  }
+}
+
 #if LXW_PART == 0
 // Sets the end time of every mesh (a kernel, so that it is ordered on the stream and may be
 // captured).
@@ -3160,6 +3229,8 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
 
 template hipError_t launch<EL, double>(KernelId, const View<double>&, const LaunchCfg&, hipStream_t, int, int);
 template hipError_t launch<EL, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
+template hipError_t launch_solo<EL, double>(const View<double>&, hipStream_t, int);
+template hipError_t launch_solo<EL, float>(const View<float>&, hipStream_t, int);
 #if LXW_PART < 3
 template hipError_t launch_persistent<EL, double>(const View<double>&, int, hipStream_t, int, int);
 template hipError_t launch_persistent<EL, float>(const View<float>&, int, hipStream_t, int, int);

@@ -1031,11 +1031,13 @@ struct ElemShape {
   // interior states kept in LDS per lane, where four wavefronts per CU still fit (float64 tetrahedra form
   // them twice)
   static constexpr bool keep = E::kind == ElTri::kind || (E::DIM == 3 && sizeof(R) == 4);
-  static constexpr int lds = keep ? E::NI * E::V * (int)sizeof(R) : 0;
+  // bytes per lane: those, or the float32 square's modes and monomials of D
+  static constexpr int lds = keep ? E::NI * E::V * (int)sizeof(R)
+                                  : (E::kind == ElQuad::kind && sizeof(R) == 4 ? 16 * E::V * (int)sizeof(R) : 0);
   // Waves per SIMD the register allocation targets, the most that spill next to nothing: three for float32
-  // triangles (168 registers, 8 bytes of scratch a lane; 129 us on 999,698 against 138 at two), two for
-  // float64 triangles (58 / 65 us on 250k), float32 P3 triangles (138 / 184 us on 250k) and the float32
-  // square (111 / 153 us on 262k), one elsewhere
+  // triangles (168 registers; 129 us on 999,698 against 138 at two), two for float64 triangles (58 / 65 us on
+  // 250k), float32 P3 triangles (138 / 184 us on 250k) and the float32 square (its LDS holds no third; 74 us on
+  // 262k with the modes and D in LDS, 135 with them in registers and 59 of those spilled), one elsewhere
   // (float32 tetrahedra: their states fill the LDS with one; 307 us on 280k, 463 at two without them).
   static constexpr int waves = E::DIM != 2 || (sizeof(R) == 8 && E::ML > ElTri::ML) ? 1 : (sizeof(R) == 4 && E::ML == ElTri::ML ? 3 : 2);
 };
@@ -1432,7 +1434,7 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
   }
 }
 
-// P2 on the line and Q2 on the square.
+// P2 on the line.
 template <class E, class RS>
 __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const StepDt& D) {
   // The line computes in float64 whatever it stores: the same rate, few registers, and the rounding that is
@@ -1482,10 +1484,8 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
     }
   };
 
-  // P2 on the line: grad q and div F^h are linear and their derivatives constant, so they are formed
-  // once per element from their values at the reference origin.  On the tensor Q2 square they are not
-  // linear: its points contract F^h and the modes directly.
-  constexpr bool AFF = DIM == 1;
+  // grad q and div F^h are linear and their derivatives constant, so they are formed once per element from
+  // their values at the reference origin.
   // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m)
   R Fh[DIM][V][ML];
   R D0[V], gDr[V][DIM];
@@ -1522,38 +1522,36 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
     for (int l = 0; l < ML - 1; ++l) vol[c][l] = R(0);
 
   R g0[V][DIM], Hq[V][E::ND2], gDx[DIM][V];
-  if constexpr (AFF) {
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      R dd = R(0), hh = R(0);  // div F^h and its derivative at the origin
+  for (int c = 0; c < V; ++c) {
+    R dd = R(0), hh = R(0);  // div F^h and its derivative at the origin
 #pragma unroll
-      for (int l = 0; l < ML; ++l) {
-        dd += Fh[0][c][l] * T.dphi0[0][l];
-        hh += Fh[0][c][l] * T.d2c[0][l];
-      }
-      D0[c] = dd;
-      gDr[c][0] = hh;
+    for (int l = 0; l < ML; ++l) {
+      dd += Fh[0][c][l] * T.dphi0[0][l];
+      hh += Fh[0][c][l] * T.d2c[0][l];
+    }
+    D0[c] = dd;
+    gDr[c][0] = hh;
 #pragma unroll
-      for (int a = 0; a < DIM; ++a) {
-        R acc = R(0);
+    for (int a = 0; a < DIM; ++a) {
+      R acc = R(0);
 #pragma unroll
-        for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.dphi0[a][l];
-        g0[c][a] = thR * acc;
-      }
+      for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.dphi0[a][l];
+      g0[c][a] = thR * acc;
+    }
 #pragma unroll
-      for (int k = 0; k < E::ND2; ++k) {
-        R acc = R(0);
+    for (int k = 0; k < E::ND2; ++k) {
+      R acc = R(0);
 #pragma unroll
-        for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.d2c[k][l];
-        Hq[c][k] = thR * acc;
-      }
+      for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.d2c[k][l];
+      Hq[c][k] = thR * acc;
+    }
 #pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        R sh = R(0);
+    for (int d = 0; d < DIM; ++d) {
+      R sh = R(0);
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) sh += Ji[a][d] * gDr[c][a];
-        gDx[d][c] = sg3 * sh;
-      }
+      for (int a = 0; a < DIM; ++a) sh += Ji[a][d] * gDr[c][a];
+      gDx[d][c] = sg3 * sh;
     }
   }
 
@@ -1561,55 +1559,12 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
   auto derivs = [&](int p, R* q, R* qt, R* qtt) {
     R gq[DIM][V], D[V], gD[DIM][V];
     state_at(p, q);
-    if constexpr (AFF) {
-      R x[DIM];
+    const R x = T.xr[p][0];
 #pragma unroll
-      for (int a = 0; a < DIM; ++a) x[a] = T.xr[p][a];
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R g[DIM];
-        g[0] = g0[c][0] + Hq[c][0] * x[0];
-        D[c] = D0[c] + gDr[c][0] * x[0];
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          R sg = R(0);
-#pragma unroll
-          for (int a = 0; a < DIM; ++a) sg += Ji[a][d] * g[a];
-          gq[d][c] = sg3 * sg;
-          gD[d][c] = gDx[d][c];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R g[DIM];
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) g[a] = R(0);
-        R dd = R(0);
-        R h[DIM];
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) h[a] = R(0);
-#pragma unroll
-        for (int l = 0; l < ML; ++l) {
-#pragma unroll
-          for (int a = 0; a < DIM; ++a) {
-            if (l > 0) g[a] += Qr[c][l - 1] * T.dphi[p][a][l];
-            dd += Fh[a][c][l] * T.dphi[p][a][l];
-          }
-          // d/dxi_b sum_a d/dxi_a Fc_a: b = 0 uses (xx, xy), b = 1 uses (xy, yy)
-          h[0] += Fh[0][c][l] * T.d2phi[p][0][l] + Fh[DIM - 1][c][l] * T.d2phi[p][1][l];
-          h[DIM - 1] += Fh[0][c][l] * T.d2phi[p][1][l] + Fh[DIM - 1][c][l] * T.d2phi[p][DIM][l];
-        }
-        D[c] = dd;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          R sg = R(0), sh = R(0);
-#pragma unroll
-          for (int a = 0; a < DIM; ++a) { sg += Ji[a][d] * g[a]; sh += Ji[a][d] * h[a]; }
-          gq[d][c] = (sg3 * thR) * sg;
-          gD[d][c] = sg3 * sh;
-        }
-      }
+    for (int c = 0; c < V; ++c) {
+      D[c] = D0[c] + gDr[c][0] * x;
+      gq[0][c] = sg3 * (Ji[0][0] * (g0[c][0] + Hq[c][0] * x));
+      gD[0][c] = gDx[0][c];
     }
 #pragma unroll
     for (int c = 0; c < V; ++c) qt[c] = -D[c];
@@ -1702,6 +1657,296 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
       }
     }
   }
+}
+
+// Q2 on the square (its cells are rectangles: the map's gradient is diagonal), by lines of points: the three
+// interior rows and the four edges.  A line fixes one coordinate, so the modes and D = div F^h collapse to
+// polynomials along it once per line (q and its two derivatives as quadratics, D as its 8 monomials
+// collapsed likewise) and a point costs 11 multiply-adds per variable; contracting all 9 modes of q and of
+// both F^h at every point took 86.  F^h itself is kept only in the modes that div sees (6 of 9 per direction),
+// and the mass flux is its own projection.
+//
+// Bound by instruction issue.  512x512 squares FP32-mixed 108 -> 74 us, 128,700 in float64 120 -> 60 us.
+template <class E, class R>
+__device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const StepDt& D) {
+  constexpr int V = 4, ML = 9, NQE = 3;
+  constexpr int MI[9] = {0, 1, 0, 2, 1, 0, 2, 1, 2}, MJ[9] = {0, 0, 1, 0, 1, 2, 1, 2, 2};  // mode l = L_MI(x) L_MJ(y)
+  constexpr int AT[3][3] = {{0, 2, 5}, {1, 4, 7}, {3, 6, 8}};
+  constexpr double r3 = 1.7320508075688772935, r5 = 2.2360679774997896964;  // L_1 = r3 x, L_2 = r5 (3 x^2 - 1) / 2
+  const RefTab<E, R>& T = TabSel<E, R>::get();
+  const RefTab<E, double>& TD = TabSel<E, double>::get();
+  const int N = v.N;
+  if (i >= N) return;
+  const bool idle = D.idle;  // applied at the store: at the end time the step changes nothing
+  const R dt = R(D.dt);
+  const R gm1 = R(v.gamma - 1.0);
+
+  // stored modes (before the limiter) and the limiter factor theta of this step
+  double qb[V];
+  R Qr[V][ML - 1];
+#pragma unroll
+  for (int c = 0; c < V; ++c) {
+    qb[c] = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
+#pragma unroll
+    for (int l = 1; l < ML; ++l) Qr[c][l - 1] = at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i);
+  }
+  const double th = at(v.theta, i);
+  const R thR = R(th);
+  const R Ji[2] = {at(v.Jinv, i), at(v.Jinv + (size_t)3 * N, i)};
+  // float32: the modes and D's monomials wait in LDS between the lines, which read them once each; read at an
+  // offset the compiler cannot follow, or it would keep them in registers
+  constexpr bool lds = ElemShape<E, R>::lds > 0;
+  extern __shared__ __align__(16) unsigned char dyn[];
+  auto put = [&](int at4, const R* x) { *reinterpret_cast<float4*>(dyn + ((size_t)at4 * blockDim.x + threadIdx.x) * 16) = make_float4(x[0], x[1], x[2], x[3]); };
+  auto take = [&](int at4, int lane, R* x) {
+    const float4 f = *reinterpret_cast<const float4*>(dyn + ((size_t)at4 * blockDim.x + lane) * 16);
+    x[0] = f.x; x[1] = f.y; x[2] = f.z; x[3] = f.w;
+  };
+  auto hidden_lane = [] { int t = (int)threadIdx.x; asm volatile("" : "+v"(t)); return t; };
+  auto modes = [&](int lane, int c, R* x) {
+    if constexpr (lds) { take(2 * c, lane, x); take(2 * c + 1, lane, x + 4); }
+    else {
+#pragma unroll
+      for (int l = 0; l < ML - 1; ++l) x[l] = Qr[c][l];
+    }
+  };
+  if constexpr (lds)
+#pragma unroll
+    for (int c = 0; c < V; ++c) { put(2 * c, Qr[c]); put(2 * c + 1, Qr[c] + 4); }
+  const R JG[2] = {dt * R(1.0 / 3.0) * Ji[0], dt * R(1.0 / 3.0) * Ji[1]};  // scaled for q's gradients, see Pt2
+
+  // q on the line where the cross coordinate is x0: U_0 + U_1 L_1 + U_2 L_2, limited, in float64
+  // (Y: the line runs along y)
+  auto state_line = [&](auto Y, double x0, int lane, double (&U)[V][3]) {
+    const double l1 = r3 * x0, l2 = 0.5 * r5 * (3.0 * x0 * x0 - 1.0);
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      R Qc[ML - 1];
+      modes(lane, c, Qc);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        auto Q = [&](int j) { return double(Qc[(Y.value ? AT[j][m] : AT[m][j]) - 1]); };
+        double t = Q(1) * l1 + Q(2) * l2;
+        if (m) t += Q(0);
+        U[c][m] = m ? th * t : qb[c] + th * t;
+      }
+    }
+  };
+
+  // Sec. 2.3 Step 1 composed with div: c1 D in monomials, dm[3 a + b] x^a y^b (x^2 y^2 does not occur)
+  R dm[V][8];
+  auto monomials = [&](int lane, int c, R* x) {
+    if constexpr (lds) { take(2 * V + 2 * c, lane, x); take(2 * V + 2 * c + 1, lane, x + 4); }
+    else {
+#pragma unroll
+      for (int l = 0; l < 8; ++l) x[l] = dm[c][l];
+    }
+  };
+  {
+    R Fx[V][2][3], Fy[V][2][3];  // the modes of F^h_x with i = 1, 2 and of F^h_y with j = 1, 2
+    const R jc[2] = {R(0.5) * dt * Ji[0], R(0.5) * dt * Ji[1]};
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        Fx[0][m][j] = jc[0] * (thR * Qr[1][AT[m + 1][j] - 1]);
+        Fy[0][m][j] = jc[1] * (thR * Qr[2][AT[j][m + 1] - 1]);
+#pragma unroll
+        for (int c = 1; c < V; ++c) Fx[c][m][j] = Fy[c][m][j] = R(0);
+      }
+#pragma unroll 1
+    for (int row = 0; row < 3; ++row) {
+      double U[V][3];
+      state_line(std::false_type{}, TD.xr[3 * row][1], lds ? hidden_lane() : 0, U);
+#pragma unroll 1
+      for (int n = 0; n < 3; ++n) {
+        const int m = 3 * row + n;
+        const double x = TD.xr[n][0];
+        const double l1 = r3 * x, l2 = 0.5 * r5 * (3.0 * x * x - 1.0);
+        R q[V], F[2][V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) q[c] = R(U[c][0] + l1 * U[c][1] + l2 * U[c][2]);
+        const St<2, R> s = base_state<2, R>(q, gm1);
+#pragma unroll
+        for (int d = 0; d < 2; ++d) flux<2, R>(s, d, F[d]);
+#pragma unroll
+        for (int c = 1; c < V; ++c) {
+          const R fx = jc[0] * F[0][c], fy = jc[1] * F[1][c];
+#pragma unroll
+          for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              Fx[c][a][j] += T.wphi[m][AT[a + 1][j]] * fx;
+              Fy[c][a][j] += T.wphi[m][AT[j][a + 1]] * fy;
+            }
+        }
+      }
+    }
+    // d/dx: L_1' = r3, L_2' = 3 r5 x; the other factor L_j in monomials
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+#pragma unroll
+      for (int a = 0; a < 8; ++a) dm[c][a] = R(0);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const R g = a ? R(3.0 * r5) : R(r3);
+        dm[c][3 * a] += g * (Fx[c][a][0] - R(0.5 * r5) * Fx[c][a][2]);
+        dm[c][3 * a + 1] += g * (R(r3) * Fx[c][a][1]);
+        dm[c][3 * a + 2] += g * (R(1.5 * r5) * Fx[c][a][2]);
+        dm[c][a] += g * (Fy[c][a][0] - R(0.5 * r5) * Fy[c][a][2]);
+        dm[c][3 + a] += g * (R(r3) * Fy[c][a][1]);
+        dm[c][6 + a] += g * (R(1.5 * r5) * Fy[c][a][2]);
+      }
+      if constexpr (lds) { put(2 * V + 2 * c, dm[c]); put(2 * V + 2 * c + 1, dm[c] + 4); }
+    }
+  }
+
+  // Sec. 2.3 Step 2 at the three points of a line: body(n, q, qt, qtt, s), n the point's place on the line
+  auto line = [&](auto Y, const double x0, auto&& body) {
+    constexpr int al = Y.value ? 1 : 0, cr = 1 - al;  // directions along and across
+    const R t0 = R(x0);
+    double U[V][3];
+    const int lane = lds ? hidden_lane() : 0;
+    state_line(Y, x0, lane, U);
+    R ga[V][2], gc[V][3], e[V][3], ea[V][2], ec[V][3];
+    const R c1 = JG[cr] * thR * R(r3), c2 = JG[cr] * thR * R(3.0 * r5) * t0;
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      R Qc[ML - 1], dc[8];
+      modes(lane, c, Qc);
+      monomials(lane, c, dc);
+      ga[c][0] = JG[al] * R(r3) * R(U[c][1]);
+      ga[c][1] = JG[al] * R(3.0 * r5) * R(U[c][2]);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        auto Q = [&](int j) { return Qc[(Y.value ? AT[j][m] : AT[m][j]) - 1]; };
+        auto d = [&](int j) { return dc[Y.value ? 3 * j + m : 3 * m + j]; };
+        gc[c][m] = c1 * Q(1) + c2 * Q(2);
+        e[c][m] = m == 2 ? d(0) + t0 * d(1) : d(0) + t0 * (d(1) + t0 * d(2));
+        ec[c][m] = m == 2 ? JG[cr] * d(1) : JG[cr] * (d(1) + R(2) * t0 * d(2));
+      }
+      ea[c][0] = JG[al] * e[c][1];
+      ea[c][1] = R(2) * JG[al] * e[c][2];
+    }
+#pragma unroll 1
+    for (int n = 0; n < 3; ++n) {
+      const double xd = TD.xr[n][0];
+      const double p1 = r3 * xd, p2 = 0.5 * r5 * (3.0 * xd * xd - 1.0);
+      const R x = R(xd), l1 = R(p1), l2 = R(p2);
+      R q[V], qt[V], qtt[V], gq[2][V], gD[2][V];
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        q[c] = R(U[c][0] + p1 * U[c][1] + p2 * U[c][2]);
+        qt[c] = -(e[c][0] + x * (e[c][1] + x * e[c][2]));
+        gq[al][c] = ga[c][0] + x * ga[c][1];
+        gq[cr][c] = gc[c][0] + l1 * gc[c][1] + l2 * gc[c][2];
+        gD[al][c] = ea[c][0] + x * ea[c][1];
+        gD[cr][c] = ec[c][0] + x * (ec[c][1] + x * ec[c][2]);
+      }
+      const Pt2<2, R> s = pt2_of<2, R>(q, qt, gm1);
+      qtt_of<2, R>(s, q, qt, gq, gD, gm1, qtt);
+      body(n, q, qt, qtt, s);
+    }
+  };
+
+  // interior points: volume term V_l = sum_m w_m grad phi_l . F_T
+  {
+    R vol[V][ML - 1];
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+#pragma unroll
+      for (int l = 0; l < ML - 1; ++l) vol[c][l] = R(0);
+#pragma unroll 1
+    for (int row = 0; row < 3; ++row)
+      line(std::false_type{}, TD.xr[3 * row][1], [&](int n, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
+        const int m = 3 * row + n;
+        R FT[2][V];
+        ft2<2, R>(s, q, qt, qtt, gm1, FT);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int c = 0; c < V; ++c) {
+            const R fc = Ji[a] * FT[a][c];
+#pragma unroll
+            for (int l = 1; l < ML; ++l)
+              if ((a == 0 ? MI[l] : MJ[l]) > 0) vol[c][l - 1] += T.wdphi[m][a][l] * fc;
+          }
+      });
+    // Sec. 2.3 Step 3 / Sec. 3.3 Step 6, volume part: Q^(l) += dt V_l for l >= 2.  Stored before the
+    // edge points (which use the modes held in registers), so the accumulators are free for them.
+    const int lane = lds ? hidden_lane() : 0;
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      R Qc[ML - 1];
+      modes(lane, c, Qc);
+#pragma unroll
+      for (int l = 1; l < ML; ++l)
+        at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i) = idle ? Qc[l - 1] : thR * Qc[l - 1] + dt * vol[c][l - 1];
+    }
+    if (v.dbg_vol) {
+#pragma unroll
+      for (int c = 0; c < V; ++c) {
+        v.dbg_vol[(c * ML) * N + i] = 0.0;
+#pragma unroll
+        for (int l = 1; l < ML; ++l) v.dbg_vol[(c * ML + l) * N + i] = double(vol[c][l - 1]);
+      }
+    }
+  }
+
+  // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
+  const double hs0 = 0.5 * D.s;
+  // edges 0 (y = -1) and 2 (y = 1, points in descending x), 3 (x = -1, descending y) and 1 (x = 1)
+  auto edge_pair = [&](auto Y) {
+#pragma unroll 1
+    for (int hi = 0; hi < 2; ++hi) {
+      const int k = Y.value ? 3 - 2 * hi : 2 * hi;
+      const bool rev = k >= 2;
+      const int slot = at(v.eslot + (size_t)k * N, i);
+      const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
+      R n[2], len2 = R(0);
+#pragma unroll
+      for (int d = 0; d < 2; ++d) { n[d] = at(v.nout + (size_t)(k * 2 + d) * N, i); len2 += n[d] * n[d]; }
+      // s |n_e| / 2: both elements of an edge hold the same normal up to sign, so they form it alike
+      const R hs = R(hs0 * double(sqrt(len2)));
+      line(Y, hi ? 1.0 : -1.0, [&](int np, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
+        const int jj = (side != 0) == rev ? np : NQE - 1 - np;  // point order of i_e along the edge
+        R fn[V], b[V];
+        ftn2<2, R>(s, q, qt, qtt, n, gm1, fn);
+#pragma unroll
+        for (int c = 0; c < V; ++c) b[c] = R(0.5) * fn[c] + hs * q[c];
+        store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
+        if (bc != SB_INTERIOR) {
+          R qg[V], fgn[V];
+          if (bc == SB_TRANSPARENT) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) { qg[c] = q[c]; fgn[c] = fn[c]; }
+          } else if (bc == SB_REFLECTIVE) {
+            const R il = R(1) / sqrt(here(len2));
+            const R nh[2] = {n[0] * il, n[1] * il};
+            R qtg[V], qttg[V];
+            reflect<2, R>(q, nh, qg);
+            reflect<2, R>(qt, nh, qtg);
+            reflect<2, R>(qtt, nh, qttg);
+            ftn_from<2, R>(qg, qtg, qttg, n, gm1, fgn);
+          } else {
+            R z[V];
+#pragma unroll
+            for (int c = 0; c < V; ++c) z[c] = R(0);
+            inflow_state<2, R>(v.inflow, qg);
+            qg[0] = here(qg[0]);
+            ftn_from<2, R>(qg, z, z, n, gm1, fgn);
+          }
+          R bg[V];  // the ghost is side 1: its outward normal is -n
+#pragma unroll
+          for (int c = 0; c < V; ++c) bg[c] = hs * qg[c] - R(0.5) * fgn[c];
+          store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
+        }
+      });
+    }
+  };
+  edge_pair(std::false_type{});
+  edge_pair(std::true_type{});
 }
 
 // P3 on triangles.  The Taylor series of Sec. 2.2 one term further: F_T needs q_ttt = -div F_tt, which takes
@@ -2562,6 +2807,7 @@ __device__ __forceinline__ void elem_step(const View<R>& v, const int i, const S
   if constexpr (E::DEG == 3 && E::DIM == 2) elem_tri3<E, R>(v, i, D);
   else if constexpr (E::DEG == 3) elem_item3<E, R>(v, i, D);
   else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i, D);
+  else if constexpr (E::kind == ElQuad::kind) elem_quad<E, R>(v, i, D);
   else elem_item2<E, R>(v, i, D);
 }
 

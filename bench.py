@@ -52,26 +52,26 @@ STEP_BYTES_PER_ELEM = 228
 # div F^h, grad div F^h and F_T at 16 points, volume term, traces.  Counted from the kernel's
 # executed VALU instructions per wavefront (64 triangles): fp32 FMA x 2 + fp32 add + fp32 mul +
 # fp64 FMA x 2 + fp64 add + fp64 mul, divided by 64 (profiles/lxw_kernels_tri_c3_counters.md).
-KELEM_FLOPS_PER_ELEM = 9.41e3
+KELEM_FLOPS_PER_ELEM = 6.13e3
 # The bound k_elem actually meets: VALU instruction issue.  Executed VALU instructions per wavefront
 # of 64 triangles (SQ_INSTS_VALU / SQ_WAVES, same counter file); a wave64 VALU instruction occupies a
 # 16-lane SIMD for 4 cycles, and the chip has 256 CUs x 4 SIMDs at 2.4 GHz.
-KELEM_VALU_INSTS_PER_WAVE = 5872
+KELEM_VALU_INSTS_PER_WAVE = 3838
 VALU_SIMDS, CLOCK_GHZ = 1024, 2.4
 # Bytes k_elem must move per triangle (FP32-mixed): cell averages in (4 x f64), higher modes in
 # (20 x f32), limiter factor (f64), geometry (Jinv 4 x f32, outward normals 6 x f32, edge slots
 # 3 x i32), higher modes out (20 x f32), traces out (3 edges x 3 points x 4 x f32: one record per
-# edge side and point, n_out.F_T/2 + (s|n|/2) q).
+# edge side and point, n_out.F_T/2 + (s|n|/2) q), the averages' copy out (4 x f64).
 def kelem_bytes_per_elem(rsize):
-    return 4 * 8 + 20 * rsize + 8 + 10 * rsize + 12 + 20 * rsize + 36 * rsize
+    return 4 * 8 + 20 * rsize + 8 + 10 * rsize + 12 + 20 * rsize + 36 * rsize + 4 * 8
 
 
 # HBM traffic of one launch of each step kernel on the 2D triangle workload (FP32-mixed) from
 # rocprofv3 counters (FETCH_SIZE x 2 + WRITE_SIZE, scale factors from a copy of known size), valid
 # only for the kernel source it was measured on.
-TRAFFIC = {"src_sha256": "e2c6f33d22e97d9db911cd1b7a12a36f6a8142f6f385f2e124f4789be58e47d0",
-           "bytes_per_launch": {"k_pre": 138976369, "k_elem": 409446605, "k_edge": 381145088,
-                                "k_flim": 174059520, "k_update": 399809536}}  # profiles/lxw_kernels_tri_c3_counters.md
+TRAFFIC = {"src_sha256": "ad54c769fb570fc90086194d53228f36ed36b3313ca37c908a96a765dcef1929",
+           "bytes_per_launch": {"k_pre": 135326413, "k_elem": 597375283, "k_edge": 460419482,
+                                "k_update": 68331520}}  # profiles/lxw_kernels_tri_c3_counters.md
 
 
 def traffic_valid():

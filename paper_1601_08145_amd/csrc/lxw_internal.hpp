@@ -85,7 +85,7 @@ struct Scalars {
   double geo;                 // max_i |dT_i| / (2|T_i|)
   double cfl;
   int shock_pending;          // the shock-capturing limiter of the previous step is still due
-  int idle;                   // set by k_dt when t >= T: the rest of the step changes nothing
+  int idle;                   // set with dt when t >= T: the rest of the step changes nothing
   long long steps;
 };
 

@@ -1022,7 +1022,7 @@ __device__ __forceinline__ R here(R x) {
 // The edges come before the volume term: the coefficients a are dead by the time its accumulators live,
 // and the modes are read again for the update.
 //
-// Bound by instruction issue: 3,700 VALU instructions per wavefront of float32 triangles (5,870 with
+// Bound by instruction issue: 3,840 VALU instructions per wavefront of float32 triangles (5,870 with
 // Jacobian and Hessian products, states evaluated mode by mode and every V_l accumulated at every point):
 // 168 -> 129 us on 999,698 triangles; float64 250k 78 -> 58 us; tetrahedra 467 -> 307 us (280k, FP32-mixed)
 // and 163 -> 104 us (25k, float64).

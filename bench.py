@@ -69,7 +69,7 @@ def kelem_bytes_per_elem(rsize):
 # HBM traffic of one launch of each step kernel on the 2D triangle workload (FP32-mixed) from
 # rocprofv3 counters (FETCH_SIZE x 2 + WRITE_SIZE, scale factors from a copy of known size), valid
 # only for the kernel source it was measured on.
-TRAFFIC = {"src_sha256": "98b788ef283d0d1a9f15265c94a941a0e5e0986da65d838db14de78c9c5bdaee",
+TRAFFIC = {"src_sha256": "f8f34bfca1a77eac7c9709f1d402ea216096359d04f8f47576f8b5a36e212487",
            "bytes_per_launch": {"k_pre": 135326413, "k_elem": 597375283, "k_edge": 460419482,
                                 "k_update": 68331520}}  # profiles/lxw_kernels_tri_c3_counters.md
 

@@ -1666,7 +1666,7 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
 // both F^h at every point took 86.  F^h itself is kept only in the modes that div sees (6 of 9 per direction),
 // and the mass flux is its own projection.
 //
-// Bound by instruction issue.  512x512 squares FP32-mixed 108 -> 74 us, 128,700 in float64 120 -> 60 us.
+// Bound by instruction issue.  512x512 squares FP32-mixed 108 -> 74 us, 123,300 in float64 120 -> 60 us.
 template <class E, class R>
 __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = 4, ML = 9, NQE = 3;
@@ -3013,7 +3013,7 @@ __device__ double mu_solve(const double* qL, const double* qa, double gam, doubl
 // Faces one after another in a loop, their fluxes kept in LDS, or all unrolled, their fluxes in registers:
 // unrolled where every face's loads then fit the registers together (1D; float32 P2 triangles: 235
 // registers, 115 us on 999,698 against 126 us in the loop), the loop elsewhere (it needs no spill and
-// little code: float64 triangles 42 against 49 us on 250k, the float64 square 35 / 40 us on 118k, P3
+// little code: float64 triangles 42 against 49 us on 250k, the float64 square 35 / 40 us on 123k, P3
 // 38 / 46 us on 250k, tetrahedra 133 / 182 us on 280k and 37 / 109 us in float64 on 25k).
 template <class E, class R>
 struct FluxShape {

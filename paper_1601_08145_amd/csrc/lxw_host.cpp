@@ -859,7 +859,7 @@ struct lxw_solver {
   Scalars hsc{};
   bool debug = false;
   // diagnostics copies
-  double *dfw = nullptr, *dff = nullptr;  // [E][V] fluxes
+  double *dfw = nullptr, *dff = nullptr;  // [E][2][V] fluxes
   double* dq_upd_bar = nullptr;
   void* dq_upd_h = nullptr;
   // timing
@@ -2054,8 +2054,8 @@ lxw_status lxw_set_debug(lxw_solver* S, int32_t keep) {
     if ((s = S->alloc(&p2, (size_t)V * (ML - 1) * N * rs))) return s;
     S->dq_upd_h = p2;
     double *a, *b, *c, *d, *q, *fw, *ff;
-    if ((s = S->alloc(&fw, (size_t)V * M.E))) return s;
-    if ((s = S->alloc(&ff, (size_t)V * M.E))) return s;
+    if ((s = S->alloc(&fw, (size_t)2 * V * M.E))) return s;
+    if ((s = S->alloc(&ff, (size_t)2 * V * M.E))) return s;
     S->dfw = fw;
     S->dff = ff;
     if ((s = S->alloc(&q, (size_t)V * ML * N))) return s;
@@ -2132,13 +2132,11 @@ lxw_status lxw_debug_stage(lxw_solver* S, int32_t stage, double* out) {
     case LXW_STAGE_FLXW:
     case LXW_STAGE_FLXF: {
       const bool w = stage == LXW_STAGE_FLXW;
-      if ((s = dget(w ? S->dfw : S->dff, (size_t)V * E, h))) return s;
+      if ((s = dget(w ? S->dfw : S->dff, (size_t)2 * V * E, h))) return s;
       for (int i = 0; i < N; ++i)
         for (int k = 0; k < K; ++k) {
-          const int slot = M.eslot[(size_t)i * K + k];
-          const int e = slot >> 3;
-          const double ep = ((slot >> 2) & 1) ? -1.0 : 1.0;
-          for (int v = 0; v < V; ++v) out[((size_t)M.perm[i] * K + k) * V + v] = ep * h[(size_t)e * V + v];
+          const int es = M.eslot[(size_t)i * K + k] >> 2;  // edge and side
+          for (int v = 0; v < V; ++v) out[((size_t)M.perm[i] * K + k) * V + v] = h[(size_t)es * V + v];
         }
       return LXW_OK;
     }

@@ -151,8 +151,8 @@ struct View {
   double* dbg_theta;      // [N]
   double* dbg_theta_sc;   // [N]
   double* dbg_vol;        // [V][ML][N]
-  double* fLxW;           // [E][V] f^LxW of edge e, in the first element's orientation
-  double* fLxF;           // [E][V] f^LxF likewise
+  double* fLxW;           // [E][2][V] f^LxW of edge e out of the element of each side, as that element formed it
+  double* fLxF;           // [E][2][V] f^LxF likewise
   double* dbg_lame;       // [K][N]
   double* dbg_qlim;       // [V][ML][N] limited state at the start of the step
 };
@@ -178,6 +178,22 @@ __device__ __forceinline__ const Global<T>& at(const T* col, int i) {
   const Global<T>* g = (const Global<T>*)col;
   asm("" : "+s"(g));
   return *(const Global<T>*)((const Global<char>*)g + (unsigned)i * (unsigned)sizeof(T));
+}
+
+// A product, a sum and a difference rounded each by itself: no fused multiply-add is formed from them, whatever
+// they are combined with.  (HIP's __dmul_rn, __dadd_rn and __dsub_rn are the plain operators, which the compiler
+// contracts.)
+__device__ __forceinline__ double mul_rn(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+__device__ __forceinline__ double add_rn(double a, double b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+__device__ __forceinline__ double sub_rn(double a, double b) {
+#pragma clang fp contract(off)
+  return a - b;
 }
 
 // All reference tables in both precisions (built on the host by lxw_host.cpp).

@@ -2839,7 +2839,8 @@ __global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_elem(View<R> 
 // f^LxF_e = (1/2) n_e.(F(q_bar_j) + F(q_bar_i)) - (s |n_e| / 2)(q_bar_j - q_bar_i) in float64.  The two
 // elements get the same bits up to the sign (the averages' update is conservative to rounding): F* and
 // f^LxW are formed in the first element's orientation and point order, and every operation of f^LxF
-// is written out, changes sign with the normal and is symmetric in the two states.
+// is written out with its own rounding, changes sign with the normal and is symmetric in the two states.
+// (Left to the compiler, one side's energy row was fused into the sum and the other's was not.)
 // ---------------------------------------------------------------------------------------------
 // F* at the points of edge e in the first element's order
 template <class E, class R>
@@ -2869,7 +2870,7 @@ __device__ __forceinline__ void lxw_average(const RefTab<E, R>& T, const R (&fs)
   }
 }
 
-// Velocity and pressure of an average, every operation written out
+// Velocity and pressure of an average, every operation with its own rounding
 template <int DIM>
 struct AvgPrim { double u[DIM], p; };
 template <int DIM>
@@ -2879,22 +2880,22 @@ __device__ __forceinline__ AvgPrim<DIM> avg_prim(const double* q, double gm1) {
   double mu = 0.0;
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
-    P.u[d] = __dmul_rn(q[1 + d], r);
+    P.u[d] = mul_rn(q[1 + d], r);
     mu = __fma_rn(q[1 + d], P.u[d], mu);
   }
-  P.p = __dmul_rn(gm1, __fma_rn(-0.5, mu, q[DIM + 1]));
+  P.p = mul_rn(gm1, __fma_rn(-0.5, mu, q[DIM + 1]));
   return P;
 }
 // n . F(q)
 template <int DIM>
 __device__ __forceinline__ void avg_flux(const double* q, const AvgPrim<DIM>& P, const double* n, double* F) {
-  double un = __dmul_rn(P.u[0], n[0]), mn = __dmul_rn(q[1], n[0]);
+  double un = mul_rn(P.u[0], n[0]), mn = mul_rn(q[1], n[0]);
 #pragma unroll
   for (int d = 1; d < DIM; ++d) { un = __fma_rn(P.u[d], n[d], un); mn = __fma_rn(q[1 + d], n[d], mn); }
   F[0] = mn;
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) F[1 + k] = __fma_rn(q[1 + k], un, __dmul_rn(P.p, n[k]));
-  F[DIM + 1] = __dmul_rn(un, __dadd_rn(q[DIM + 1], P.p));
+  for (int k = 0; k < DIM; ++k) F[1 + k] = __fma_rn(q[1 + k], un, mul_rn(P.p, n[k]));
+  F[DIM + 1] = mul_rn(un, add_rn(q[DIM + 1], P.p));
 }
 
 // f^LxF through local edge k of element i (edge e on its side `side`), out of the element; q and P are
@@ -2935,9 +2936,9 @@ __device__ __forceinline__ void lxf_out(const View<R>& v, int i, int k, int e, i
   double Fo[V], Fn[V];
   avg_flux<DIM>(q, P, n, Fo);
   avg_flux<DIM>(qn, Pn, n, Fn);
-  const double h = __dmul_rn(0.5, __dmul_rn(s, len));
+  const double h = mul_rn(0.5, mul_rn(s, len));
 #pragma unroll
-  for (int c = 0; c < V; ++c) f[c] = __fma_rn(-h, __dsub_rn(qn[c], q[c]), __dmul_rn(0.5, __dadd_rn(Fo[c], Fn[c])));
+  for (int c = 0; c < V; ++c) f[c] = __fma_rn(-h, sub_rn(qn[c], q[c]), mul_rn(0.5, add_rn(Fo[c], Fn[c])));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3114,15 +3115,14 @@ __device__ __forceinline__ void flux_step(const View<R>& v, const int i, const S
       for (int l = 0; l < ML - 1; ++l) at(v.Qh + (size_t)(c * (ML - 1) + l) * N, i) = Qh[c][l];
     }
   }
-  if (v.fLxW) {  // stage read-out: the first element's fluxes
+  if (v.fLxW) {  // stage read-out
 #pragma unroll
     for (int k = 0; k < K; ++k)
-      if (!((slot[k] >> 2) & 1))
 #pragma unroll
-        for (int c = 0; c < V; ++c) {
-          v.fLxW[(size_t)(slot[k] >> 3) * V + c] = fW[k][c];
-          v.fLxF[(size_t)(slot[k] >> 3) * V + c] = fF[k][c];
-        }
+      for (int c = 0; c < V; ++c) {
+        v.fLxW[(size_t)(slot[k] >> 2) * V + c] = fW[k][c];
+        v.fLxF[(size_t)(slot[k] >> 2) * V + c] = fF[k][c];
+      }
   }
   // Steps 4-5
   double Gam = area * qb[0] / dt, df[K];

@@ -103,8 +103,8 @@ __global__ __launch_bounds__(TPB) void k_check(const double* Q, int c0, int n, i
   if (e >= m) return;
   const double* qb = lds + e * S;
   double k = 0.0;
-  for (int d = 1; d < V - 1; ++d) k = __dadd_rn(k, __dmul_rn(qb[d], qb[d]));
-  const double p = __dmul_rn(gm1, __dsub_rn(qb[V - 1], __ddiv_rn(__dmul_rn(0.5, k), qb[0])));
+  for (int d = 1; d < V - 1; ++d) k = add_rn(k, mul_rn(qb[d], qb[d]));
+  const double p = mul_rn(gm1, sub_rn(qb[V - 1], mul_rn(0.5, k) / qb[0]));
   if (fail[e] || !(qb[0] >= eps0) || !(p > 0.0)) atomicMin(bad, c0 + i0 + e);
 }
 

@@ -561,9 +561,10 @@ __device__ __forceinline__ float max_num(float a, float b) {
   return d;
 }
 
-// sqrt(x) in float64 for x >= 0 within the normal range (0 gives 1e-140, nothing beside a sound speed):
+// sqrt(x) in float64 for x >= 0 (0 gives 1e-140, nothing beside a sound speed; infinity itself):
 // the hardware's reciprocal square root and two coupled Newton steps on sqrt(x) and 1/(2 sqrt(x)), to within
-// an ulp, in half the instructions of the correctly rounded root with its scaling.
+// an ulp, in half the instructions of the correctly rounded root with its scaling.  The steps turn infinity
+// into a NaN, which the maximum with 1e-200 x, far below the root of every finite x, turns back.
 __device__ __forceinline__ double sqrt_nr(double x) {
   const double z = max_num(x, 1e-280);
   const double y = __builtin_amdgcn_rsq(z);
@@ -572,7 +573,7 @@ __device__ __forceinline__ double sqrt_nr(double x) {
   g = __fma_rn(g, r, g);
   h = __fma_rn(h, r, h);
   r = __fma_rn(-g, g, z);
-  return __fma_rn(r, h, g);
+  return max_num(__fma_rn(r, h, g), 1e-200 * z);
 }
 
 // Largest |u| + c over states given by u2 = |u|^2 and c2 = gamma p / rho (both float64), for the global
@@ -869,7 +870,7 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
         }
         smax = S.get();
       }
-      if (!isfinite(smax)) {  // fmax-based reductions would drop a NaN: report it here
+      if (!isfinite(smax)) {  // |u|^2 or gamma p / rho of a point beyond the range of the arithmetic
         report(v.err, E_NONFINITE, i);
         smax = INFINITY;
       }

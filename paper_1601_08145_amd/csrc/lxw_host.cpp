@@ -408,6 +408,15 @@ void fill_tab(RefTab<E, R>& T) {
   }
   for (int p = 0; p < E::NP; ++p)
     for (int d = 0; d < E::DIM; ++d) T.xr[p][d] = R(pts[p * E::DIM + d]);
+  if constexpr (E::kind == LXW_QUAD)
+    for (int p = 0; p < E::NP; ++p) {
+      const bool y = p >= E::NI && (p - E::NI) / E::NQE % 2 == 1;  // on edges 1 and 3, which run along y
+      const double xi[2] = {pts[p * 2 + (y ? 0 : 1)], pts[p * 2 + (y ? 1 : 0)]};  // across, along
+      for (int d = 0; d < 2; ++d) {
+        T.leg[p][2 * d] = R(std::sqrt(3.0) * xi[d]);
+        T.leg[p][2 * d + 1] = R(0.5 * std::sqrt(5.0) * (3.0 * xi[d] * xi[d] - 1.0));
+      }
+    }
   if constexpr (E::DIM == 3) {
     const double o[3] = {0.0, 0.0, 0.0};
     for (int l = 0; l < E::ML; ++l) {

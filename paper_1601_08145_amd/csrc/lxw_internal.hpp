@@ -59,6 +59,8 @@ struct RefTab {
   R ephi[E::K][E::NQE][E::ML];     // (1/2) omega_j phi_l(x_kj): edge term of the update
   R om[E::NQE];                    // Gauss-Legendre weights on [-1, 1]
   R xr[E::NP][E::DIM];             // reference coordinates of the points
+  R leg[E::kind == 1 ? E::NP : 1][4];  // square: the Legendre values L_1, L_2 of a point's coordinate across its
+                                   // line of points (rows, edges) and along it
   R dphi0[E::DIM][E::ML];          // reference gradient at the reference origin
   R d2c[E::ND2][E::ML];            // reference second derivatives at the origin (constant for
                                    // complete P2 on the line and the triangle)

@@ -520,9 +520,8 @@ __device__ __forceinline__ void atomic_max_per_mesh(Scalars* sc, int mid, double
 //           (training data for the learned indicator).
 // With a learned indicator, elements it clears (ind_flag 0) skip the shock-capturing limiter in
 // modes 0 and 1; the positivity limiter is never skipped.
-// All limiter arithmetic is float64 on the stored state, evaluated as q_bar + theta sum_l Q_l phi_l,
-// the same expression k_elem uses for its point states, so the positivity the limiter establishes
-// holds for the states the time-averaged flux is built from.
+// All limiter arithmetic is float64 on the stored state, its point states those of k_elem (point_dev, limited),
+// so the positivity the limiter establishes holds for the states the time-averaged flux is built from.
 // ---------------------------------------------------------------------------------------------
 // 1/x in float64 for the limiter passes of k_pre (x a positive normal number: a point density
 // checked > 0 first, or a cell average >= eps0): the hardware estimate (about 2^-23 relative) and
@@ -607,13 +606,60 @@ __device__ __forceinline__ void add_speed(Speed<R>& S, const double* q, double g
   S.add(u2, gam * pressure_r<DIM>(q, r, gam) * r);
 }
 
-// deviation of variable c from the cell average at point p, float64, from the stored modes
-template <class E, class R>
-__device__ __forceinline__ double point_dev(const RefTab<E, double>& T, const R (&Qh)[E::V][E::ML - 1], int p, int c) {
-  double acc = 0.0;
+// Point states in float64, q_bar + theta d with the deviation d = sum_l Q_l phi_l of the unlimited modes.  k_pre's
+// limiters and k_elem both evaluate them by these functions, whose every operation is written out, so that the
+// states F_T is built from are those the moment limiter made positive, to the last bit.  The factor and the
+// average stay outside the sum: where theta brings a density down to eps0, only theta's own few roundings
+// (about 4 2^-53 rho_bar) are left in it.  With monomial coefficients scaled by theta and the average among
+// them, densities of 1e-12 came out negative beside an average of 100 (P3), of 1000 (P2 and the square).
+__device__ __forceinline__ double limited(double qb, double th, double dev) { return __fma_rn(th, dev, qb); }
+// mode(l), l = 1 .. ML - 1: the modes
+template <int ML, class M>
+__device__ __forceinline__ double deviation(M&& mode, const double (&phi)[ML]) {
+  double d = mul_rn(mode(1), phi[1]);
 #pragma unroll
-  for (int l = 1; l < E::ML; ++l) acc += double(Qh[c][l - 1]) * T.phi[p][l];
-  return acc;
+  for (int l = 2; l < ML; ++l) d = __fma_rn(mode(l), phi[l], d);
+  return d;
+}
+// The square's modes along a line of points: mode(m, j) has degree m along it and j across, leg holds L_1 and L_2 of
+// the line's coordinate across; d = U_0 + U_1 L_1 + U_2 L_2 of the coordinate along it.
+template <class M>
+__device__ __forceinline__ void line_modes(M&& mode, const double* leg, double (&U)[3]) {
+  U[0] = __fma_rn(mode(0, 2), leg[1], mul_rn(mode(0, 1), leg[0]));
+#pragma unroll
+  for (int m = 1; m < 3; ++m) U[m] = __fma_rn(mode(m, 2), leg[1], __fma_rn(mode(m, 1), leg[0], mode(m, 0)));
+}
+__device__ __forceinline__ double line_deviation(const double (&U)[3], const double* leg) {
+  return __fma_rn(leg[1], U[2], __fma_rn(leg[0], U[1], U[0]));
+}
+// mode numbers of the square: QUAD_AT[i][j] = that of L_i(x) L_j(y)
+constexpr int QUAD_AT[3][3] = {{0, 2, 5}, {1, 4, 7}, {3, 6, 8}};
+
+// whether a point's line runs along y (edges 1 and 3)
+template <class E>
+__device__ __forceinline__ bool along_y(int p) { return p >= E::NI && ((p - E::NI) / E::NQE) % 2 == 1; }
+// deviation of variable c from the cell average at point p, from the stored modes (square: y = along_y(p))
+template <class E, class R>
+__device__ __forceinline__ double point_dev(const RefTab<E, double>& T, const R (&Qh)[E::V][E::ML - 1], int p, bool y, int c) {
+  if constexpr (E::kind == ElQuad::kind) {
+    double U[3];
+    line_modes([&](int m, int j) { return double(Qh[c][(y ? QUAD_AT[j][m] : QUAD_AT[m][j]) - 1]); }, T.leg[p], U);
+    return line_deviation(U, T.leg[p] + 2);
+  } else {
+    return deviation<E::ML>([&](int l) { return double(Qh[c][l - 1]); }, T.phi[p]);
+  }
+}
+// the state q_bar + theta d at point p (one branch for all variables of the square)
+template <class E, class R>
+__device__ __forceinline__ void point_state(const RefTab<E, double>& T, const double (&qb)[E::V],
+                                            const R (&Qh)[E::V][E::ML - 1], double th, int p, double (&q)[E::V]) {
+  auto form = [&](auto y) {
+#pragma unroll
+    for (int c = 0; c < E::V; ++c) q[c] = limited(qb[c], th, point_dev<E, R>(T, Qh, p, y.value, c));
+  };
+  if constexpr (E::kind == ElQuad::kind)
+    if (along_y<E>(p)) return form(std::true_type{});
+  form(std::false_type{});
 }
 
 // Exact variant of the moment limiter's pressure step (Sec. 3.1; the paper notes the optimal factor
@@ -725,8 +771,7 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
 #pragma unroll 1
       for (int p = 0; p < NP; ++p) {
         double q[V];
-#pragma unroll
-        for (int c = 0; c < V; ++c) q[c] = qb[c] + point_dev<E, R>(T, Qh, p, c);
+        point_state<E, R>(T, qb, Qh, 1.0, p, q);
         wmax[0] = max_num(wmax[0], q[0]);
         wmin[0] = min_num(wmin[0], q[0]);
         if (q[0] > 0.0) {
@@ -829,7 +874,7 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
         } else {
 #pragma unroll
           for (int p = 0; p < NP; ++p) {
-            const double rm = qb[0] + th_sc * point_dev<E, R>(T, Qh, p, 0);
+            const double rm = limited(qb[0], th_sc, point_dev<E, R>(T, Qh, p, along_y<E>(p), 0));
             if (rm < eps0) thr = fmin(thr, (qb[0] - eps0) / (qb[0] - rm));
           }
         }
@@ -840,8 +885,7 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
           double q[V];
-#pragma unroll
-          for (int c = 0; c < V; ++c) q[c] = qb[c] + ts * point_dev<E, R>(T, Qh, p, c);
+          point_state<E, R>(T, qb, Qh, ts, p, q);
           const double pt = pressure_r<DIM>(q, rcp_nr(q[0]), gam);
           if (pt < epsp) {
             if (kExact) th = fmin(th, thr * exact_segment<DIM>(qb, q, epsp, gam, (pb - epsp) / (pb - pt)));
@@ -863,8 +907,7 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
 #pragma unroll
           for (int p = 0; p < NP; ++p) {
             double q[V];
-#pragma unroll
-            for (int c = 0; c < V; ++c) q[c] = qb[c] + tt * point_dev<E, R>(T, Qh, p, c);
+            point_state<E, R>(T, qb, Qh, tt, p, q);
             add_speed<DIM, R>(S, q, gam);
           }
         }
@@ -1012,16 +1055,16 @@ __device__ __forceinline__ R here(R x) {
 
 // P2 on triangles and tetrahedra (affine elements): everything at a point comes from polynomial
 // coefficients formed once per element.
-//  * The limited state q_bar + theta sum_l Q_l phi_l as monomial coefficients a in float64 (the basis in
-//    monomials is the table cm), evaluated by Horner's rule and rounded to the bulk type; on an edge of a
-//    triangle it is a quadratic in one variable.  Interior states serve twice (projection and F_T): they
-//    wait in LDS between the two where they fit.
-//  * grad q in physical coordinates as an affine function of the reference point, G0 + Hx . xi.
+//  * The limited state q_bar + theta sum_l Q_l phi_l in float64 from the modes, as the limiter has it, rounded
+//    to the bulk type.  Interior states serve twice (projection and F_T): they wait in LDS between the two
+//    where they fit.
+//  * grad q in physical coordinates as an affine function of the reference point, G0 + Hx . xi, from the
+//    modes' monomial coefficients (the basis in monomials is the table cm).
 //  * div F^h and its gradient: Step 1's projection composed with div (and its gradient) at the origin is
 //    a fixed table (kd0, kd1), so F^h is never formed; the mass flux M is its own projection, so its
 //    divergence comes from grad q.
-// The edges come before the volume term: the coefficients a are dead by the time its accumulators live,
-// and the modes are read again for the update.
+// The edges come before the volume term: the modes in float64 are dead by the time its accumulators live,
+// and are read again for the update.
 //
 // Bound by instruction issue: 3,840 VALU instructions per wavefront of float32 triangles (5,870 with
 // Jacobian and Hessian products, states evaluated mode by mode and every V_l accumulated at every point):
@@ -1059,23 +1102,15 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
   extern __shared__ __align__(16) unsigned char dyn[];
   R* sq = reinterpret_cast<R*>(dyn);
 
-  // monomial coefficients of the limited state
+  // the stored modes (before the limiter) and the limiter factor theta of this step
   const double th = at(v.theta, i);
-  double a[V][ML];
+  double qb[V], Q[V][ML - 1];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
-    const double qb = v.Qbar[(size_t)i * V + c];
-    v.Qold[(size_t)i * V + c] = qb;  // the step's averages, for the edge fluxes (k_flux, k_update)
-    double Q[ML - 1];
+    qb[c] = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
-    for (int l = 1; l < ML; ++l) Q[l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
-#pragma unroll
-    for (int m = 0; m < ML; ++m) {
-      double acc = 0.0;
-#pragma unroll
-      for (int l = (m > 1 ? m : 1); l < ML; ++l) acc += Q[l - 1] * TD.cm[l][m];
-      a[c][m] = m == 0 ? qb + th * acc : th * acc;
-    }
+    for (int l = 1; l < ML; ++l) Q[c][l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
   }
   // the map's gradient scaled for q's gradients (dt/3) and for D (c1 = dt/2), see Pt2
   R JG[DIM][DIM], JC[DIM][DIM];
@@ -1089,33 +1124,31 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
     }
 
   auto state_at = [&](int p, R* q) {
-    const double x = TD.xr[p][0], y = TD.xr[p][1];
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      const double* A = a[c];
-      if constexpr (DIM == 2) {
-        const double px = A[1] + x * A[3] + y * A[4], py = A[2] + y * A[5];
-        q[c] = R(A[0] + x * px + y * py);
-      } else {
-        const double z = TD.xr[p][2];
-        const double px = A[1] + x * A[4] + y * A[5] + z * A[6], py = A[2] + y * A[7] + z * A[8], pz = A[3] + z * A[9];
-        q[c] = R(A[0] + x * px + y * py + z * pz);
-      }
-    }
+    for (int c = 0; c < V; ++c)
+      q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return Q[c][l - 1]; }, TD.phi[p])));
   };
 
   // (dt/3) grad q at the reference point xi: G0[d][c] + sum_b Hx[b][d][c] xi_b
   R G0[DIM][V], Hx[DIM][DIM][V];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
+    double a[ML];  // monomial coefficients of theta sum_l Q_l phi_l (without the constant)
+#pragma unroll
+    for (int m = 1; m < ML; ++m) {
+      double acc = 0.0;
+#pragma unroll
+      for (int l = m; l < ML; ++l) acc += Q[c][l - 1] * TD.cm[l][m];
+      a[m] = th * acc;
+    }
     R g[DIM], h[DIM][DIM];  // reference gradient at the origin and (symmetric) Hessian
     if constexpr (DIM == 2) {
-      g[0] = R(a[c][1]); g[1] = R(a[c][2]);
-      h[0][0] = R(2) * R(a[c][3]); h[0][1] = h[1][0] = R(a[c][4]); h[1][1] = R(2) * R(a[c][5]);
+      g[0] = R(a[1]); g[1] = R(a[2]);
+      h[0][0] = R(2) * R(a[3]); h[0][1] = h[1][0] = R(a[4]); h[1][1] = R(2) * R(a[5]);
     } else {
-      g[0] = R(a[c][1]); g[1] = R(a[c][2]); g[DIM - 1] = R(a[c][3]);
-      h[0][0] = R(2) * R(a[c][4]); h[0][1] = h[1][0] = R(a[c][5]); h[0][DIM - 1] = h[DIM - 1][0] = R(a[c][6 % ML]);
-      h[1][1] = R(2) * R(a[c][7 % ML]); h[1][DIM - 1] = h[DIM - 1][1] = R(a[c][8 % ML]); h[DIM - 1][DIM - 1] = R(2) * R(a[c][9 % ML]);
+      g[0] = R(a[1]); g[1] = R(a[2]); g[DIM - 1] = R(a[3]);
+      h[0][0] = R(2) * R(a[4]); h[0][1] = h[1][0] = R(a[5]); h[0][DIM - 1] = h[DIM - 1][0] = R(a[6 % ML]);
+      h[1][1] = R(2) * R(a[7 % ML]); h[1][DIM - 1] = h[DIM - 1][1] = R(a[8 % ML]); h[DIM - 1][DIM - 1] = R(2) * R(a[9 % ML]);
     }
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
@@ -1253,8 +1286,8 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
       slots[k] = at(v.eslot + (size_t)k * N, i);
       load_normal(k, nk[k]);
     }
-    // along edge k the reference point is (t, 0), (1 - t, t), (0, t), t one of its coordinates; edge 1,
-    // whose coefficients are sums, last: the others' are the element's own
+    // along edge k the reference point is (t, 0), (1 - t, t), (0, t), t one of its coordinates: gradients and D are
+    // affine in t; edge 1, whose coefficients are sums, last: the others' are the element's own
 #pragma unroll
     for (int x = 0; x < K; ++x) {
       const int k = x == 0 ? 0 : 3 - x;
@@ -1262,14 +1295,9 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
       R* n = nk[k];
       R len2;
       const R hs = half_speed(n, len2);
-      double e0[V], e1[V], e2[V];
       R g0[DIM][V], g1[DIM][V], d0[V], d1[V];
 #pragma unroll
       for (int c = 0; c < V; ++c) {
-        const double* A = a[c];
-        e0[c] = k == 1 ? A[0] + A[1] + A[3] : A[0];
-        e1[c] = k == 0 ? A[1] : (k == 1 ? A[2] - A[1] - 2.0 * A[3] + A[4] : A[2]);
-        e2[c] = k == 0 ? A[3] : (k == 1 ? A[3] - A[4] + A[5] : A[5]);
 #pragma unroll
         for (int d = 0; d < DIM; ++d) {
           g0[d][c] = k == 1 ? G0[d][c] + Hx[0][d][c] : G0[d][c];
@@ -1281,12 +1309,11 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
 #pragma unroll 1
       for (int jl = 0; jl < NQE; ++jl) {
         const int p = NI + k * NQE + jl;
-        const double td = TD.xr[p][k == 0 ? 0 : 1];
         const R t = T.xr[p][k == 0 ? 0 : 1];
         R q[V], gq[DIM][V], D[V];
+        state_at(p, q);
 #pragma unroll
         for (int c = 0; c < V; ++c) {
-          q[c] = R(e0[c] + td * (e1[c] + td * e2[c]));
 #pragma unroll
           for (int d = 0; d < DIM; ++d) gq[d][c] = g0[d][c] + g1[d][c] * t;
           D[c] = d0[c] + d1[c] * t;
@@ -1473,16 +1500,11 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
   // scaled for q's gradients and for F^h (D comes out as c1 D, its gradient as c2 grad D), see Pt2
   const R sg3 = dt * R(1.0 / 3.0), sc1 = R(0.5) * dt;
 
-  // point state of the limited polynomial in float64, q_bar + theta sum_l Q_l phi_l (the
-  // expression the moment limiter made positive), then rounded to the bulk precision
+  // point state of the limited polynomial
   auto state_at = [&](int p, R* q) {
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int l = 1; l < ML; ++l) acc += double(Qr[c][l - 1]) * TD.phi[p][l];
-      q[c] = R(qb[c] + th * acc);
-    }
+    for (int c = 0; c < V; ++c)
+      q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return double(Qr[c][l - 1]); }, TD.phi[p])));
   };
 
   // grad q and div F^h are linear and their derivatives constant, so they are formed once per element from
@@ -1672,7 +1694,6 @@ template <class E, class R>
 __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = 4, ML = 9, NQE = 3;
   constexpr int MI[9] = {0, 1, 0, 2, 1, 0, 2, 1, 2}, MJ[9] = {0, 0, 1, 0, 1, 2, 1, 2, 2};  // mode l = L_MI(x) L_MJ(y)
-  constexpr int AT[3][3] = {{0, 2, 5}, {1, 4, 7}, {3, 6, 8}};
   constexpr double r3 = 1.7320508075688772935, r5 = 2.2360679774997896964;  // L_1 = r3 x, L_2 = r5 (3 x^2 - 1) / 2
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
@@ -1717,21 +1738,13 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
     for (int c = 0; c < V; ++c) { put(2 * c, Qr[c]); put(2 * c + 1, Qr[c] + 4); }
   const R JG[2] = {dt * R(1.0 / 3.0) * Ji[0], dt * R(1.0 / 3.0) * Ji[1]};  // scaled for q's gradients, see Pt2
 
-  // q on the line where the cross coordinate is x0: U_0 + U_1 L_1 + U_2 L_2, limited, in float64
-  // (Y: the line runs along y)
-  auto state_line = [&](auto Y, double x0, int lane, double (&U)[V][3]) {
-    const double l1 = r3 * x0, l2 = 0.5 * r5 * (3.0 * x0 * x0 - 1.0);
+  // the deviation's modes U on the line through point p (Y: the line runs along y)
+  auto state_line = [&](auto Y, int p, int lane, double (&U)[V][3]) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       R Qc[ML - 1];
       modes(lane, c, Qc);
-#pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        auto Q = [&](int j) { return double(Qc[(Y.value ? AT[j][m] : AT[m][j]) - 1]); };
-        double t = Q(1) * l1 + Q(2) * l2;
-        if (m) t += Q(0);
-        U[c][m] = m ? th * t : qb[c] + th * t;
-      }
+      line_modes([&](int m, int j) { return double(Qc[(Y.value ? QUAD_AT[j][m] : QUAD_AT[m][j]) - 1]); }, TD.leg[p], U[c]);
     }
   };
 
@@ -1751,23 +1764,21 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
     for (int m = 0; m < 2; ++m)
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        Fx[0][m][j] = jc[0] * (thR * Qr[1][AT[m + 1][j] - 1]);
-        Fy[0][m][j] = jc[1] * (thR * Qr[2][AT[j][m + 1] - 1]);
+        Fx[0][m][j] = jc[0] * (thR * Qr[1][QUAD_AT[m + 1][j] - 1]);
+        Fy[0][m][j] = jc[1] * (thR * Qr[2][QUAD_AT[j][m + 1] - 1]);
 #pragma unroll
         for (int c = 1; c < V; ++c) Fx[c][m][j] = Fy[c][m][j] = R(0);
       }
 #pragma unroll 1
     for (int row = 0; row < 3; ++row) {
       double U[V][3];
-      state_line(std::false_type{}, TD.xr[3 * row][1], lds ? hidden_lane() : 0, U);
+      state_line(std::false_type{}, 3 * row, lds ? hidden_lane() : 0, U);
 #pragma unroll 1
       for (int n = 0; n < 3; ++n) {
         const int m = 3 * row + n;
-        const double x = TD.xr[n][0];
-        const double l1 = r3 * x, l2 = 0.5 * r5 * (3.0 * x * x - 1.0);
         R q[V], F[2][V];
 #pragma unroll
-        for (int c = 0; c < V; ++c) q[c] = R(U[c][0] + l1 * U[c][1] + l2 * U[c][2]);
+        for (int c = 0; c < V; ++c) q[c] = R(limited(qb[c], th, line_deviation(U[c], TD.leg[m] + 2)));
         const St<2, R> s = base_state<2, R>(q, gm1);
 #pragma unroll
         for (int d = 0; d < 2; ++d) flux<2, R>(s, d, F[d]);
@@ -1778,8 +1789,8 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
           for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
-              Fx[c][a][j] += T.wphi[m][AT[a + 1][j]] * fx;
-              Fy[c][a][j] += T.wphi[m][AT[j][a + 1]] * fy;
+              Fx[c][a][j] += T.wphi[m][QUAD_AT[a + 1][j]] * fx;
+              Fy[c][a][j] += T.wphi[m][QUAD_AT[j][a + 1]] * fy;
             }
         }
       }
@@ -1803,13 +1814,13 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
     }
   }
 
-  // Sec. 2.3 Step 2 at the three points of a line: body(n, q, qt, qtt, s), n the point's place on the line
-  auto line = [&](auto Y, const double x0, auto&& body) {
+  // Sec. 2.3 Step 2 at the three points of a line, p0 .. p0 + 2: body(n, q, qt, qtt, s), n the point's place
+  auto line = [&](auto Y, const int p0, auto&& body) {
     constexpr int al = Y.value ? 1 : 0, cr = 1 - al;  // directions along and across
-    const R t0 = R(x0);
+    const R t0 = T.xr[p0][cr];
     double U[V][3];
     const int lane = lds ? hidden_lane() : 0;
-    state_line(Y, x0, lane, U);
+    state_line(Y, p0, lane, U);
     R ga[V][2], gc[V][3], e[V][3], ea[V][2], ec[V][3];
     const R c1 = JG[cr] * thR * R(r3), c2 = JG[cr] * thR * R(3.0 * r5) * t0;
 #pragma unroll
@@ -1817,11 +1828,11 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
       R Qc[ML - 1], dc[8];
       modes(lane, c, Qc);
       monomials(lane, c, dc);
-      ga[c][0] = JG[al] * R(r3) * R(U[c][1]);
-      ga[c][1] = JG[al] * R(3.0 * r5) * R(U[c][2]);
+      ga[c][0] = JG[al] * R(r3) * R(th * U[c][1]);
+      ga[c][1] = JG[al] * R(3.0 * r5) * R(th * U[c][2]);
 #pragma unroll
       for (int m = 0; m < 3; ++m) {
-        auto Q = [&](int j) { return Qc[(Y.value ? AT[j][m] : AT[m][j]) - 1]; };
+        auto Q = [&](int j) { return Qc[(Y.value ? QUAD_AT[j][m] : QUAD_AT[m][j]) - 1]; };
         auto d = [&](int j) { return dc[Y.value ? 3 * j + m : 3 * m + j]; };
         gc[c][m] = c1 * Q(1) + c2 * Q(2);
         e[c][m] = m == 2 ? d(0) + t0 * d(1) : d(0) + t0 * (d(1) + t0 * d(2));
@@ -1832,13 +1843,12 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
     }
 #pragma unroll 1
     for (int n = 0; n < 3; ++n) {
-      const double xd = TD.xr[n][0];
-      const double p1 = r3 * xd, p2 = 0.5 * r5 * (3.0 * xd * xd - 1.0);
-      const R x = R(xd), l1 = R(p1), l2 = R(p2);
+      const int p = p0 + n;
+      const R x = T.xr[p][al], l1 = T.leg[p][2], l2 = T.leg[p][3];
       R q[V], qt[V], qtt[V], gq[2][V], gD[2][V];
 #pragma unroll
       for (int c = 0; c < V; ++c) {
-        q[c] = R(U[c][0] + p1 * U[c][1] + p2 * U[c][2]);
+        q[c] = R(limited(qb[c], th, line_deviation(U[c], TD.leg[p] + 2)));
         qt[c] = -(e[c][0] + x * (e[c][1] + x * e[c][2]));
         gq[al][c] = ga[c][0] + x * ga[c][1];
         gq[cr][c] = gc[c][0] + l1 * gc[c][1] + l2 * gc[c][2];
@@ -1860,7 +1870,7 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
       for (int l = 0; l < ML - 1; ++l) vol[c][l] = R(0);
 #pragma unroll 1
     for (int row = 0; row < 3; ++row)
-      line(std::false_type{}, TD.xr[3 * row][1], [&](int n, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
+      line(std::false_type{}, 3 * row, [&](int n, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
         const int m = 3 * row + n;
         R FT[2][V];
         ft2<2, R>(s, q, qt, qtt, gm1, FT);
@@ -1902,7 +1912,6 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
 #pragma unroll 1
     for (int hi = 0; hi < 2; ++hi) {
       const int k = Y.value ? 3 - 2 * hi : 2 * hi;
-      const bool rev = k >= 2;
       const int slot = at(v.eslot + (size_t)k * N, i);
       const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
       R n[2], len2 = R(0);
@@ -1910,8 +1919,8 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
       for (int d = 0; d < 2; ++d) { n[d] = at(v.nout + (size_t)(k * 2 + d) * N, i); len2 += n[d] * n[d]; }
       // s |n_e| / 2: both elements of an edge hold the same normal up to sign, so they form it alike
       const R hs = R(hs0 * double(sqrt(len2)));
-      line(Y, hi ? 1.0 : -1.0, [&](int np, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
-        const int jj = (side != 0) == rev ? np : NQE - 1 - np;  // point order of i_e along the edge
+      line(Y, 9 + 3 * k, [&](int jl, const R* q, const R* qt, const R* qtt, const Pt2<2, R>& s) {
+        const int jj = side ? NQE - 1 - jl : jl;  // point order of i_e along the edge
         R fn[V], b[V];
         ftn2<2, R>(s, q, qt, qtt, n, gm1, fn);
 #pragma unroll
@@ -2171,25 +2180,21 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
   extern __shared__ __align__(16) unsigned char dyn[];
   R* sq = reinterpret_cast<R*>(dyn);
 
-  // monomial coefficients of the limited state (float64), and from them the Taylor coefficients at the
-  // reference origin: gradient, Hessian and third derivatives
+  // the stored modes (before the limiter) and the limiter factor theta of this step; point states
   const double th = at(v.theta, i);
-  double a[V][ML];
+  double qb[V], Q[V][ML - 1];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
-    const double qb = v.Qbar[(size_t)i * V + c];
-    v.Qold[(size_t)i * V + c] = qb;  // the step's averages, for the edge fluxes (k_flux, k_update)
-    double Q[ML - 1];
+    qb[c] = v.Qbar[(size_t)i * V + c];
+    v.Qold[(size_t)i * V + c] = qb[c];  // the step's averages, for the edge fluxes (k_flux, k_update)
 #pragma unroll
-    for (int l = 1; l < ML; ++l) Q[l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
-#pragma unroll
-    for (int m = 0; m < ML; ++m) {
-      double acc = 0.0;
-#pragma unroll
-      for (int l = (m > 1 ? m : 1); l < ML; ++l) acc += Q[l - 1] * TD.cm[l][m];
-      a[c][m] = m == 0 ? qb + th * acc : th * acc;
-    }
+    for (int l = 1; l < ML; ++l) Q[c][l - 1] = double(at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i));
   }
+  auto state_at = [&](int p, R* q) {
+#pragma unroll
+    for (int c = 0; c < V; ++c)
+      q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return Q[c][l - 1]; }, TD.phi[p])));
+  };
   R JG[2][2], JC[2][2];  // dt/3 and -dt/2 times the map's gradient
 #pragma unroll
   for (int x = 0; x < 2; ++x)
@@ -2199,12 +2204,21 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
       JG[x][d] = dt * R(1.0 / 3.0) * J;
       JC[x][d] = R(-0.5) * dt * J;
     }
+  // Taylor coefficients at the reference origin (gradient, Hessian, third derivatives) from the monomial ones
   R g0[2][V], h0[3][V], t3[4][V];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
-    g0[0][c] = R(a[c][1]); g0[1][c] = R(a[c][2]);
-    h0[0][c] = R(2) * R(a[c][3]); h0[1][c] = R(a[c][4]); h0[2][c] = R(2) * R(a[c][5]);
-    t3[0][c] = R(6) * R(a[c][6]); t3[1][c] = R(2) * R(a[c][7]); t3[2][c] = R(2) * R(a[c][8]); t3[3][c] = R(6) * R(a[c][9]);
+    double a[ML];
+#pragma unroll
+    for (int m = 1; m < ML; ++m) {
+      double acc = 0.0;
+#pragma unroll
+      for (int l = m; l < ML; ++l) acc += Q[c][l - 1] * TD.cm[l][m];
+      a[m] = th * acc;
+    }
+    g0[0][c] = R(a[1]); g0[1][c] = R(a[2]);
+    h0[0][c] = R(2) * R(a[3]); h0[1][c] = R(a[4]); h0[2][c] = R(2) * R(a[5]);
+    t3[0][c] = R(6) * R(a[6]); t3[1][c] = R(2) * R(a[7]); t3[2][c] = R(2) * R(a[8]); t3[3][c] = R(6) * R(a[9]);
   }
   // Sec. 2.3 Step 1 composed with -c1 div and its derivatives at the origin (kd0, kd1, kd2): the Taylor
   // coefficients of q1, a quadratic; M is its own projection, so rho's come from the gradients of M
@@ -2230,14 +2244,8 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
     }
 #pragma unroll 1
   for (int m = 0; m < NI; ++m) {
-    const double x = TD.xr[m][0], y = TD.xr[m][1];
     R q[V];
-#pragma unroll
-    for (int c = 0; c < V; ++c) {
-      const double* A = a[c];
-      const double p2 = A[5] + x * A[8] + y * A[9], p1 = A[2] + x * (A[4] + x * A[7]);
-      q[c] = R(A[0] + x * (A[1] + x * (A[3] + x * A[6])) + y * (p1 + y * p2));
-    }
+    state_at(m, q);
     store_rec<R, V>(sq + ((size_t)m * blockDim.x + threadIdx.x) * V, q);
     const St<2, R> s = base_state<2, R>(q, gm1);
     R F[2][V];
@@ -2260,7 +2268,7 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
   for (int e = 0; e < 2; ++e)
     r2e[e] = -(JG[0][0] * h1[e][1] + JG[0][1] * h1[e][2] + JG[1][0] * h1[1 + e][1] + JG[1][1] * h1[1 + e][2]);
 
-  // edges (before the volume term: its accumulators and the coefficients a are then not live together)
+  // edges (before the volume term: its accumulators and the modes are then not live together)
   {
     const double hs0 = 0.5 * D.s;
     int slots[K];
@@ -2287,17 +2295,11 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
 #pragma unroll 1
       for (int jl = 0; jl < NQE; ++jl) {
         const int p = NI + k * NQE + jl;
-        const double td = TD.xr[p][k == 0 ? 0 : 1];
         const R tt = T.xr[p][k == 0 ? 0 : 1];
         R q[V], q1[V], gq[2][V], g1[2][V], hq[3][V];
+        state_at(p, q);
 #pragma unroll
         for (int c = 0; c < V; ++c) {
-          const double* A = a[c];
-          const double e0 = k == 1 ? A[0] + A[1] + A[3] + A[6] : A[0];
-          const double e1 = k == 0 ? A[1] : (k == 2 ? A[2] : A[2] - A[1] - 2.0 * A[3] + A[4] - 3.0 * A[6] + A[7]);
-          const double e2 = k == 0 ? A[3] : (k == 2 ? A[5] : A[3] - A[4] + A[5] + 3.0 * A[6] - 2.0 * A[7] + A[8]);
-          const double e3 = k == 0 ? A[6] : (k == 2 ? A[9] : A[7] - A[6] - A[8] + A[9]);
-          q[c] = R(e0 + td * (e1 + td * (e2 + td * e3)));
 #pragma unroll
           for (int w = 0; w < 2; ++w) {
             const R l0 = k == 1 ? g0[w][c] + h0[w][c] + R(0.5) * t3[w][c] : g0[w][c];
@@ -2489,14 +2491,11 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
 #pragma unroll
     for (int d = 0; d < DIM; ++d) Ji[a][d] = at(v.Jinv + (size_t)(a * DIM + d) * N, i);
 
+  // point state of the limited polynomial in float64, then rounded to the bulk precision
   auto state_at = [&](int p, R* q) {
 #pragma unroll
-    for (int c = 0; c < V; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int l = 1; l < ML; ++l) acc += double(Qr[c][l - 1]) * TD.phi[p][l];
-      q[c] = R(qb[c] + th * acc);
-    }
+    for (int c = 0; c < V; ++c)
+      q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return double(Qr[c][l - 1]); }, TD.phi[p])));
   };
   // physical second derivatives from the reference ones (xx[, xy, yy] at index a + b)
   auto map2 = [&](const R* hr, R out[DIM][DIM]) {

@@ -275,6 +275,7 @@ lxw_status lxw_sync(lxw_solver* s);
  *   LXW_STAGE_SDT      {s, dt} [2]
  * Per-kernel timing: lxw_set_timing(s, 1) records HIP events around every kernel of later steps;
  * lxw_kernel_times returns, per kernel id (LXW_K_*), the summed milliseconds and launch counts.
+ * LXW_K_DT runs on single meshes of more than 512 workgroups of LXW_K_PRE only.
  * LXW_K_EDGE is the kernel of the edge fluxes, the flux limiter and the higher moments' edge terms (one
  * lane per element); LXW_K_FLIM launches nothing (its work is in LXW_K_EDGE).
  * A step ends inside the LXW_K_UPDATE kernel; LXW_K_FINAL counts only the kernel that closes a

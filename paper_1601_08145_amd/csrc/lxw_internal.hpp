@@ -238,6 +238,13 @@ inline bool tunable(int k) { return k == K_PRE || k == K_ELEM || k == K_FLUX || 
 // Number of workgroups of an element kernel: padded to a multiple of 8 (one contiguous
 // range of workgroups per XCD).
 inline int egrid_blocks(int n, int bs) { return ((n + bs - 1) / bs + 7) / 8 * 8; }
+// Workgroups of k_pre up to which a single mesh's wave speed is one atomic maximum per workgroup, as a
+// batch's is (one per wavefront and mesh); above it the workgroups' maxima go to an array that
+// k_dt reduces.  One launch less is 4 to 5 us of a step (122,258 triangles, 480 workgroups: 71.6 -> 66.6 us
+// with k_pre's shorter point pass); the atomics queue on one address at some 8 ns each, as long as a launch
+// at 512 workgroups.
+constexpr int DIRECT_BLOCKS = 512;
+inline bool dt_kernel(int n, bool batch, const LaunchCfg& c) { return !batch && egrid_blocks(n, c.bs[0]) > DIRECT_BLOCKS; }
 
 template <class E, class R>
 hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_t st, int n_mesh, int mode);

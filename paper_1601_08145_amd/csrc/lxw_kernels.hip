@@ -933,13 +933,6 @@ __device__ __forceinline__ double pre_elem(const View<R>& v, const int i, const 
   return smax;
 }
 
-// Workgroups of k_pre up to which a single mesh's wave speed is one atomic maximum per workgroup, as a
-// batch's is (one per wavefront and mesh); above it the workgroups' maxima go to an array that
-// k_dt reduces.  One launch less is 4 to 5 us of a step (122,258 triangles, 480 workgroups: 71.6 -> 66.6 us
-// with the shorter point pass below); the atomics queue on one address at some 8 ns each, as long as a launch
-// at 512 workgroups.
-constexpr int DIRECT_BLOCKS = 512;
-
 // Element i of k_pre (i may be past the last element: every lane of a wavefront takes part in the
 // wave-speed reduction).
 template <class E, class R, int mode>
@@ -3457,7 +3450,7 @@ hipError_t launch(KernelId k, const View<R>& v, const LaunchCfg& cfg, hipStream_
     case K_IND:
       return hipErrorInvalidValue;  // launched through launch_indicator
     case K_DT:
-      if (!v.mesh_of && egrid_blocks(v.N, cfg.bs[K_PRE]) > DIRECT_BLOCKS)
+      if (dt_kernel(v.N, v.mesh_of != nullptr, cfg))
         hipLaunchKernelGGL(k_dt_single, dim3(1), dim3(1024), 0, st, v.sc, v.spart, egrid_blocks(v.N, cfg.bs[K_PRE]));
       break;
     case K_ELEM:

@@ -1,0 +1,47 @@
+"""The wave speed's reduction and the launch shapes: the kernel that forms the maximum of many workgroups is
+counted where it is launched, changes no bit, and its time counts when the size of k_pre's workgroups, which
+decides whether it is launched, is tuned."""
+import numpy as np
+import pytest
+
+from paper_1601_08145_amd import inputs as I
+from paper_1601_08145_amd import lxw as L
+
+pytestmark = pytest.mark.gpu
+
+
+def solver(n, precision):
+    mesh = L.Mesh.cart(n, n, 0.0, 1.0, 0.0, 1.0, [0, 0, 0, 0])
+    S = L.Solver(mesh, precision=precision)
+    S.set_state(I.random_modal_state(mesh.N, 2, 9, seed=n, amp=0.1))
+    return S
+
+
+def dt_launches(S, steps=3):
+    S.set_timing(True)
+    S.run_steps(steps)
+    n = S.kernel_times()["k_dt"][1]
+    S.set_timing(False)
+    return n
+
+
+@pytest.mark.parametrize("precision", [L.FP64, L.FP32_MIXED])
+@pytest.mark.parametrize("n", [180, 182])  # 507 and 518 wavefronts: either side of 512 workgroups of 64
+def test_both_reductions_give_the_same_bits(n, precision):
+    out = []
+    for bs in (64, 128, 256):
+        S = solver(n, precision)
+        S.set_tune({"k_pre": bs})
+        S.run_steps(6)
+        out.append(S.get_state())
+        assert dt_launches(S) == (3 if n > 181 and bs == 64 else 0)
+    for Q, t in out[1:]:
+        assert np.array_equal(Q, out[0][0]) and t == out[0][1]
+
+
+@pytest.mark.parametrize("precision", [L.FP64, L.FP32_MIXED])
+def test_autotune_counts_the_reduction(precision):
+    """40,000 squares: 64 lanes are the fastest k_pre by a microsecond and bring a launch of 6 us with them."""
+    S = solver(200, precision)
+    S.autotune(20)
+    assert dt_launches(S) == 0

@@ -206,20 +206,22 @@ lxw_status lxw_refelem_info_deg(int32_t kind, int32_t degree, int32_t* n_pts, do
 
 /* Creates a solver on device 0 for mesh m (which must outlive it).  stream: a hipStream_t (null
  * for the default stream); every kernel of the solver runs on it.  Allocates all device memory
- * the step needs.  Device arrays use 32-bit indices: n_var * n_modes * n_elem and
- * 2 * q * n_var * n_edges (q = degree + 1 edge points in 2D, 1 in 1D) must not exceed 2^31 - 1 (about 89
- * million P2 triangles or 59 million Q2 quadrilaterals per solver).  Errors: LXW_ERR_ARG / LXW_ERR_UNSUPPORTED for bad parameters or a
- * mesh above that size, LXW_ERR_OOM, LXW_ERR_DEVICE. */
+ * that the step needs and that a state in host memory goes through (one state of the mesh, at most
+ * 64 MiB; a larger state crosses in pieces, twice when it is checked).  Device arrays use 32-bit
+ * indices: n_var * n_modes * n_elem and 2 * q * n_var * n_edges (q = degree + 1 edge points in 2D, 1
+ * in 1D) must not exceed 2^31 - 1 (about 89 million P2 triangles or 59 million Q2 quadrilaterals per
+ * solver).  Errors: LXW_ERR_ARG / LXW_ERR_UNSUPPORTED for bad parameters or a mesh above that size,
+ * LXW_ERR_OOM, LXW_ERR_DEVICE. */
 lxw_status lxw_solver_create(const lxw_mesh* m, const lxw_params* p, void* stream, lxw_solver** out);
 lxw_status lxw_solver_destroy(lxw_solver* s);
 
 /* Sets the state: Q as described above (host or device memory per flags) and the time t0.
  * Checks rho_bar >= eps0, p_bar > 0 and finiteness of every coefficient (LXW_ERR_STATE, naming
- * the first bad element in the caller's order).  With LXW_STATE_UNCHECKED in flags these host-side
- * checks are skipped (a state the caller already trusts, e.g. one read back from a solver of the
- * same mesh); the device-side checks of the next step still report a cell average that is not
- * positive (LXW_ERR_POSITIVITY) or not finite (LXW_ERR_NONFINITE), naming the element.
- * Synchronous. */
+ * the first bad element in the caller's order) before anything of the solver's state changes.
+ * With LXW_STATE_UNCHECKED in flags these checks are skipped (a state the caller already trusts,
+ * e.g. one read back from a solver of the same mesh); the checks of the next step still report a
+ * cell average that is not positive (LXW_ERR_POSITIVITY) or not finite (LXW_ERR_NONFINITE), naming
+ * the element.  Synchronous. */
 lxw_status lxw_set_state(lxw_solver* s, const double* Q, double t0, int32_t flags);
 
 /* Copies the state after the last completed step (shock-capturing limiter applied) into Q and

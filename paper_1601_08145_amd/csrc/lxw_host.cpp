@@ -863,8 +863,7 @@ struct lxw_solver {
   Scalars* sc = nullptr;       // [n_mesh], followed by *tail
   DevTail* tail = nullptr;
   int* perm = nullptr;         // [N] internal -> caller element (state transfer)
-  double* stage = nullptr;     // staging buffer of states in host memory
-  size_t stage_bytes = 0;
+  double* stage = nullptr;     // staging buffer of states in host memory (stage_rows)
   Scalars hsc{};
   bool debug = false;
   // diagnostics copies
@@ -901,7 +900,6 @@ struct lxw_solver {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (cap) (void)hipStreamDestroy(cap);
     for (auto& b : bufs) if (b.p) (void)hipFree(b.p);
-    if (stage) (void)hipFree(stage);
     for (auto& e : ev_pool) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
   }
   template <class T>
@@ -1171,29 +1169,12 @@ lxw_status sync_check(lxw_solver* S) {
   return LXW_OK;
 }
 
-// Rows of the caller's array that one piece of a state in host memory holds: the staging buffer is at
-// most 64 MiB (a state above that goes through it in pieces, so that the solver's device memory stays
-// that of the step).
-int stage_rows(const lxw_mesh& Mloc) {
-  const size_t row = (size_t)Mloc.V * Mloc.ML * sizeof(double);
-  return (int)std::min<size_t>((size_t)Mloc.N, std::max<size_t>(1, ((size_t)64 << 20) / row));
-}
-
-// Staging buffer of `bytes` for states in host memory (kept with the solver, grown when a larger mesh
-// of a batch needs it).
-lxw_status staging(lxw_solver* S, size_t bytes, double** out) {
-  if (S->stage_bytes < bytes) {
-    if (S->stage) HIPCHK(hipFree(S->stage));
-    S->stage = nullptr;
-    S->stage_bytes = 0;
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) return fail(LXW_ERR_OOM, std::string("device allocation failed: ") + hipGetErrorString(e));
-    S->stage = (double*)p;
-    S->stage_bytes = bytes;
-  }
-  *out = S->stage;
-  return LXW_OK;
+// Rows of n elements' states that one piece of a state in host memory holds.  The solver's staging buffer takes one
+// piece of its largest mesh, at most 64 MiB (a state above that goes through it in pieces); it is allocated with
+// the solver, so that setting and reading a state need no device memory.
+int stage_rows(const lxw_mesh& M, int n) {
+  const size_t row = (size_t)M.V * M.ML * sizeof(double);
+  return (int)std::min<size_t>((size_t)n, std::max<size_t>(1, ((size_t)64 << 20) / row));
 }
 
 // Checks a caller state of mesh Mloc (rho_bar >= eps0, p_bar > 0, finite) and brings it, in the
@@ -1206,12 +1187,8 @@ lxw_status load_state(lxw_solver* S, const lxw_mesh& Mloc, int off, const double
   HIPCHK(hipStreamSynchronize(nullptr));
   HIPCHK(hipStreamSynchronize(S->st));
   const bool dev = (flags & LXW_DEVICE_PTR) != 0;
-  const int rows = dev ? N : stage_rows(Mloc);
-  double* buf = nullptr;
-  if (!dev) {
-    lxw_status s = staging(S, (size_t)rows * row * sizeof(double), &buf);
-    if (s) return s;
-  }
+  const int rows = dev ? N : stage_rows(Mloc, N);
+  double* buf = S->stage;
   int staged = -1;  // first row the staging buffer holds
   auto piece = [&](int c0, int n) -> hipError_t {
     if (dev || staged == c0) return hipSuccess;
@@ -1266,12 +1243,8 @@ lxw_status store_state(lxw_solver* S, const lxw_mesh& Mloc, int off, double* Q, 
   const int N = Mloc.N, V = Mloc.V, ML = Mloc.ML, Nt = S->M->N;
   const size_t row = (size_t)V * ML;
   const bool dev = (flags & LXW_DEVICE_PTR) != 0;
-  const int rows = dev ? N : stage_rows(Mloc);
-  double* buf = nullptr;
-  if (!dev) {
-    lxw_status s = staging(S, (size_t)rows * row * sizeof(double), &buf);
-    if (s) return s;
-  }
+  const int rows = dev ? N : stage_rows(Mloc, N);
+  double* buf = S->stage;
   for (int c0 = 0; c0 < N; c0 += rows) {
     const int n = std::min(rows, N - c0);
     double* dst = dev ? Q : buf;
@@ -1435,6 +1408,9 @@ lxw_status create_solver(const lxw_mesh* m, const lxw_params* p, void* stream, B
   const int* perm = nullptr;
   if ((s = upload(S.get(), &perm, m->perm))) return s;
   S->perm = const_cast<int*>(perm);
+  int largest = 0;
+  for (int b = 0; b < S->n_mesh; ++b) largest = std::max(largest, S->eoff[b + 1] - S->eoff[b]);
+  if ((s = S->alloc(&S->stage, (size_t)stage_rows(*m, largest) * m->V * m->ML))) return s;
   if (S->fp32) s = setup_view<float>(S.get(), S->vf);
   else s = setup_view<double>(S.get(), S->vd);
   if (s) return s;

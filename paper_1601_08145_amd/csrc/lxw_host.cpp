@@ -1245,6 +1245,8 @@ lxw_status store_state(lxw_solver* S, const lxw_mesh& Mloc, int off, double* Q, 
   const bool dev = (flags & LXW_DEVICE_PTR) != 0;
   const int rows = dev ? N : stage_rows(Mloc, N);
   double* buf = S->stage;
+  // device memory of the caller may still be in use by work on the default stream
+  if (dev) HIPCHK(hipStreamSynchronize(nullptr));
   for (int c0 = 0; c0 < N; c0 += rows) {
     const int n = std::min(rows, N - c0);
     double* dst = dev ? Q : buf;

@@ -387,24 +387,7 @@ void fill_tab(RefTab<E, R>& T) {
   static const int D2[6][3] = {{2, 0, 0}, {1, 1, 0}, {1, 0, 1}, {0, 2, 0}, {0, 1, 1}, {0, 0, 2}};
   for (int p = 0; p < E::NP; ++p) {
     double xi[3] = {pts[p * E::DIM], E::DIM >= 2 ? pts[p * E::DIM + 1] : 0.0, E::DIM == 3 ? pts[p * E::DIM + 2] : 0.0};
-    if constexpr (E::DIM == 3) {
-      for (int l = 0; l < E::ML; ++l) {
-        T.phi[p][l] = R(B(l, xi, 0, 0, 0));
-        for (int a = 0; a < 3; ++a) T.dphi[p][a][l] = R(B(l, xi, a == 0, a == 1, a == 2));
-        for (int k = 0; k < 6; ++k) T.d2phi[p][k][l] = R(B(l, xi, D2[k][0], D2[k][1], D2[k][2]));
-      }
-      continue;
-    }
-    for (int l = 0; l < E::ML; ++l) {
-      T.phi[p][l] = R(B(l, xi, 0, 0));
-      T.dphi[p][0][l] = R(B(l, xi, 1, 0));
-      T.d2phi[p][0][l] = R(B(l, xi, 2, 0));
-      if constexpr (E::DIM == 2) {
-        T.dphi[p][1][l] = R(B(l, xi, 0, 1));
-        T.d2phi[p][1][l] = R(B(l, xi, 1, 1));
-        T.d2phi[p][2][l] = R(B(l, xi, 0, 2));
-      }
-    }
+    for (int l = 0; l < E::ML; ++l) T.phi[p][l] = R(B(l, xi, 0, 0));
   }
   for (int p = 0; p < E::NP; ++p)
     for (int d = 0; d < E::DIM; ++d) T.xr[p][d] = R(pts[p * E::DIM + d]);
@@ -1428,21 +1411,15 @@ lxw_status set_end_time(lxw_solver* S, double T) {
   return LXW_OK;
 }
 
-// Steps of a batch by the persistent kernel, at most 1024 per cooperative launch.
-template <class E, class R>
-lxw_status persistent_steps_t(lxw_solver* S, const View<R>& v, int64_t n_steps) {
-  for (int64_t k = 0; k < n_steps; k += 1024)
-    HIPCHK((launch_persistent<E, R>(v, S->cfg.persistent, S->st, S->n_mesh, (int)std::min<int64_t>(1024, n_steps - k))));
-  return LXW_OK;
-}
-
+// Steps of a batch of triangles by the persistent kernel, at most 1024 per cooperative launch.
 lxw_status persistent_steps(lxw_solver* S, int64_t n_steps) {
-  if (S->M->deg != 2) return fail(LXW_ERR_UNSUPPORTED, "the persistent kernel is for degree-2 batches");
-  switch (S->M->kind) {
-    case LXW_LINE: return S->fp32 ? persistent_steps_t<ElLine, float>(S, S->vf, n_steps) : persistent_steps_t<ElLine, double>(S, S->vd, n_steps);
-    case LXW_QUAD: return S->fp32 ? persistent_steps_t<ElQuad, float>(S, S->vf, n_steps) : persistent_steps_t<ElQuad, double>(S, S->vd, n_steps);
-    default: return S->fp32 ? persistent_steps_t<ElTri, float>(S, S->vf, n_steps) : persistent_steps_t<ElTri, double>(S, S->vd, n_steps);
+  if (ekind(*S->M) != EK_TRI) return fail(LXW_ERR_UNSUPPORTED, "the persistent kernel runs batches of triangle meshes only");
+  for (int64_t k = 0; k < n_steps; k += 1024) {
+    const int n = (int)std::min<int64_t>(1024, n_steps - k);
+    HIPCHK((S->fp32 ? launch_persistent<ElTri, float>(S->vf, S->cfg.persistent, S->st, n)
+                    : launch_persistent<ElTri, double>(S->vd, S->cfg.persistent, S->st, n)));
   }
+  return LXW_OK;
 }
 
 // Whether the steps run as one workgroup (a small single mesh, nothing recorded per kernel).

@@ -46,8 +46,6 @@ struct ElTet {
 template <class E, class R>
 struct RefTab {
   R phi[E::NP][E::ML];             // basis values
-  R dphi[E::NP][E::DIM][E::ML];    // reference gradient
-  R d2phi[E::NP][E::ND2][E::ML];   // reference second derivatives (xx[, xy, yy])
   R wphi[E::NI][E::ML];            // w_m phi_l(x_m): projection onto the basis
   R wdphi[E::NI][E::DIM][E::ML];   // w_m grad phi_l(x_m): volume term
   R kd0[E::NI][E::DIM];            // sum_l w_m phi_l(x_m) d phi_l/d xi_a (origin): the projection of
@@ -257,10 +255,10 @@ template <> struct SoloMax<ElLine3> { static constexpr int n = 512; };
 template <> struct SoloMax<ElTri> { static constexpr int n = 256; };
 template <class E, class R>
 hipError_t launch_solo(const View<R>& v, hipStream_t st, int n_steps);
-// n_steps whole steps of a batch (v.mesh_of set) in one cooperative launch of workgroups of bs
-// lanes (64, 128 or 256), as many as stay resident together; same results as the separate kernels.
+// n_steps whole steps of a batch of triangles (v.mesh_of set) in one cooperative launch of workgroups of bs
+// lanes (128 or 256), as many as stay resident together; same results as the separate kernels.
 template <class E, class R>
-hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mesh, int n_steps);
+hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_steps);
 
 // ---- state transfer (lxw_state.hip) -----------------------------------------------------------
 // Rows [c0, c1) of a caller's array Q[.][V][ML] (row c0 at Q) to and from elements off .. off + n of a

@@ -165,17 +165,6 @@ __device__ __forceinline__ void d2flux(const St<DIM, R>& s, int d, const R* a, c
   F[DIM + 1] = d2u * s.Ep + va.du[d] * (b[DIM + 1] + vb.dp) + vb.du[d] * (a[DIM + 1] + va.dp) + s.u[d] * d2p;
 }
 
-// H_d(a, a), the same terms with the two symmetric ones gathered
-template <int DIM, class R>
-__device__ __forceinline__ void d2flux_sym(const St<DIM, R>& s, int d, const R* a, const Var<DIM, R>& va, R d2p, R* F) {
-  const R du2 = R(2) * va.du[d];
-  const R d2u = -du2 * a[0] * s.r;
-  F[0] = R(0);
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) F[1 + k] = a[1 + k] * du2 + s.m[k] * d2u + (k == d ? d2p : R(0));
-  F[DIM + 1] = d2u * s.Ep + du2 * (a[DIM + 1] + va.dp) + s.u[d] * d2p;
-}
-
 template <int DIM, class R>
 __device__ __forceinline__ R d2p_of(const St<DIM, R>& s, const Var<DIM, R>& va, const Var<DIM, R>& vb, R gm1) {
   R t = R(0);
@@ -382,10 +371,10 @@ __device__ __forceinline__ void d3flux_sym(const St<DIM, R>& s, int d, const R* 
 // A is linear and H bilinear, so the terms are gathered as
 //   F + A (c1 q_t + c2 q_tt + c3 q_ttt) + H(q_t, c2 q_t + 3 c3 q_tt) + c3 F^(3)(q_t, q_t, q_t)
 // with c1 = dt/2, c2 = dt^2/6, c3 = dt^3/24: one Jacobian and one Hessian product per direction.
-template <int DIM, class R>
-__device__ __forceinline__ void ft4_core(const St<DIM, R>& s, const R* qt, const Var<DIM, R>& vt, const R* qtt,
-                                         const R* qttt, R gm1, R dt, R FT[DIM][DIM + 2]) {
-  constexpr int V = DIM + 2;
+template <class R>
+__device__ __forceinline__ void ft4_core(const St<1, R>& s, const R* qt, const Var<1, R>& vt, const R* qtt, const R* qttt,
+                                         R gm1, R dt, R* FT) {
+  constexpr int V = 3;
   const R c1 = R(0.5) * dt, c2 = dt * dt * R(1.0 / 6.0), c3 = dt * dt * dt * R(1.0 / 24.0);
   const R c33 = R(3) * c3;
   R qc[V], qh[V];
@@ -394,42 +383,28 @@ __device__ __forceinline__ void ft4_core(const St<DIM, R>& s, const R* qt, const
     qc[c] = c1 * qt[c] + c2 * qtt[c] + c3 * qttt[c];
     qh[c] = c2 * qt[c] + c33 * qtt[c];
   }
-  const Var<DIM, R> vc = var1<DIM, R>(s, qc, gm1);
-  const Var<DIM, R> vh = var1<DIM, R>(s, qh, gm1);
-  const R d2p = d2p_of<DIM, R>(s, vt, vh, gm1);
+  const Var<1, R> vc = var1<1, R>(s, qc, gm1), vh = var1<1, R>(s, qh, gm1);
+  R F[V], A[V], H[V], T3[V];
+  flux<1, R>(s, 0, F);
+  dflux<1, R>(s, 0, qc, vc, A);
+  d2flux<1, R>(s, 0, qt, vt, qh, vh, d2p_of<1, R>(s, vt, vh, gm1), H);
+  d3flux_sym<1, R>(s, 0, qt, vt, gm1, T3);
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) {
-    R F[V], A[V], H[V], T3[V];
-    flux<DIM, R>(s, d, F);
-    dflux<DIM, R>(s, d, qc, vc, A);
-    d2flux<DIM, R>(s, d, qt, vt, qh, vh, d2p, H);
-    d3flux_sym<DIM, R>(s, d, qt, vt, gm1, T3);
-#pragma unroll
-    for (int c = 0; c < V; ++c) FT[d][c] = F[c] + A[c] + H[c] + c3 * T3[c];
-  }
+  for (int c = 0; c < V; ++c) FT[c] = F[c] + A[c] + H[c] + c3 * T3[c];
 }
-template <int DIM, class R>
-__device__ __forceinline__ void ft4_from(const R* q, const R* qt, const R* qtt, const R* qttt, R gm1, R dt,
-                                         R FT[DIM][DIM + 2]) {
-  const St<DIM, R> s = base_state<DIM, R>(q, gm1);
-  ft4_core<DIM, R>(s, qt, var1<DIM, R>(s, qt, gm1), qtt, qttt, gm1, dt, FT);
+template <class R>
+__device__ __forceinline__ void ft4_from(const R* q, const R* qt, const R* qtt, const R* qttt, R gm1, R dt, R* FT) {
+  const St<1, R> s = base_state<1, R>(q, gm1);
+  ft4_core<R>(s, qt, var1<1, R>(s, qt, gm1), qtt, qttt, gm1, dt, FT);
 }
 
-// Pressure and wave speed (double, for the limiters and s).
+// Pressure (double, for the limiters).
 template <int DIM>
 __device__ __forceinline__ double pressure(const double* q, double gam) {
   double k = 0.0;
 #pragma unroll
   for (int d = 0; d < DIM; ++d) k += q[1 + d] * q[1 + d];
   return (gam - 1.0) * (q[DIM + 1] - 0.5 * k / q[0]);
-}
-
-template <int DIM>
-__device__ __forceinline__ double wave_speed(const double* q, double gam) {
-  double u2 = 0.0;
-#pragma unroll
-  for (int d = 0; d < DIM; ++d) u2 += (q[1 + d] / q[0]) * (q[1 + d] / q[0]);
-  return sqrt(u2) + sqrt(gam * pressure<DIM>(q, gam) / q[0]);
 }
 
 // Boundary operator of Sec. 2.4: keep the tangential momentum, negate the normal one.
@@ -1005,8 +980,6 @@ __device__ __forceinline__ void store_dt(Scalars& S, DevError* err, const StepDt
 // F^h is projected in contravariant form Fc_a = sum_d Jinv[a][d] F_d, so that div F^h =
 // sum_a d/dxi_a Fc_a^h and grad D follows from reference second derivatives (affine elements).
 // ---------------------------------------------------------------------------------------------
-// Waves per SIMD the register allocation of k_elem targets: two for float32 triangles (measured
-// faster: latency of the trace stores is hidden), one elsewhere (float64 would spill at two).
 // Stores V values of one record (consecutive, 16-byte aligned when V values fill whole 16-byte
 // words) with vector stores.
 template <class R, int V>
@@ -1457,25 +1430,23 @@ __device__ __forceinline__ void elem_affine(const View<R>& v, const int i, const
 
 // P2 on the line.
 template <class E, class RS>
-__device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const StepDt& D) {
+__device__ __forceinline__ void elem_line2(const View<RS>& v, const int i, const StepDt& D) {
   // The line computes in float64 whatever it stores: the same rate, few registers, and the rounding that is
   // the same in every step where the state is constant does not add up (FP32-mixed against float64 after
   // 60 steps of Riemann problems on 76 cells: 3.2e-7 against 7.4e-7 in float32; a step of 76 cells 7.9 / 7.2 us).
-  using R = std::conditional_t<E::DIM == 1, double, RS>;
-  constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
+  using R = double;
+  constexpr int V = 3, ML = 3, NI = E::NI;
   const RefTab<E, R>& T = TabSel<E, R>::get();
-  const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
   if (i >= N) return;
   // At the end time the step changes nothing: the stored modes are written back as they were.
   // The flag is applied at the store (not by an early return), so its load overlaps the others.
   const bool idle = D.idle;
-  const R dt = R(D.dt);
-  const R gm1 = R(v.gamma - 1.0);
+  const R dt = D.dt;
+  const R gm1 = v.gamma - 1.0;
 
   // stored modes (before the limiter) and the limiter factor theta of this step
-  double qb[V];
-  R Qr[V][ML - 1];
+  R qb[V], Qr[V][ML - 1];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
     qb[c] = v.Qbar[(size_t)i * V + c];
@@ -1483,127 +1454,88 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
 #pragma unroll
     for (int l = 1; l < ML; ++l) Qr[c][l - 1] = at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i);
   }
-  const double th = at(v.theta, i);
-  const R thR = R(th);
-  R Ji[DIM][DIM];
-#pragma unroll
-  for (int a = 0; a < DIM; ++a)
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) Ji[a][d] = at(v.Jinv + (size_t)(a * DIM + d) * N, i);
-  // scaled for q's gradients and for F^h (D comes out as c1 D, its gradient as c2 grad D), see Pt2
-  const R sg3 = dt * R(1.0 / 3.0), sc1 = R(0.5) * dt;
+  const R th = at(v.theta, i);
+  const R Ji = at(v.Jinv, i);
+  // scaled for q's gradient (dt/3) and for F^h (dt/2: D comes out as c1 D, its gradient as c2 grad D), see Pt2
+  const R sg3 = dt * (1.0 / 3.0), sc1 = 0.5 * dt;
 
   // point state of the limited polynomial
   auto state_at = [&](int p, R* q) {
 #pragma unroll
-    for (int c = 0; c < V; ++c)
-      q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return double(Qr[c][l - 1]); }, TD.phi[p])));
+    for (int c = 0; c < V; ++c) q[c] = limited(qb[c], th, deviation<ML>([&](int l) { return Qr[c][l - 1]; }, T.phi[p]));
   };
 
   // grad q and div F^h are linear and their derivatives constant, so they are formed once per element from
   // their values at the reference origin.
-  // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m)
-  R Fh[DIM][V][ML];
-  R D0[V], gDr[V][DIM];
-#pragma unroll
-  for (int a = 0; a < DIM; ++a)
-#pragma unroll
-    for (int c = 0; c < V; ++c)
-#pragma unroll
-      for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
-  for (int m = 0; m < NI; ++m) {
-    R q[V];
-    state_at(m, q);
-    St<DIM, R> s = base_state<DIM, R>(q, gm1);
-    R F[DIM][V];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) flux<DIM, R>(s, d, F[d]);
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R fc = R(0);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * F[d][c];
-        fc *= sc1;
-#pragma unroll
-        for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
-      }
-  }
-
-  R vol[V][ML - 1];
+  // Sec. 2.3 Step 1: Fc^h = sum_m w_m Fc(q(x_m)) phi_l(x_m)
+  R Fh[V][ML];
 #pragma unroll
   for (int c = 0; c < V; ++c)
 #pragma unroll
-    for (int l = 0; l < ML - 1; ++l) vol[c][l] = R(0);
-
-  R g0[V][DIM], Hq[V][E::ND2], gDx[DIM][V];
+    for (int l = 0; l < ML; ++l) Fh[c][l] = 0.0;
+  for (int m = 0; m < NI; ++m) {
+    R q[V], F[V];
+    state_at(m, q);
+    flux<1, R>(base_state<1, R>(q, gm1), 0, F);
+#pragma unroll
+    for (int c = 0; c < V; ++c) {
+      const R fc = Ji * F[c] * sc1;
+#pragma unroll
+      for (int l = 0; l < ML; ++l) Fh[c][l] += T.wphi[m][l] * fc;
+    }
+  }
+  // at the origin: D and its derivative, q's gradient and second derivative; the gradient of D along x
+  R D0[V], gDr[V], g0[V], Hq[V], gDx[V];
 #pragma unroll
   for (int c = 0; c < V; ++c) {
-    R dd = R(0), hh = R(0);  // div F^h and its derivative at the origin
+    D0[c] = gDr[c] = g0[c] = Hq[c] = 0.0;
 #pragma unroll
     for (int l = 0; l < ML; ++l) {
-      dd += Fh[0][c][l] * T.dphi0[0][l];
-      hh += Fh[0][c][l] * T.d2c[0][l];
-    }
-    D0[c] = dd;
-    gDr[c][0] = hh;
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-      R acc = R(0);
-#pragma unroll
-      for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.dphi0[a][l];
-      g0[c][a] = thR * acc;
+      D0[c] += Fh[c][l] * T.dphi0[0][l];
+      gDr[c] += Fh[c][l] * T.d2c[0][l];
     }
 #pragma unroll
-    for (int k = 0; k < E::ND2; ++k) {
-      R acc = R(0);
-#pragma unroll
-      for (int l = 1; l < ML; ++l) acc += Qr[c][l - 1] * T.d2c[k][l];
-      Hq[c][k] = thR * acc;
+    for (int l = 1; l < ML; ++l) {
+      g0[c] += Qr[c][l - 1] * T.dphi0[0][l];
+      Hq[c] += Qr[c][l - 1] * T.d2c[0][l];
     }
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      R sh = R(0);
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) sh += Ji[a][d] * gDr[c][a];
-      gDx[d][c] = sg3 * sh;
-    }
+    g0[c] *= th;
+    Hq[c] *= th;
+    gDx[c] = sg3 * (Ji * gDr[c]);
   }
 
   // Sec. 2.3 Step 2 at point p: q, grad q, D = div F^h, grad D, then q_t, q_tt and what F_T needs.
   auto derivs = [&](int p, R* q, R* qt, R* qtt) {
-    R gq[DIM][V], D[V], gD[DIM][V];
+    R gq[1][V], gD[1][V];
     state_at(p, q);
     const R x = T.xr[p][0];
 #pragma unroll
     for (int c = 0; c < V; ++c) {
-      D[c] = D0[c] + gDr[c][0] * x;
-      gq[0][c] = sg3 * (Ji[0][0] * (g0[c][0] + Hq[c][0] * x));
-      gD[0][c] = gDx[0][c];
+      qt[c] = -(D0[c] + gDr[c] * x);
+      gq[0][c] = sg3 * (Ji * (g0[c] + Hq[c] * x));
+      gD[0][c] = gDx[c];
     }
-#pragma unroll
-    for (int c = 0; c < V; ++c) qt[c] = -D[c];
-    const Pt2<DIM, R> s = pt2_of<DIM, R>(q, qt, gm1);
-    qtt_of<DIM, R>(s, q, qt, gq, gD, gm1, qtt);
+    const Pt2<1, R> s = pt2_of<1, R>(q, qt, gm1);
+    qtt_of<1, R>(s, q, qt, gq, gD, gm1, qtt);
     return s;
   };
 
   // interior points: volume term V_l = sum_m w_m grad phi_l . F_T
+  R vol[V][ML - 1];
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+#pragma unroll
+    for (int l = 0; l < ML - 1; ++l) vol[c][l] = 0.0;
   for (int m = 0; m < NI; ++m) {
-    R q[V], qt[V], qtt[V], FT[DIM][V];
-    const Pt2<DIM, R> s = derivs(m, q, qt, qtt);
-    ft2<DIM, R>(s, q, qt, qtt, gm1, FT);
+    R q[V], qt[V], qtt[V], FT[1][V];
+    const Pt2<1, R> s = derivs(m, q, qt, qtt);
+    ft2<1, R>(s, q, qt, qtt, gm1, FT);
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
+    for (int c = 0; c < V; ++c) {
+      const R fc = Ji * FT[0][c];
 #pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R fc = R(0);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * FT[d][c];
-#pragma unroll
-        for (int l = 1; l < ML; ++l) vol[c][l - 1] += T.wdphi[m][a][l] * fc;
-      }
+      for (int l = 1; l < ML; ++l) vol[c][l - 1] += T.wdphi[m][0][l] * fc;
+    }
   }
 
   // Sec. 2.3 Step 3 / Sec. 3.3 Step 6, volume part: Q^(l) += dt V_l for l >= 2.  Stored before the
@@ -1612,65 +1544,50 @@ __device__ __forceinline__ void elem_item2(const View<RS>& v, const int i, const
   for (int c = 0; c < V; ++c)
 #pragma unroll
     for (int l = 1; l < ML; ++l)
-      at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i) = RS(idle ? Qr[c][l - 1] : thR * Qr[c][l - 1] + dt * vol[c][l - 1]);
+      at(v.Qh + (size_t)(c * (ML - 1) + l - 1) * N, i) = RS(idle ? Qr[c][l - 1] : th * Qr[c][l - 1] + dt * vol[c][l - 1]);
   if (v.dbg_vol) {
 #pragma unroll
     for (int c = 0; c < V; ++c) {
       v.dbg_vol[(c * ML) * N + i] = 0.0;
 #pragma unroll
-      for (int l = 1; l < ML; ++l) v.dbg_vol[(c * ML + l) * N + i] = double(vol[c][l - 1]);
+      for (int l = 1; l < ML; ++l) v.dbg_vol[(c * ML + l) * N + i] = vol[c][l - 1];
     }
   }
 
-  // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
-  const double hs0 = 0.5 * D.s;
-  for (int k = 0; k < K; ++k) {
+  // ends: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary ends), |n| = 1
+  for (int k = 0; k < 2; ++k) {
     const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
-    R n[DIM], len2 = R(0);
+    const R n[1] = {R(at(v.nout + (size_t)k * N, i))};
+    const R hs = 0.5 * D.s * fabs(n[0]);
+    R q[V], qt[V], qtt[V], fn[V];
+    const Pt2<1, R> s = derivs(NI + k, q, qt, qtt);
+    ftn2<1, R>(s, q, qt, qtt, n, gm1, fn);
+    RS b[V];
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) { n[d] = at(v.nout + (size_t)(k * DIM + d) * N, i); len2 += n[d] * n[d]; }
-    // s |n_e| / 2: both elements of an edge hold the same normal up to sign, so they form it alike
-    const R hs = R(hs0 * double(sqrt(len2)));
-    for (int jl = 0; jl < NQE; ++jl) {
-      const int p = NI + k * NQE + jl;
-      // point order of i_e along the edge (reversed on the other side)
-      const int jj = side ? (NQE - 1 - jl) : jl;
-      R q[V], qt[V], qtt[V], fn[V];
-      const Pt2<DIM, R> s = derivs(p, q, qt, qtt);
-      ftn2<DIM, R>(s, q, qt, qtt, n, gm1, fn);
-      RS b[V];
+    for (int c = 0; c < V; ++c) b[c] = RS(0.5 * fn[c] + hs * q[c]);
+    store_rec<RS, V>(v.tr + ((size_t)e * 2 + side) * V, b);
+    if (bc != SB_INTERIOR) {
+      R qg[V], fgn[V];
+      if (bc == SB_TRANSPARENT) {
 #pragma unroll
-      for (int c = 0; c < V; ++c) b[c] = RS(R(0.5) * fn[c] + hs * q[c]);
-      store_rec<RS, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
-      if (bc != SB_INTERIOR) {
-        R qg[V], fgn[V];
-        if (bc == SB_TRANSPARENT) {
-#pragma unroll
-          for (int c = 0; c < V; ++c) { qg[c] = q[c]; fgn[c] = fn[c]; }
-        } else if (bc == SB_REFLECTIVE) {
-          R nh[DIM];
-          const R il = R(1) / sqrt(len2);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) nh[d] = n[d] * il;
-          R qtg[V], qttg[V];
-          reflect<DIM, R>(q, nh, qg);
-          reflect<DIM, R>(qt, nh, qtg);
-          reflect<DIM, R>(qtt, nh, qttg);
-          ftn_from<DIM, R>(qg, qtg, qttg, n, gm1, fgn);
-        } else {
-          R z[V];
-#pragma unroll
-          for (int c = 0; c < V; ++c) z[c] = R(0);
-          inflow_state<DIM, R>(v.inflow, qg);
-          ftn_from<DIM, R>(qg, z, z, n, gm1, fgn);
-        }
-        // the ghost is side 1: its outward normal is -n
-        RS bg[V];
-#pragma unroll
-        for (int c = 0; c < V; ++c) bg[c] = RS(hs * qg[c] - R(0.5) * fgn[c]);
-        store_rec<RS, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
+        for (int c = 0; c < V; ++c) { qg[c] = q[c]; fgn[c] = fn[c]; }
+      } else if (bc == SB_REFLECTIVE) {
+        R qtg[V], qttg[V];
+        reflect<1, R>(q, n, qg);
+        reflect<1, R>(qt, n, qtg);
+        reflect<1, R>(qtt, n, qttg);
+        ftn_from<1, R>(qg, qtg, qttg, n, gm1, fgn);
+      } else {
+        const R z[V] = {};
+        inflow_state<1, R>(v.inflow, qg);
+        ftn_from<1, R>(qg, z, z, n, gm1, fgn);
       }
+      // the ghost is side 1: its outward normal is -n
+      RS bg[V];
+#pragma unroll
+      for (int c = 0; c < V; ++c) bg[c] = RS(hs * qg[c] - 0.5 * fgn[c]);
+      store_rec<RS, V>(v.tr + ((size_t)e * 2 + 1) * V, bg);
     }
   }
 }
@@ -2447,18 +2364,16 @@ __device__ __forceinline__ void elem_tri3(const View<R>& v, const int i, const S
   }
 }
 
-// k_elem at degree 3 on the line.  The same steps as above
-// with the Taylor series of Sec. 2.2 carried one term further: F_T needs q_ttt = -div F_tt, which
-// takes the gradient of q_tt, hence the Hessians of q and of D = div F^h (constant for cubic F^h).
-// With D_e = d/dx_e D and q_e = d/dx_e q:
-//   q_t = -D,  q_tt = sum_d [H_d(q_d, D) + A_d D_d],
-//   d/dx_e q_tt = sum_d [F3_d(q_e, q_d, D) + H_d(q_ed, D) + H_d(q_d, D_e) + H_d(q_e, D_d) + A_d D_ed],
-//   q_ttt = -sum_d [F3_d(q_d, q_t, q_t) - 2 H_d(D_d, q_t) + H_d(q_d, q_tt) + A_d d/dx_d q_tt].
-// Gradients and Hessians are contracted per point from the reference tables (quadratic and linear
-// in the reference coordinates), the Hessian of D once per element.
+// P3 on the line.  The Taylor series of Sec. 2.2 one term further, through the variations of the flux: F_T needs
+// q_ttt = -F_tt,x, which takes the gradient of q_tt, hence the second derivatives of q and of D = (F^h)_x
+// (constant: F^h is cubic).  With subscripts x for derivatives along the line,
+//   q_t = -D,  q_tt = H(q_x, D) + A D_x,
+//   q_tt,x = F3(q_x, q_x, D) + H(q_xx, D) + 2 H(q_x, D_x) + A D_xx,
+//   q_ttt = -(F3(q_x, q_t, q_t) - 2 H(D_x, q_t) + H(q_x, q_tt) + A q_tt,x).
+// The point derivatives come from Taylor coefficients at the reference origin, formed once per element.
 template <class E, class R>
-__device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const StepDt& D) {
-  constexpr int V = E::V, ML = E::ML, DIM = E::DIM, NI = E::NI, K = E::K, NQE = E::NQE;
+__device__ __forceinline__ void elem_line3(const View<R>& v, const int i, const StepDt& D) {
+  constexpr int V = 3, ML = 4, NI = E::NI;
   const RefTab<E, R>& T = TabSel<E, R>::get();
   const RefTab<E, double>& TD = TabSel<E, double>::get();
   const int N = v.N;
@@ -2478,11 +2393,7 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
   }
   const double th = at(v.theta, i);
   const R thR = R(th);
-  R Ji[DIM][DIM];
-#pragma unroll
-  for (int a = 0; a < DIM; ++a)
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) Ji[a][d] = at(v.Jinv + (size_t)(a * DIM + d) * N, i);
+  const R Ji = at(v.Jinv, i);
 
   // point state of the limited polynomial in float64, then rounded to the bulk precision
   auto state_at = [&](int p, R* q) {
@@ -2490,210 +2401,86 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
     for (int c = 0; c < V; ++c)
       q[c] = R(limited(qb[c], th, deviation<ML>([&](int l) { return double(Qr[c][l - 1]); }, TD.phi[p])));
   };
-  // physical second derivatives from the reference ones (xx[, xy, yy] at index a + b)
-  auto map2 = [&](const R* hr, R out[DIM][DIM]) {
-#pragma unroll
-    for (int d = 0; d < DIM; ++d)
-#pragma unroll
-      for (int e = 0; e < DIM; ++e) {
-        R t = R(0);
-#pragma unroll
-        for (int a = 0; a < DIM; ++a)
-#pragma unroll
-          for (int b = 0; b < DIM; ++b) t += Ji[a][d] * Ji[b][e] * hr[a + b];
-        out[d][e] = t;
-      }
-  };
 
-  // Sec. 2.3 Step 1: Fc^h_a = sum_m w_m Fc_a(q(x_m)) phi_l(x_m)
-  constexpr int N2 = 2 * DIM - 1;
-  R Fh[DIM][V][ML];
-  R D0[V], gD0[V][DIM], HDr[V][N2];
+  // Sec. 2.3 Step 1: Fc^h = sum_m w_m Fc(q(x_m)) phi_l(x_m)
+  R Fh[V][ML];
 #pragma unroll
-  for (int a = 0; a < DIM; ++a)
+  for (int c = 0; c < V; ++c)
 #pragma unroll
-    for (int c = 0; c < V; ++c)
-#pragma unroll
-      for (int l = 0; l < ML; ++l) Fh[a][c][l] = R(0);
+    for (int l = 0; l < ML; ++l) Fh[c][l] = R(0);
   for (int m = 0; m < NI; ++m) {
-    R q[V];
+    R q[V], F[V];
     state_at(m, q);
-    St<DIM, R> s = base_state<DIM, R>(q, gm1);
-    R F[DIM][V];
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) flux<DIM, R>(s, d, F[d]);
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R fc = R(0);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * F[d][c];
-#pragma unroll
-        for (int l = 0; l < ML; ++l) Fh[a][c][l] += T.wphi[m][l] * fc;
-      }
-  }
-
-  // The point derivatives come from Taylor coefficients at the reference origin, formed once per
-  // element (reference derivative indices count the eta derivatives: second xx, xy, yy; third xxx,
-  // xxy, xyy, yyy): q is cubic, so its reference gradient is g0 + H0 x + T3[x, x]/2 and its
-  // reference Hessian H0 + T3 x; D = div F^h is quadratic, D0 + gD0 . x + x^T HDr x / 2, with
-  // reference gradient gD0 + HDr x and constant Hessian HDr (the physical HD).  The limiter
-  // factor theta is folded into q's coefficients.
-  R qg0[V][DIM], qH0[V][N2], qT3[V][E::ND3];
-  R HD[DIM][DIM][V];
-#pragma unroll
-  for (int c = 0; c < V; ++c) {
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-      R t = R(0), u = R(0);
-#pragma unroll
-      for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.dphi0[a][l];
-      qg0[c][a] = thR * t;
-#pragma unroll
-      for (int l = 0; l < ML; ++l)
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) u += Fh[b][c][l] * T.d2c[a + b][l];
-      gD0[c][a] = u;
-    }
-#pragma unroll
-    for (int j = 0; j < N2; ++j) {
-      R t = R(0), u = R(0);
-#pragma unroll
-      for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.d2c[j][l];
-      qH0[c][j] = thR * t;
-#pragma unroll
-      for (int l = 0; l < ML; ++l)
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) u += Fh[a][c][l] * T.d3c[a + j][l];
-      HDr[c][j] = u;
-    }
-#pragma unroll
-    for (int j = 0; j < E::ND3; ++j) {
-      R t = R(0);
-#pragma unroll
-      for (int l = 1; l < ML; ++l) t += Qr[c][l - 1] * T.d3c[j][l];
-      qT3[c][j] = thR * t;
-    }
-    R t0 = R(0);
-#pragma unroll
-    for (int l = 0; l < ML; ++l)
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) t0 += Fh[a][c][l] * T.dphi0[a][l];
-    D0[c] = t0;
-    R h[DIM][DIM];
-    map2(HDr[c], h);
-#pragma unroll
-    for (int d = 0; d < DIM; ++d)
-#pragma unroll
-      for (int e = 0; e < DIM; ++e) HD[d][e][c] = h[d][e];
-  }
-
-  auto point = [&](int p, R* q, R* qt, R* qtt, R* qttt, R FT[DIM][V]) {
-    R gq[DIM][V], Hq[DIM][DIM][V], D[V], gD[DIM][V];
-    state_at(p, q);
-    // the point's reference coordinates x and the quadratic monomials m2[j] (j eta factors), with
-    // the factor 1/2 of the Taylor series and the two orderings of a mixed product
-    R x[DIM], m2[N2];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) x[a] = T.xr[p][a];
-    if constexpr (DIM == 1) {
-      m2[0] = R(0.5) * x[0] * x[0];
-    } else {
-      m2[0] = R(0.5) * x[0] * x[0];
-      m2[1] = x[0] * x[1];
-      m2[2] = R(0.5) * x[1] * x[1];
-    }
+    flux<1, R>(base_state<1, R>(q, gm1), 0, F);
 #pragma unroll
     for (int c = 0; c < V; ++c) {
-      R g[DIM], hq[N2], gd[DIM];
-      R dd = D0[c];
+      const R fc = Ji * F[c];
 #pragma unroll
-      for (int j = 0; j < N2; ++j) dd += HDr[c][j] * m2[j];
-#pragma unroll
-      for (int a = 0; a < DIM; ++a) {
-        R t = qg0[c][a], u = gD0[c][a];
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) { t += qH0[c][a + b] * x[b]; u += HDr[c][a + b] * x[b]; }
-#pragma unroll
-        for (int j = 0; j < N2; ++j) t += qT3[c][a + j] * m2[j];
-        g[a] = t;
-        gd[a] = u;
-        dd += gD0[c][a] * x[a];
-      }
-#pragma unroll
-      for (int j = 0; j < N2; ++j) {
-        R t = qH0[c][j];
-#pragma unroll
-        for (int e = 0; e < DIM; ++e) t += qT3[c][j + e] * x[e];
-        hq[j] = t;
-      }
-      D[c] = dd;
-      R h[DIM][DIM];
-      map2(hq, h);
-#pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        R sg = R(0), sd = R(0);
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) { sg += Ji[a][d] * g[a]; sd += Ji[a][d] * gd[a]; }
-        gq[d][c] = sg;
-        gD[d][c] = sd;
-#pragma unroll
-        for (int e = 0; e < DIM; ++e) Hq[d][e][c] = h[d][e];
-      }
+      for (int l = 0; l < ML; ++l) Fh[c][l] += T.wphi[m][l] * fc;
     }
-    St<DIM, R> s = base_state<DIM, R>(q, gm1);
-    Var<DIM, R> vD = var1<DIM, R>(s, D, gm1);
-    Var<DIM, R> vq[DIM], vg[DIM];
+  }
+
+  // Taylor coefficients in the reference coordinate: q's first, second and third derivative (theta folded in),
+  // D, its first and second; HD the second derivative of D along x
+  R g0[V], h0[V], t3[V], D0[V], D1[V], D2[V], HD[V];
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      vq[d] = var1<DIM, R>(s, gq[d], gm1);
-      vg[d] = var1<DIM, R>(s, gD[d], gm1);
+  for (int c = 0; c < V; ++c) {
+    g0[c] = h0[c] = t3[c] = D0[c] = D1[c] = D2[c] = R(0);
+#pragma unroll
+    for (int l = 0; l < ML; ++l) {
+      D0[c] += Fh[c][l] * T.dphi0[0][l];
+      D1[c] += Fh[c][l] * T.d2c[0][l];
+      D2[c] += Fh[c][l] * T.d3c[0][l];
     }
 #pragma unroll
-    for (int c = 0; c < V; ++c) { qt[c] = -D[c]; qtt[c] = R(0); qttt[c] = R(0); }
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      R H[V], A[V];
-      d2flux<DIM, R>(s, d, gq[d], vq[d], D, vD, d2p_of<DIM, R>(s, vq[d], vD, gm1), H);
-      dflux<DIM, R>(s, d, gD[d], vg[d], A);
-#pragma unroll
-      for (int c = 0; c < V; ++c) qtt[c] += H[c] + A[c];
+    for (int l = 1; l < ML; ++l) {
+      g0[c] += Qr[c][l - 1] * T.dphi0[0][l];
+      h0[c] += Qr[c][l - 1] * T.d2c[0][l];
+      t3[c] += Qr[c][l - 1] * T.d3c[0][l];
     }
-    Var<DIM, R> vt;  // the variation of q_t = -D (var1 is linear)
+    g0[c] *= thR;
+    h0[c] *= thR;
+    t3[c] *= thR;
+    HD[c] = Ji * Ji * D2[c];
+  }
+
+  auto point = [&](int p, R* q, R* qt, R* qtt, R* qttt, R* FT) {
+    R gq[V], Hq[V], Dp[V], gD[V];
+    state_at(p, q);
+    const R x = T.xr[p][0], x2 = R(0.5) * x * x;
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) vt.du[d] = -vD.du[d];
+    for (int c = 0; c < V; ++c) {
+      Dp[c] = D0[c] + D2[c] * x2 + D1[c] * x;
+      gq[c] = Ji * (g0[c] + h0[c] * x + t3[c] * x2);
+      gD[c] = Ji * (D1[c] + D2[c] * x);
+      Hq[c] = Ji * Ji * (h0[c] + t3[c] * x);
+    }
+    const St<1, R> s = base_state<1, R>(q, gm1);
+    const Var<1, R> vD = var1<1, R>(s, Dp, gm1), vq = var1<1, R>(s, gq, gm1), vg = var1<1, R>(s, gD, gm1);
+    R H[V], A[V];
+    d2flux<1, R>(s, 0, gq, vq, Dp, vD, d2p_of<1, R>(s, vq, vD, gm1), H);
+    dflux<1, R>(s, 0, gD, vg, A);
+#pragma unroll
+    for (int c = 0; c < V; ++c) { qt[c] = -Dp[c]; qtt[c] = H[c] + A[c]; }
+    Var<1, R> vt;  // the variation of q_t = -D (var1 is linear)
+    vt.du[0] = -vD.du[0];
     vt.dp = -vD.dp;
-    Var<DIM, R> vtt = var1<DIM, R>(s, qtt, gm1);
+    const Var<1, R> vtt = var1<1, R>(s, qtt, gm1), vH = var1<1, R>(s, Hq, gm1), vHD = var1<1, R>(s, HD, gm1);
+    R t1[V], t2[V], t3v[V], t4[V], dq2[V];  // dq2 = q_tt,x
+    d3flux<1, R>(s, 0, gq, vq, gq, vq, Dp, vD, gm1, t1);
+    d2flux<1, R>(s, 0, Hq, vH, Dp, vD, d2p_of<1, R>(s, vH, vD, gm1), t2);
+    d2flux<1, R>(s, 0, gq, vq, gD, vg, d2p_of<1, R>(s, vq, vg, gm1), t3v);
+    dflux<1, R>(s, 0, HD, vHD, t4);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      // d/dx_d q_tt
-      R dq2[V];
+    for (int c = 0; c < V; ++c) dq2[c] = t1[c] + t2[c] + R(2) * t3v[c] + t4[c];
+    const Var<1, R> v2 = var1<1, R>(s, dq2, gm1);
+    d3flux<1, R>(s, 0, gq, vq, qt, vt, qt, vt, gm1, t1);
+    d2flux<1, R>(s, 0, gD, vg, qt, vt, d2p_of<1, R>(s, vg, vt, gm1), t2);
+    d2flux<1, R>(s, 0, gq, vq, qtt, vtt, d2p_of<1, R>(s, vq, vtt, gm1), t3v);
+    dflux<1, R>(s, 0, dq2, v2, t4);
 #pragma unroll
-      for (int c = 0; c < V; ++c) dq2[c] = R(0);
-#pragma unroll
-      for (int k = 0; k < DIM; ++k) {
-        R t1[V], t2[V], t3[V], t4[V], t5[V];
-        Var<DIM, R> vH = var1<DIM, R>(s, Hq[d][k], gm1);
-        Var<DIM, R> vHD = var1<DIM, R>(s, HD[d][k], gm1);
-        d3flux<DIM, R>(s, k, gq[d], vq[d], gq[k], vq[k], D, vD, gm1, t1);
-        d2flux<DIM, R>(s, k, Hq[d][k], vH, D, vD, d2p_of<DIM, R>(s, vH, vD, gm1), t2);
-        d2flux<DIM, R>(s, k, gq[k], vq[k], gD[d], vg[d], d2p_of<DIM, R>(s, vq[k], vg[d], gm1), t3);
-        d2flux<DIM, R>(s, k, gq[d], vq[d], gD[k], vg[k], d2p_of<DIM, R>(s, vq[d], vg[k], gm1), t4);
-        dflux<DIM, R>(s, k, HD[d][k], vHD, t5);
-#pragma unroll
-        for (int c = 0; c < V; ++c) dq2[c] += t1[c] + t2[c] + t3[c] + t4[c] + t5[c];
-      }
-      R t1[V], t2[V], t3[V], t4[V];
-      Var<DIM, R> v2 = var1<DIM, R>(s, dq2, gm1);
-      d3flux<DIM, R>(s, d, gq[d], vq[d], qt, vt, qt, vt, gm1, t1);
-      d2flux<DIM, R>(s, d, gD[d], vg[d], qt, vt, d2p_of<DIM, R>(s, vg[d], vt, gm1), t2);
-      d2flux<DIM, R>(s, d, gq[d], vq[d], qtt, vtt, d2p_of<DIM, R>(s, vq[d], vtt, gm1), t3);
-      dflux<DIM, R>(s, d, dq2, v2, t4);
-#pragma unroll
-      for (int c = 0; c < V; ++c) qttt[c] -= t1[c] - R(2) * t2[c] + t3[c] + t4[c];
-    }
-    ft4_core<DIM, R>(s, qt, vt, qtt, qttt, gm1, dt, FT);
+    for (int c = 0; c < V; ++c) qttt[c] = -(t1[c] - R(2) * t2[c] + t3v[c] + t4[c]);
+    ft4_core<R>(s, qt, vt, qtt, qttt, gm1, dt, FT);
   };
 
   R vol[V][ML - 1];
@@ -2702,18 +2489,14 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
 #pragma unroll
     for (int l = 0; l < ML - 1; ++l) vol[c][l] = R(0);
   for (int m = 0; m < NI; ++m) {
-    R q[V], qt[V], qtt[V], qttt[V], FT[DIM][V];
+    R q[V], qt[V], qtt[V], qttt[V], FT[V];
     point(m, q, qt, qtt, qttt, FT);
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
+    for (int c = 0; c < V; ++c) {
+      const R fc = Ji * FT[c];
 #pragma unroll
-      for (int c = 0; c < V; ++c) {
-        R fc = R(0);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fc += Ji[a][d] * FT[d][c];
-#pragma unroll
-        for (int l = 1; l < ML; ++l) vol[c][l - 1] += T.wdphi[m][a][l] * fc;
-      }
+      for (int l = 1; l < ML; ++l) vol[c][l - 1] += T.wdphi[m][0][l] * fc;
+    }
   }
 #pragma unroll
   for (int c = 0; c < V; ++c)
@@ -2729,68 +2512,38 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
     }
   }
 
-  // edge points: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary edges)
-  const double hs0 = 0.5 * D.s;
-  for (int k = 0; k < K; ++k) {
+  // ends: the trace n_out . F_T / 2 + hs q (and the ghost side's on boundary ends), |n| = 1
+  for (int k = 0; k < 2; ++k) {
     const int slot = at(v.eslot + (size_t)k * N, i);
     const int e = slot >> 3, side = (slot >> 2) & 1, bc = slot & 3;
-    R n[DIM], len2 = R(0);
+    const R n[1] = {at(v.nout + (size_t)k * N, i)};
+    const R hs = R(0.5 * D.s * double(fabs(n[0])));
+    R q[V], qt[V], qtt[V], qttt[V], FT[V], b[V];
+    point(NI + k, q, qt, qtt, qttt, FT);
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) { n[d] = at(v.nout + (size_t)(k * DIM + d) * N, i); len2 += n[d] * n[d]; }
-    const R hs = R(hs0 * double(sqrt(len2)));
-    for (int jl = 0; jl < NQE; ++jl) {
-      const int p = NI + k * NQE + jl;
-      const int jj = side ? (NQE - 1 - jl) : jl;
-      R q[V], qt[V], qtt[V], qttt[V], FT[DIM][V];
-      point(p, q, qt, qtt, qttt, FT);
-      R fn[V];
+    for (int c = 0; c < V; ++c) b[c] = R(0.5) * (n[0] * FT[c]) + hs * q[c];
+    store_rec<R, V>(v.tr + ((size_t)e * 2 + side) * V, b);
+    if (bc != SB_INTERIOR) {
+      R qg[V], FTg[V];
+      if (bc == SB_TRANSPARENT) {
 #pragma unroll
-      for (int c = 0; c < V; ++c) {
-        fn[c] = R(0);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) fn[c] += n[d] * FT[d][c];
+        for (int c = 0; c < V; ++c) { qg[c] = q[c]; FTg[c] = FT[c]; }
+      } else if (bc == SB_REFLECTIVE) {
+        R qtg[V], qttg[V], q3g[V];
+        reflect<1, R>(q, n, qg);
+        reflect<1, R>(qt, n, qtg);
+        reflect<1, R>(qtt, n, qttg);
+        reflect<1, R>(qttt, n, q3g);
+        ft4_from<R>(qg, qtg, qttg, q3g, gm1, dt, FTg);
+      } else {
+        const R z[V] = {};
+        inflow_state<1, R>(v.inflow, qg);
+        ft4_from<R>(qg, z, z, z, gm1, dt, FTg);
       }
-      R b[V];
+      R bg[V];  // the ghost is side 1: its outward normal is -n
 #pragma unroll
-      for (int c = 0; c < V; ++c) b[c] = R(0.5) * fn[c] + hs * q[c];
-      store_rec<R, V>(v.tr + (((size_t)e * 2 + side) * NQE + jj) * V, b);
-      if (bc != SB_INTERIOR) {
-        R qg[V], FTg[DIM][V];
-        if (bc == SB_TRANSPARENT) {
-#pragma unroll
-          for (int c = 0; c < V; ++c) qg[c] = q[c];
-#pragma unroll
-          for (int d = 0; d < DIM; ++d)
-#pragma unroll
-            for (int c = 0; c < V; ++c) FTg[d][c] = FT[d][c];
-        } else if (bc == SB_REFLECTIVE) {
-          R nh[DIM];
-          const R il = R(1) / sqrt(len2);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) nh[d] = n[d] * il;
-          R qtg[V], qttg[V], q3g[V];
-          reflect<DIM, R>(q, nh, qg);
-          reflect<DIM, R>(qt, nh, qtg);
-          reflect<DIM, R>(qtt, nh, qttg);
-          reflect<DIM, R>(qttt, nh, q3g);
-          ft4_from<DIM, R>(qg, qtg, qttg, q3g, gm1, dt, FTg);
-        } else {
-          R z[V];
-#pragma unroll
-          for (int c = 0; c < V; ++c) z[c] = R(0);
-          inflow_state<DIM, R>(v.inflow, qg);
-          ft4_from<DIM, R>(qg, z, z, z, gm1, dt, FTg);
-        }
-        R bg[V];  // the ghost is side 1: its outward normal is -n
-#pragma unroll
-        for (int c = 0; c < V; ++c) {
-          R f = R(0);
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) f += n[d] * FTg[d][c];
-          bg[c] = hs * qg[c] - R(0.5) * f;
-        }
-        store_rec<R, V>(v.tr + (((size_t)e * 2 + 1) * NQE + jj) * V, bg);
-      }
+      for (int c = 0; c < V; ++c) bg[c] = hs * qg[c] - R(0.5) * (n[0] * FTg[c]);
+      store_rec<R, V>(v.tr + ((size_t)e * 2 + 1) * V, bg);
     }
   }
 }
@@ -2798,10 +2551,10 @@ __device__ __forceinline__ void elem_item3(const View<R>& v, const int i, const 
 template <class E, class R>
 __device__ __forceinline__ void elem_step(const View<R>& v, const int i, const StepDt& D) {
   if constexpr (E::DEG == 3 && E::DIM == 2) elem_tri3<E, R>(v, i, D);
-  else if constexpr (E::DEG == 3) elem_item3<E, R>(v, i, D);
+  else if constexpr (E::DEG == 3) elem_line3<E, R>(v, i, D);
   else if constexpr (E::kind == ElTri::kind || E::DIM == 3) elem_affine<E, R>(v, i, D);
   else if constexpr (E::kind == ElQuad::kind) elem_quad<E, R>(v, i, D);
-  else elem_item2<E, R>(v, i, D);
+  else elem_line2<E, R>(v, i, D);
 }
 
 // whether element i is the first of its mesh
@@ -3305,9 +3058,9 @@ __global__ __launch_bounds__(256, (ElemShape<E, R>::waves)) void k_persist(View<
 }
 
 template <class E, class R>
-hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_mesh, int n_steps) {
+hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_steps) {
   if (bs != 128 && bs != 256) return hipErrorInvalidConfiguration;
-  if (!v.mesh_of || n_steps < 1 || E::kind != ElTri::kind) return hipErrorInvalidValue;
+  if (!v.mesh_of || n_steps < 1) return hipErrorInvalidValue;
   const void* fn = nullptr;
   switch ((v.theta_exact ? 1 : 0) + (v.s_avg ? 2 : 0)) {
     case 0: fn = reinterpret_cast<const void*>(&k_persist<E, R, 0>); break;
@@ -3474,9 +3227,9 @@ template hipError_t launch<EL, double>(KernelId, const View<double>&, const Laun
 template hipError_t launch<EL, float>(KernelId, const View<float>&, const LaunchCfg&, hipStream_t, int, int);
 template hipError_t launch_solo<EL, double>(const View<double>&, hipStream_t, int);
 template hipError_t launch_solo<EL, float>(const View<float>&, hipStream_t, int);
-#if LXW_PART < 3
-template hipError_t launch_persistent<EL, double>(const View<double>&, int, hipStream_t, int, int);
-template hipError_t launch_persistent<EL, float>(const View<float>&, int, hipStream_t, int, int);
+#if LXW_PART == 2
+template hipError_t launch_persistent<EL, double>(const View<double>&, int, hipStream_t, int);
+template hipError_t launch_persistent<EL, float>(const View<float>&, int, hipStream_t, int);
 #endif
 
 }  // namespace lxw

@@ -1447,8 +1447,8 @@ lxw_status solo_steps(lxw_solver* S, int64_t n_steps) {
   return LXW_OK;
 }
 
-// Enqueues n steps: one workgroup (a small mesh), the persistent kernel (a batch with that launch shape), replays of the captured
-// step graph, or eager launches while timing, stage read-out or graphs are off.
+// Enqueues n steps: one workgroup (a small mesh), the persistent kernel (a batch with that launch shape),
+// replays of the captured step graph, or eager launches while timing, stage read-out or graphs are off.
 lxw_status replay_steps(lxw_solver* S, int64_t n_steps) {
   if (S->batch && S->cfg.persistent && !S->timing && !S->debug && !S->ind) return persistent_steps(S, n_steps);
   if (solo(S)) return solo_steps(S, n_steps);

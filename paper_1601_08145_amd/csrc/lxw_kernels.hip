@@ -1032,10 +1032,10 @@ __device__ __forceinline__ R here(R x) {
 // The edges come before the volume term: the modes in float64 are dead by the time its accumulators live,
 // and are read again for the update.
 //
-// Bound by instruction issue: 3,840 VALU instructions per wavefront of float32 triangles (5,870 with
-// Jacobian and Hessian products, states evaluated mode by mode and every V_l accumulated at every point):
-// 168 -> 129 us on 999,698 triangles; float64 250k 78 -> 58 us; tetrahedra 467 -> 307 us (280k, FP32-mixed)
-// and 163 -> 104 us (25k, float64).
+// Bound by instruction issue: 4,020 VALU instructions per wavefront of float32 triangles (5,872 with
+// Jacobian and Hessian products and every V_l accumulated at every point): 168 -> 143 us on 999,698 triangles;
+// float64 250k 78 -> 62 us; tetrahedra 467 -> 310 us (280k, FP32-mixed) and 163 -> 108 us (25k, float64).
+// (States through monomials, whose positivity did not hold, took 3,838 instructions and 140 us; 58, 310, 104.)
 template <class E, class R>
 struct ElemShape {
   // interior states kept in LDS per lane, where four wavefronts per CU still fit (float64 tetrahedra form
@@ -1045,10 +1045,10 @@ struct ElemShape {
   static constexpr int lds = keep ? E::NI * E::V * (int)sizeof(R)
                                   : (E::kind == ElQuad::kind && sizeof(R) == 4 ? 16 * E::V * (int)sizeof(R) : 0);
   // Waves per SIMD the register allocation targets, the most that spill next to nothing: three for float32
-  // triangles (168 registers; 129 us on 999,698 against 138 at two), two for float64 triangles (58 / 65 us on
-  // 250k), float32 P3 triangles (138 / 184 us on 250k) and the float32 square (its LDS holds no third; 74 us on
-  // 262k with the modes and D in LDS, 135 with them in registers and 59 of those spilled), one elsewhere
-  // (float32 tetrahedra: their states fill the LDS with one; 307 us on 280k, 463 at two without them).
+  // triangles (168 registers; 143 us on 999,698 against 146 at two), two for float64 triangles (62 / 67 us on
+  // 250k), float32 P3 triangles (152 / 195 us on 250k) and the float32 square (its LDS holds no third; 80 us on
+  // 262k with the modes and D in LDS, 128 with them in registers), one elsewhere (float32 tetrahedra: their
+  // states fill the LDS with one; 310 us on 280k, 563 at two without them).
   static constexpr int waves = E::DIM != 2 || (sizeof(R) == 8 && E::ML > ElTri::ML) ? 1 : (sizeof(R) == 4 && E::ML == ElTri::ML ? 3 : 2);
 };
 
@@ -1599,7 +1599,7 @@ __device__ __forceinline__ void elem_line2(const View<RS>& v, const int i, const
 // both F^h at every point took 86.  F^h itself is kept only in the modes that div sees (6 of 9 per direction),
 // and the mass flux is its own projection.
 //
-// Bound by instruction issue.  512x512 squares FP32-mixed 108 -> 74 us, 123,300 in float64 120 -> 60 us.
+// Bound by instruction issue.  512x512 squares FP32-mixed 108 -> 79 us, 123,300 in float64 120 -> 62 us.
 template <class E, class R>
 __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const StepDt& D) {
   constexpr int V = 4, ML = 9, NQE = 3;
@@ -1883,9 +1883,9 @@ __device__ __forceinline__ void elem_quad(const View<R>& v, const int i, const S
 // a product's time average is a (b + b1 + b2 + b3) + a1 (b + 4/3 b1 + 3/2 b2) + a2 (b + 3/2 b1) + a3 b.
 // Second reference derivatives are indexed by their number of eta (0 xx, 1 xy, 2 yy), third ones likewise.
 //
-// Bound by instruction issue.  250,632 triangles: FP32-mixed 321 -> 138 us, with third variations of the
-// flux per direction and every gradient and Hessian mapped at every point before; float64 spilled 780 bytes a
-// lane and now nothing.
+// Bound by instruction issue.  250,632 triangles: FP32-mixed 321 -> 151 us, with third variations of the
+// flux per direction and every gradient and Hessian mapped at every point before (139 us with the states
+// through monomials, whose positivity did not hold); float64 spilled 780 bytes a lane and now nothing.
 template <class R>
 struct Pt3 {  // what F_T needs of a point besides q and its time derivatives
   R u2[2], p2, H2;  // c2 times the second time derivatives of u, p and H
@@ -2754,14 +2754,14 @@ __device__ double mu_solve(const double* qL, const double* qa, double gam, doubl
 // Bound by HBM: the traces and the modes in and out.  Each edge's fluxes are formed twice (by both
 // elements) so that no per-edge flux record is written and gathered again: on 999,698 triangles,
 // FP32-mixed, k_edge, k_flim and k_update (380 + 174 + 400 MB) took 67 + 43 + 88 us; k_flux and the new
-// k_update take 115 + 18 us.  Traces of an edge's two sides are one record (96 bytes here): the element
+// k_update (461 + 68 MB) take 120 + 19 us.  Traces of an edge's two sides are one record (96 bytes here): the element
 // that reads both touches one or two cache lines.
 // ---------------------------------------------------------------------------------------------
 // Faces one after another in a loop, their fluxes kept in LDS, or all unrolled, their fluxes in registers:
-// unrolled where every face's loads then fit the registers together (1D; float32 P2 triangles: 235
-// registers, 115 us on 999,698 against 126 us in the loop), the loop elsewhere (it needs no spill and
-// little code: float64 triangles 42 against 49 us on 250k, the float64 square 35 / 40 us on 123k, P3
-// 38 / 46 us on 250k, tetrahedra 133 / 182 us on 280k and 37 / 109 us in float64 on 25k).
+// unrolled where every face's loads then fit the registers together (1D; float32 P2 triangles: 191
+// registers, 120 us on 999,698 against 134 us in the loop), the loop elsewhere (it needs no spill and
+// little code: float64 triangles 46 against 50 us on 250k, the float64 square 36 / 41 us on 123k (FP32-mixed
+// 42 / 41 on 262k), P3 39 / 39.5 us on 250k, tetrahedra 112 / 138 us on 280k and 37 / 84 us in float64 on 25k).
 template <class E, class R>
 struct FluxShape {
   static constexpr bool roll = E::DIM > 1 && !(E::kind == ElTri::kind && E::DEG == 2 && sizeof(R) == 4);
@@ -3087,9 +3087,10 @@ hipError_t launch_persistent(const View<R>& v, int bs, hipStream_t st, int n_ste
 // ---------------------------------------------------------------------------------------------
 // k_solo: n_steps whole steps of a small mesh in one workgroup, its phases (the bodies of k_pre, k_elem,
 // k_flux, k_update) between workgroup barriers.  A step of separate launches takes 4 to 5 us per launch
-// whatever the mesh.  Per step, here against separate launches: 200 cells in float64 8.6 / 19.6 us (512:
-// 12.0 / 20.9, 1024: 22.2 / 21.2), P3 13.0 / 23.1 (512: 20.1 / 24.9, 1024: 36.8 / 25.0), 242 triangles 28.1 /
-// 40.4 us (512: 42.3 / 41.5); hence the limits in SoloMax.
+// whatever the mesh.  Per step, here against separate launches: 200 cells in float64 8.5 / 19.5 us (512:
+// 11.9 / 21.4, 1024: 21.8 / 21.3), P3 12.8 / 23.0 (512: 19.6 / 25.1, 1024: 36.1 / 24.9), 242 triangles 28.7 /
+// 42.0 us (512: 43.3 / 44.0, FP32-mixed 30.4 / 37.3); hence the limits in SoloMax,
+// one for both precisions.
 // The wave speed is reduced in LDS and t, dt and s stay in registers; the mesh's scalars are read once and
 // written once.
 // ---------------------------------------------------------------------------------------------

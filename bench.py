@@ -52,11 +52,11 @@ STEP_BYTES_PER_ELEM = 228
 # div F^h, grad div F^h and F_T at 16 points, volume term, traces.  Counted from the kernel's
 # executed VALU instructions per wavefront (64 triangles): fp32 FMA x 2 + fp32 add + fp32 mul +
 # fp64 FMA x 2 + fp64 add + fp64 mul, divided by 64 (profiles/lxw_kernels_tri_c3_counters.md).
-KELEM_FLOPS_PER_ELEM = 6.13e3
+KELEM_FLOPS_PER_ELEM = 6.36e3
 # The bound k_elem actually meets: VALU instruction issue.  Executed VALU instructions per wavefront
 # of 64 triangles (SQ_INSTS_VALU / SQ_WAVES, same counter file); a wave64 VALU instruction occupies a
 # 16-lane SIMD for 4 cycles, and the chip has 256 CUs x 4 SIMDs at 2.4 GHz.
-KELEM_VALU_INSTS_PER_WAVE = 3838
+KELEM_VALU_INSTS_PER_WAVE = 4020
 VALU_SIMDS, CLOCK_GHZ = 1024, 2.4
 # Bytes k_elem must move per triangle (FP32-mixed): cell averages in (4 x f64), higher modes in
 # (20 x f32), limiter factor (f64), geometry (Jinv 4 x f32, outward normals 6 x f32, edge slots
@@ -69,9 +69,9 @@ def kelem_bytes_per_elem(rsize):
 # HBM traffic of one launch of each step kernel on the 2D triangle workload (FP32-mixed) from
 # rocprofv3 counters (FETCH_SIZE x 2 + WRITE_SIZE, scale factors from a copy of known size), valid
 # only for the kernel source it was measured on.
-TRAFFIC = {"src_sha256": "f8f34bfca1a77eac7c9709f1d402ea216096359d04f8f47576f8b5a36e212487",
-           "bytes_per_launch": {"k_pre": 135326413, "k_elem": 597375283, "k_edge": 460419482,
-                                "k_update": 68331520}}  # profiles/lxw_kernels_tri_c3_counters.md
+TRAFFIC = {"src_sha256": "4e5dd142e64fb54ead9191bb63649a1b34622081f8ec77562f8f92d4b72437b1",
+           "bytes_per_launch": {"k_pre": 136955344, "k_elem": 592315648, "k_edge": 461180304,
+                                "k_update": 68331328}}  # profiles/lxw_kernels_tri_c3_counters.md
 
 
 def traffic_valid():

@@ -43,5 +43,5 @@ def test_both_reductions_give_the_same_bits(n, precision):
 def test_autotune_counts_the_reduction(precision):
     """40,000 squares: 64 lanes are the fastest k_pre by a microsecond and bring a launch of 6 us with them."""
     S = solver(200, precision)
-    S.autotune(20)
+    S.autotune(100)
     assert dt_launches(S) == 0
